@@ -175,6 +175,8 @@ __global__ __launch_bounds__(1024) void batch_finish_kernel(int mode, const doub
     const int quarter = static_cast<int>(threadIdx.x >> 8);
     const int q0 = s0 + (s1 - s0) * quarter / 4, q1 = s0 + (s1 - s0) * (quarter + 1) / 4;
     __shared__ double sq[3][6][256];
+    __shared__ uint32_t n_acc;  // accepted so far (their list: acc.list[b np ..])
+    if (threadIdx.x == 0) n_acc = 0u;
     for (int64_t base = 0; base < np; base += 256) {
         const int64_t i = base + (threadIdx.x & 255);
         const bool valid = i < np;
@@ -232,8 +234,8 @@ __global__ __launch_bounds__(1024) void batch_finish_kernel(int mode, const doub
                 if (w0 + 1 < fw) fbits[b * fw + w0 + 1] = static_cast<uint32_t>(m >> 32);
             }
         }
-        // accepted trials listed (as instance * np + slot) for
-        // batch_materialize_kernel, with the flags from before the selection
+        // accepted trials or candidates listed per instance for the
+        // materialise kernels, with the flags from before the selection
         if (quarter == 0 && mode == 2 && acc.list != nullptr) {
             const int lane = threadIdx.x & 63;
             const uint64_t mo = __ballot(fl_old != 0u);
@@ -244,14 +246,15 @@ __global__ __launch_bounds__(1024) void batch_finish_kernel(int mode, const doub
                 if (w0 + 1 < fw) acc.fbits_prev[b * fw + w0 + 1] = static_cast<uint32_t>(mo >> 32);
             }
             uint32_t basec = 0;
-            if (lane == 0 && am != 0) basec = atomicAdd(acc.cnt, static_cast<uint32_t>(__popcll(am)));
+            if (lane == 0 && am != 0) basec = atomicAdd(&n_acc, static_cast<uint32_t>(__popcll(am)));
             basec = static_cast<uint32_t>(__shfl(static_cast<int>(basec), 0));
             if (accepted)
-                acc.list[basec + static_cast<uint32_t>(__popcll(am & ((uint64_t(1) << lane) - 1)))] =
-                    static_cast<int32_t>(static_cast<int64_t>(b) * np + i);
+                acc.list[static_cast<int64_t>(b) * np + basec +
+                         static_cast<uint32_t>(__popcll(am & ((uint64_t(1) << lane) - 1)))] = static_cast<int32_t>(i);
         }
         __syncthreads();  // sq is refilled for the next 256 genomes
     }
+    if (threadIdx.x == 0 && mode == 2 && acc.list != nullptr) acc.cnt[b] = n_acc;
     if (mode == 1 || mode == 2) {
         __syncthreads();
         block_top3<T, 1024>(fb, np, Lb);
@@ -298,150 +301,89 @@ __global__ __launch_bounds__(256) void batch_init_kernel(int64_t np, const InstD
 
 // DE: tiles (instance, chunk of CW = 256 / IPW genes) dealt round-robin to
 // the XCDs (workgroup id mod 8); a workgroup makes R passes over groups of
-// 4 IPW consecutive individuals of one tile, loading the rows of pass r + 1
-// before storing the trials of pass r. Each row's buffer flag comes from
-// the instance's packed flags (np / 32 words, np <= 4096), copied to LDS
-// first, instead of a dependent global load after the draw.
-template <int IPW, int R>
+// 4 IPW consecutive individuals of one tile (de_rows). Each row's buffer flag
+// comes from the instance's packed flags (np / 32 words, np <= 4096), copied
+// to LDS first, instead of a dependent global load after the draw. Bound by
+// the row reads (16 B per gene, a quarter of them from HBM): 32 designs of
+// 26,000 domains on average, NP = 256, bits only: 219 us with 4 passes, 276 us
+// with 1; 306-343 us with 1 pass when the row pointers sat in LDS (their
+// loads then were flat ones, waited for all at once).
+template <int IPW, int R, typename OFF>
 __global__ __launch_bounds__(256) void batch_de_kernel(BatchPop bp, const InstDesc *__restrict__ inst,
                                                        const Tile *__restrict__ tiles, int ntiles, int groups,
                                                        const int4 *__restrict__ draws, float F, uint32_t cr_max,
                                                        uint32_t k0, uint32_t k1, const uint32_t *__restrict__ gen,
                                                        uint32_t inst0, uint32_t *__restrict__ bits, int64_t ld,
-                                                       const uint32_t *__restrict__ fbits, int store_genes,
-                                                       uint32_t *__restrict__ reset_cnt)
+                                                       const uint32_t *__restrict__ fbits, int store_genes)
 {
-    constexpr int LPI = 64 / IPW;
-    if (reset_cnt != nullptr && blockIdx.x == 0 && threadIdx.x == 0) reset_cnt[0] = 0u;
-    constexpr int CW = 4 * LPI;
-    constexpr int WPC = CW / 32;
-    constexpr int IPG = 4 * IPW;
-    constexpr int IPB = R * IPG;
-    static_assert(IPB * WPC <= 256, "one bit word per thread at the end");
+    constexpr int IPB = 4 * IPW * R;
     const uint32_t blk = blockIdx.x;
-    const int xcd = static_cast<int>(blk & 7u);
     const int k = static_cast<int>(blk >> 3);
     const int gi = k % groups;
-    const int ti = xcd + 8 * (k / groups);
+    const int ti = static_cast<int>(blk & 7u) + 8 * (k / groups);
     if (ti >= ntiles) return;
     const Tile tl = tiles[ti];
     const InstDesc id = inst[tl.inst];
-    const PopView pv = view_of(bp, id, tl.inst);
+    const int64_t np = bp.np;
     const int t = threadIdx.x;
-    const int local = t / LPI, li = t % LPI;
-    const int64_t np = bp.np, D = id.n;
-    const int64_t i0 = static_cast<int64_t>(gi) * IPB + local;
-    const int64_t j0 = static_cast<int64_t>(tl.chunk) * CW + 4 * li;
-    const uint32_t g = gen[0];
-    const uint32_t instb = inst0 + static_cast<uint32_t>(tl.inst);
-    __shared__ uint32_t wsh[IPB][WPC];
     __shared__ uint32_t sfb[128];
-    // per individual of the workgroup: its target row, three donor rows and
-    // output row, and jrand, worked out once by one lane (lane t < IPB
-    // takes individual gi IPB + t) instead of by every lane of every pass
-    __shared__ const float *srow[IPB][4];
-    __shared__ float *sout[IPB];
-    __shared__ int sjr[IPB];
-    bool act[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) act[r] = i0 + r * IPG < np && j0 < D;
-    const int64_t ip = static_cast<int64_t>(gi) * IPB + t;
-    int4 d4 = make_int4(0, 0, 0, 0);
-    if (t < IPB) d4 = draws[static_cast<int64_t>(tl.inst) * np + (ip < np ? ip : np - 1)];
     const int fw = static_cast<int>((np + 31) / 32);
+    int4 d = make_int4(0, 0, 0, 0);
+    if (t < IPB) d = draws[tl.inst * np + min(static_cast<int64_t>(gi) * IPB + t, np - 1)];
     if (t < fw) sfb[t] = fbits[static_cast<int64_t>(tl.inst) * fw + t];
     __syncthreads();
-    auto second = [&](int64_t r) -> bool { return ((sfb[r >> 5] >> (r & 31)) & 1u) != 0u; };
-    auto src = [&](int64_t r) -> const float * { return (second(r) ? pv.x1 : pv.x0) + r * pv.ldx; };
-    if (t < IPB && ip < np) {
-        srow[t][0] = src(ip);
-        srow[t][1] = src(d4.x);
-        srow[t][2] = src(d4.y);
-        srow[t][3] = src(d4.z);
-        sout[t] = (second(ip) ? pv.out0 : pv.out1) + ip * pv.ldx;
-        sjr[t] = d4.w;
-    }
-    __syncthreads();
-    // two row buffers used alternately by the unrolled passes (no register
-    // copy between passes)
-    float4 buf0[4], buf1[4];
-    auto load = [&](int r, float4 *v) {
-        if (act[r]) {
-            const float *const *rw = srow[r * IPG + local];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) v[m] = *reinterpret_cast<const float4 *>(rw[m] + j0);
-        }
-    };
-    load(0, buf0);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float4 *cur = (r & 1) ? buf1 : buf0;
-        if (r + 1 < R) load(r + 1, (r & 1) ? buf0 : buf1);
-        uint32_t nib = 0;
-        if (act[r]) {
-            const int64_t i = i0 + r * IPG;
-            const float4 uv = de_quad(cur[0], cur[1], cur[2], cur[3], j0, sjr[r * IPG + local], static_cast<uint32_t>(i),
-                                      g, instb, k0, k1, F, cr_max);
-            if (store_genes) store_quad_nt(sout[r * IPG + local], j0, D, uv);
-            nib = quad_nibble(uv, j0, D);
-        }
-        const uint32_t w = or8_into_last(nib << (4 * (t & 7)));
-        if ((t & 7) == 7) wsh[r * IPG + local][li >> 3] = w;
-    }
-    __syncthreads();
-    if (t < IPB * WPC) {
-        const int wd = t / IPB, ii = t % IPB;
-        const int64_t row = static_cast<int64_t>(gi) * IPB + ii;
-        const int64_t wg = static_cast<int64_t>(tl.chunk) * WPC + wd;
-        if (row < np && wg * 32 < D) bits[(id.wofs + wg) * ld + row] = wsh[ii][wd];
-    }
+    de_rows<IPW, R, OFF>(view_of(bp, id, tl.inst), gi, tl.chunk, F, cr_max, gen[0],
+                         inst0 + static_cast<uint32_t>(tl.inst), k0, k1, bits + id.wofs * ld, ld, store_genes != 0, d,
+                         [&](int r) -> bool { return ((sfb[r >> 5] >> (r & 31)) & 1u) != 0u; });
 }
 
-// The accepted trials of a batched run whose DE step stored only bits:
-// entry e = b np + i of list[0 .. cnt) is slot i of instance b; its trial
-// genes are computed again exactly as batch_de_kernel computed them, from
-// the rows before the selection (fb_old: the instance's packed flags before
-// it), and written to the buffer the selection made current. Work items
-// (chunk of 256 genes, entry), chunk c on XCD c mod 8, walked chunk by
-// chunk; chunks past an instance's genes are skipped.
+// The accepted trials of a batched run whose DE step stored only bits: the
+// entries list[0 .. cnt[b]) of instance b's list are slots whose trial genes
+// are computed again exactly as batch_de_kernel computed them, from the rows
+// before the selection (fb_old: the instance's packed flags before it), and
+// written to the buffer the selection made current. Grid: x = shares of the
+// list, y = tile (instance, 1024-gene chunk); a thread keeps one gene quad
+// (and its Philox head) and walks its share of the list.
 __global__ __launch_bounds__(256) void batch_materialize_kernel(BatchPop bp, const InstDesc *__restrict__ inst,
+                                                                const Tile *__restrict__ tiles,
                                                                 const int4 *__restrict__ draws,
                                                                 const uint32_t *__restrict__ fb_old, float F,
                                                                 uint32_t cr_max, uint32_t k0, uint32_t k1,
                                                                 const uint32_t *__restrict__ gen, uint32_t inst0,
                                                                 const int32_t *__restrict__ list,
-                                                                const uint32_t *__restrict__ cnt, int64_t n_inst,
-                                                                int64_t max_chunks)
+                                                                const uint32_t *__restrict__ cnt)
 {
+    const Tile tl = tiles[blockIdx.y];
     const int64_t np = bp.np;
-    const int64_t n_acc = min(static_cast<int64_t>(cnt[0]), n_inst * np);
+    const uint32_t n_acc = min(cnt[tl.inst], static_cast<uint32_t>(np));
+    if (blockIdx.x >= n_acc) return;
+    const InstDesc id = inst[tl.inst];
+    const int64_t q = static_cast<int64_t>(tl.chunk) * 256 + threadIdx.x, j0 = 4 * q;
+    if (j0 >= id.n) return;
     const uint32_t g = gen[0];
-    const int xcd = static_cast<int>(blockIdx.x & 7u);
-    const int64_t wg_per_xcd = gridDim.x / 8;  // the grid is a multiple of 8
-    const int64_t my_chunks = max_chunks > xcd ? (max_chunks - xcd + 7) / 8 : 0;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t fw = (np + 31) / 32;
-    for (int64_t it = static_cast<int64_t>(blockIdx.x >> 3) * 4 + wave; it < n_acc * my_chunks;
-         it += wg_per_xcd * 4) {
-        const int64_t c = xcd + 8 * (it / n_acc);
-        const int64_t e = list[it % n_acc];
-        if (e < 0 || e >= n_inst * np) continue;
-        const int b = static_cast<int>(e / np);
-        const int64_t i = e % np;
-        const InstDesc id = inst[b];
-        const int64_t j0 = c * 256 + 4 * lane;
-        if (j0 >= id.n) continue;
-        const uint32_t *fo = fb_old + b * fw;
-        auto old = [&](int64_t r) -> bool { return ((fo[r >> 5] >> (r & 31)) & 1u) != 0u; };
-        auto src = [&](int64_t r) -> const float * { return (old(r) ? bp.x1 : bp.x0) + id.xofs + r * id.ldx; };
-        const int4 dr = draws[e];
-        const float4 xv = *reinterpret_cast<const float4 *>(src(i) + j0);
-        const float4 a = *reinterpret_cast<const float4 *>(src(dr.x) + j0);
-        const float4 bq = *reinterpret_cast<const float4 *>(src(dr.y) + j0);
-        const float4 cq = *reinterpret_cast<const float4 *>(src(dr.z) + j0);
-        const float4 uv = de_quad(xv, a, bq, cq, j0, dr.w, static_cast<uint32_t>(i), g,
-                                  inst0 + static_cast<uint32_t>(b), k0, k1, F, cr_max);
-        store_quad_nt((old(i) ? bp.out0 : bp.out1) + id.xofs + i * id.ldx, j0, id.n, uv);
+    const uint32_t *fo = fb_old + tl.inst * fw;
+    const int32_t *lb = list + tl.inst * np;
+    const int4 *db = draws + tl.inst * np;
+    const float *const x0 = bp.x0 + id.xofs + j0;
+    float *const out0 = bp.out0 + id.xofs;
+    const int64_t dx = bp.x1 - bp.x0, ldx = id.ldx;  // (the outputs are the same two buffers)
+    auto src = [&](int32_t r) -> const float * {
+        return x0 + (r * ldx + (((fo[r >> 5] >> (r & 31)) & 1u) != 0u ? dx : 0));
+    };
+    const PhiloxHead h = philox10_head(static_cast<uint32_t>(q), g,
+                                       ((inst0 + static_cast<uint32_t>(tl.inst)) << 8) | kTagDeCr, k0, k1);
+    for (uint32_t ir = blockIdx.x; ir < n_acc; ir += gridDim.x) {
+        const int32_t i = lb[ir];
+        if (i < 0 || i >= np) continue;
+        const int4 dr = db[i];
+        const bool old = ((fo[i >> 5] >> (i & 31)) & 1u) != 0u;
+        const float4 v[4] = {*reinterpret_cast<const float4 *>(src(i)), *reinterpret_cast<const float4 *>(src(dr.x)),
+                             *reinterpret_cast<const float4 *>(src(dr.y)),
+                             *reinterpret_cast<const float4 *>(src(dr.z))};
+        const float4 uv = de_quad_shared(h, philox10_individual(static_cast<uint32_t>(i), g, k0), v,
+                                         dr.w - static_cast<int>(j0), k0, k1, F, cr_max);
+        store_quad_nt(out0 + (i * ldx + (old ? 0 : dx)), j0, id.n, uv);
     }
 }
 
@@ -870,7 +812,8 @@ struct qpm_batch_run_s {
     qpm_run_config cfg{};
     hipStream_t st = nullptr;
     int64_t ld = 0;
-    float *buf[2] = {nullptr, nullptr};
+    float *buf[2] = {nullptr, nullptr};  // one allocation
+    size_t gene_bytes = 0;               // of each buffer
     uint32_t *flags = nullptr;
     uint32_t *fbits = nullptr;  // flags packed one bit per individual, ceil(np / 32) words per instance
     void *f_cur = nullptr;
@@ -888,10 +831,9 @@ struct qpm_batch_run_s {
     // accepted-only trials (as in a single-design run): the DE step writes
     // bits only, the finish lists accepted slots, a kernel recomputes them
     bool lazy = false;
-    int32_t *acc_list = nullptr;   // n_inst np entries
-    uint32_t *acc_cnt = nullptr;
+    int32_t *acc_list = nullptr;   // np entries per instance
+    uint32_t *acc_cnt = nullptr;   // entries in use per instance
     uint32_t *fbits_prev = nullptr;
-    int64_t max_chunks = 0;        // 256-gene chunks of the largest instance
     BatchFitPlan fplan;
     FitPlanDev fdev;
     hipGraph_t graph = nullptr;
@@ -914,7 +856,6 @@ static void release_batch_run(qpm_batch_run_s *r)
     if (r->exec) (void)hipGraphExecDestroy(r->exec);
     if (r->graph) (void)hipGraphDestroy(r->graph);
     (void)hipFree(r->buf[0]);
-    (void)hipFree(r->buf[1]);
     (void)hipFree(r->fbits);
     (void)hipFree(r->flags);
     (void)hipFree(r->f_cur);
@@ -951,16 +892,25 @@ static qpm_status launch_batch_de(qpm_batch_run_s *r, int ipw, int passes)
     const unsigned nb = static_cast<unsigned>(blocks);
     const BatchPop bp = r->pop();
     const int gr = static_cast<int>(groups);
-#define QPM_BDE(I, P)                                                                                       \
-    batch_de_kernel<I, P><<<nb, 256, 0, r->st>>>(bp, r->inst, tiles, ntiles, gr, r->draws, c.F,             \
-                                                 cr_threshold(c.CR), k0, k1, r->gen, c.inst, r->bits, r->ld, \
-                                                 r->fbits, r->lazy ? 0 : 1, r->lazy ? r->acc_cnt : nullptr)
+    // byte offsets of an instance's rows over both buffers fit 32 bits
+    const bool near = 2 * r->gene_bytes < (size_t(1) << 32);
+#define QPM_BDE(I, P)                                                                                           \
+    {                                                                                                           \
+        if (near)                                                                                               \
+            batch_de_kernel<I, P, uint32_t><<<nb, 256, 0, r->st>>>(bp, r->inst, tiles, ntiles, gr, r->draws, c.F, \
+                                                                   cr_threshold(c.CR), k0, k1, r->gen, c.inst,  \
+                                                                   r->bits, r->ld, r->fbits, r->lazy ? 0 : 1);  \
+        else                                                                                                    \
+            batch_de_kernel<I, P, uint64_t><<<nb, 256, 0, r->st>>>(bp, r->inst, tiles, ntiles, gr, r->draws, c.F, \
+                                                                   cr_threshold(c.CR), k0, k1, r->gen, c.inst,  \
+                                                                   r->bits, r->ld, r->fbits, r->lazy ? 0 : 1);  \
+    }
     if (ipw == 1) {
-        if (passes == 1) { QPM_BDE(1, 1); } else if (passes == 2) { QPM_BDE(1, 2); } else { QPM_BDE(1, 4); }
+        if (passes == 1) QPM_BDE(1, 1) else if (passes == 2) QPM_BDE(1, 2) else QPM_BDE(1, 4)
     } else if (ipw == 2) {
-        if (passes == 1) { QPM_BDE(2, 1); } else if (passes == 2) { QPM_BDE(2, 2); } else { QPM_BDE(2, 4); }
+        if (passes == 1) QPM_BDE(2, 1) else if (passes == 2) QPM_BDE(2, 2) else QPM_BDE(2, 4)
     } else {
-        if (passes == 1) { QPM_BDE(4, 1); } else if (passes == 2) { QPM_BDE(4, 2); } else { QPM_BDE(4, 4); }
+        if (passes == 1) QPM_BDE(4, 1) else if (passes == 2) QPM_BDE(4, 2) else QPM_BDE(4, 4)
     }
 #undef QPM_BDE
     QPM_TRY_HIP(hipGetLastError());
@@ -984,6 +934,14 @@ static qpm_status launch_batch_gwo(qpm_batch_run_s *r)
     return QPM_OK;
 }
 
+// grid of the materialise kernels: list shares x tiles, about 16 workgroups
+// per CU
+static dim3 materialize_grid(const qpm_batch_run_s *r)
+{
+    const int64_t shares = std::min<int64_t>(r->cfg.np, std::max<int64_t>(1, 4096 / r->n_gtiles));
+    return dim3(static_cast<unsigned>(shares), static_cast<unsigned>(r->n_gtiles));
+}
+
 static qpm_status batch_generation(qpm_batch_run_s *r, hipEvent_t *ev = nullptr)
 {
     const qpm_run_config &c = r->cfg;
@@ -1005,9 +963,9 @@ static qpm_status batch_generation(qpm_batch_run_s *r, hipEvent_t *ev = nullptr)
                                                           : AcceptOut{}))
     if (r->lazy) {  // the accepted trials' genes (timed with the finish)
         const uint32_t k0 = static_cast<uint32_t>(c.seed), k1 = static_cast<uint32_t>(c.seed >> 32);
-        batch_materialize_kernel<<<2048, 256, 0, r->st>>>(r->pop(), r->inst, r->draws, r->fbits_prev, c.F,
-                                                          cr_threshold(c.CR), k0, k1, r->gen, c.inst, r->acc_list,
-                                                          r->acc_cnt, r->bt->n_inst, r->max_chunks);
+        batch_materialize_kernel<<<materialize_grid(r), 256, 0, r->st>>>(r->pop(), r->inst, r->gtiles, r->draws,
+                                                                         r->fbits_prev, c.F, cr_threshold(c.CR), k0,
+                                                                         k1, r->gen, c.inst, r->acc_list, r->acc_cnt);
         QPM_TRY_HIP(hipGetLastError());
     }
     QPM_STEP(QPM_K_GWO, launch_batch_gwo(r))
@@ -1192,6 +1150,8 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
             for (int64_t ch = 0; ch * cw < h[i].n; ++ch) dt[v].push_back(Tile{i, static_cast<int>(ch)});
         }
     }
+    r->de_passes = de_passes((c.np + 4 * r->de_ipw - 1) / (4 * r->de_ipw) *
+                             static_cast<int64_t>(dt[r->de_ipw == 1 ? 0 : (r->de_ipw == 2 ? 1 : 2)].size()));
     // accepted-only trials: recomputing an accepted trial reads 20 B per
     // gene against 4 B per gene for storing every trial, so they pay below
     // about 20 % acceptance and for large populations; chosen automatically,
@@ -1203,7 +1163,7 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
     r->lazy = c.trials == QPM_TRIALS_ACCEPTED ||
               (c.trials == QPM_TRIALS_AUTO && 2 * static_cast<int64_t>(sizeof(float)) * c.np * total_n >
                                                   (int64_t(64) << 20));
-    if (r->lazy && n_inst * c.np >= (int64_t(1) << 31)) {  // list entries are int32 instance * np + slot
+    if (r->lazy && n_inst * c.np >= (int64_t(1) << 31)) {  // (a limit of the accepted-only trials)
         if (c.trials == QPM_TRIALS_ACCEPTED) {
             set_error("accepted-only trials need n_inst * np < 2^31");
             release_batch_run(r);
@@ -1211,7 +1171,6 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
         }
         r->lazy = false;
     }
-    for (const auto &d : h) r->max_chunks = std::max<int64_t>(r->max_chunks, (d.n + 255) / 256);
     if (gt.size() > 65535) {  // the GWO and init grids put these chunks on gridDim.y
         set_error("too many 1024-gene chunks over the batch (%zu > 65535)", gt.size());
         release_batch_run(r);
@@ -1220,8 +1179,10 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
     r->n_gtiles = static_cast<int>(gt.size());
     for (int v = 0; v < 3; ++v) r->n_dtiles[v] = static_cast<int>(dt[v].size());
     hipError_t e = hipStreamCreateWithFlags(&r->st, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipMalloc(&r->buf[0], gene_bytes);
-    if (e == hipSuccess) e = hipMalloc(&r->buf[1], gene_bytes);
+    // both gene buffers in one allocation: row offsets count from the first
+    if (e == hipSuccess) e = hipMalloc(&r->buf[0], 2 * gene_bytes);
+    if (e == hipSuccess) r->buf[1] = r->buf[0] + xofs;
+    r->gene_bytes = gene_bytes;
     if (e == hipSuccess) e = hipMalloc(&r->flags, sizeof(uint32_t) * n_inst * c.np);
     if (e == hipSuccess) e = hipMalloc(&r->fbits, sizeof(uint32_t) * n_inst * ((c.np + 31) / 32));
     if (e == hipSuccess) e = hipMalloc(&r->f_cur, (r->f64() ? 8 : 4) * n_inst * c.np);
@@ -1229,7 +1190,7 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
     if (e == hipSuccess) e = hipMalloc(&r->leaders, sizeof(int32_t) * 3 * n_inst);
     if (e == hipSuccess) e = hipMalloc(&r->draws, sizeof(int4) * n_inst * c.np);
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_list, sizeof(int32_t) * n_inst * c.np);
-    if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_cnt, sizeof(uint32_t));
+    if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_cnt, sizeof(uint32_t) * n_inst);
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->fbits_prev, sizeof(uint32_t) * n_inst * ((c.np + 31) / 32));
     if (e == hipSuccess) e = hipMalloc(&r->gen, sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc(&r->a_tab, sizeof(float) * c.generations);
@@ -1261,7 +1222,6 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
     if (e == hipSuccess) e = hipMemsetAsync(r->flags, 0, sizeof(uint32_t) * n_inst * c.np, r->st);
     if (e == hipSuccess) e = hipMemsetAsync(r->fbits, 0, sizeof(uint32_t) * n_inst * ((c.np + 31) / 32), r->st);
     if (e == hipSuccess) e = hipMemsetAsync(r->gen, 0, sizeof(uint32_t), r->st);
-    if (e == hipSuccess && r->lazy) e = hipMemsetAsync(r->acc_cnt, 0, sizeof(uint32_t), r->st);
     if (e == hipSuccess) e = hipMemsetAsync(r->bits, 0, sizeof(uint32_t) * b->total_words * r->ld, r->st);
     if (e == hipSuccess) e = hipStreamSynchronize(r->st);
     if (ev) (void)hipEventDestroy(ev);

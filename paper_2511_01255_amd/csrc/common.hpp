@@ -239,7 +239,6 @@ struct PopView {
 
 qpm_status launch_init(int64_t np, int64_t D, int64_t ldx, uint64_t seed, uint32_t inst, float *x,
                        uint32_t *bits, int64_t ld, hipStream_t s);
-// draws: device scratch of np int4 (donors r1, r2, r3 and jrand)
 // Crossover threshold on a raw Philox word w: (w >> 8) 2^-24 <= CR holds
 // exactly when (w >> 8) <= T = floor(CR 2^24) (CR 2^24 is exact), that is
 // when w <= 256 T + 255.
@@ -250,12 +249,24 @@ inline uint32_t cr_threshold(float CR)
     return static_cast<uint32_t>(t) * 256u + 255u;
 }
 
-// ipw: individuals per wave of the DE kernel (1, 2 or 4; 0 = chosen from np);
-// passes: groups of individuals per workgroup (1, 2 or 4); fbits: optional
+// Passes of a DE workgroup over groups of individuals, from the number of
+// (group, gene chunk) pairs: a workgroup's set-up (draws, flags and row
+// offsets before the first row is read) is spread over its passes as long as
+// enough workgroups are left to fill the chip. Accepted-only DE step,
+// individuals per wave as chosen below, 1 / 2 / 4 / 8 passes: N = 10^4, NP =
+// 4096 58.5 / 50.3 / 43.9 / 42.7 us; N = 10^4, NP = 1024 19.1 / 17.7 / 16.1 /
+// 16.0 us; N = 3001, NP = 700 (2100 pairs) 9.4 / 8.8 / 8.8 / 9.4 us; N = 660,
+// NP = 500 (375 pairs) 7.2 / 7.3 / 7.5 / 8.9 us.
+inline int de_passes(int64_t pairs) { return pairs >= 4096 ? 4 : (pairs >= 1024 ? 2 : 1); }
+
+// draws: the DE draws of the generation for every individual, or nullptr
+// (each workgroup then draws for its own); ipw: individuals per wave of the
+// DE kernel (1, 2 or 4; 0 = chosen from np); passes: groups of individuals
+// per workgroup (1, 2 or 4; 0 = chosen from the sizes); fbits: optional
 // packed copy of pv.flags (bit i % 32 of word i / 32)
 qpm_status launch_de(const PopView &pv, float F, float CR, uint64_t seed, const uint32_t *gen_dev,
-                     uint32_t gen, uint32_t inst, uint32_t *bits, int64_t ld, int4 *draws, bool compute_draws,
-                     hipStream_t s, int ipw = 0, int passes = 1, const uint32_t *fbits = nullptr,
+                     uint32_t gen, uint32_t inst, uint32_t *bits, int64_t ld, const int4 *draws,
+                     hipStream_t s, int ipw = 0, int passes = 0, const uint32_t *fbits = nullptr,
                      const float *F_tab = nullptr, bool store_genes = true, uint32_t *reset_cnt = nullptr);
 // store_genes = false: the DE kernel writes the trials' bits only (and
 // zeroes reset_cnt); launch_materialize then writes the genes of the

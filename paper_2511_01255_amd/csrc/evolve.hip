@@ -67,14 +67,15 @@ __global__ __launch_bounds__(256) void de_draws_kernel(int64_t np, int64_t D, ui
 // slice of the whole population (np x CW x 4 bytes, chosen <= 2 MB) stays in
 // the XCD's L2 and the random donor rows hit it.
 //
-// Each row's buffer is named by its flag. PACKED (a run's population: the
-// two buffers are one allocation, x1 = x0 + np ldx, out0 = x0, out1 = x1,
-// np <= 65536, ldx < 2^24): the workgroup first copies the flags, packed one
-// bit per individual, to LDS; row r of buffer b is then row r + b np of one
-// array, addressed with 24-bit multiplies, so a donor address costs an LDS
-// read and a few ALU operations instead of a second dependent global load.
-// Otherwise the flags (if any) are read from global memory.
-template <int IPW, int R, bool PACKED>
+// The set-up of a workgroup (draws, flags, row offsets) is two dependent
+// loads and two barriers before its first row is read, so the number of
+// passes it is spread over sets the speed (see de_passes).
+//
+// Where a row lives: STAGED, the flags, if any (fbits: packed one bit per
+// individual, np <= 65536), are copied to LDS first, so a donor's buffer
+// costs an LDS read instead of a second dependent global load, and row
+// offsets fit 32 bits. Otherwise the flags are read from global memory.
+template <int IPW, int R, bool STAGED>
 __global__ __launch_bounds__(256) void de_kernel(PopView pv, const int4 *__restrict__ draws,
                                                  const uint32_t *__restrict__ fbits, float F,
                                                  const float *__restrict__ F_tab, uint32_t cr_max,
@@ -83,130 +84,38 @@ __global__ __launch_bounds__(256) void de_kernel(PopView pv, const int4 *__restr
                                                  int64_t ld, int groups, int chunks, int store_genes,
                                                  uint32_t *__restrict__ reset_cnt)
 {
-    constexpr int LPI = 64 / IPW;  // lanes per individual
-    constexpr int CW = 4 * LPI;    // genes per chunk
-    constexpr int WPC = CW / 32;   // bit words per chunk and individual
-    constexpr int IPG = 4 * IPW;   // individuals per workgroup pass
-    constexpr int IPB = R * IPG;   // individuals per workgroup
-    static_assert(IPB * WPC <= 256, "one bit word per thread at the end");
+    extern __shared__ uint32_t sfb[];  // STAGED with flags: (np + 31) / 32 flag words
     const uint32_t b = blockIdx.x;
-    const int xcd = static_cast<int>(b & 7u);
     const int k = static_cast<int>(b >> 3);
     const int gi = k % groups;
-    const int c = xcd + 8 * (k / groups);
+    const int c = static_cast<int>(b & 7u) + 8 * (k / groups);
     if (c >= chunks) return;
-    const int t = threadIdx.x;
-    const int local = t / LPI;  // individual within a pass
-    const int li = t % LPI;     // lane within the individual
     const int64_t D = pv.D, np = pv.np;
-    const int64_t i0 = static_cast<int64_t>(gi) * IPB + local;
-    const int64_t j0 = static_cast<int64_t>(c) * CW + 4 * li;
     const uint32_t g = gen_dev ? gen_dev[0] : gen_c;
     const float Fg = F_tab ? F_tab[g] : F;  // a run's per-generation F
     // a run without stored trials: the list counter of the accepted trials
     // starts at 0 for this generation (the finish step appends to it)
     if (reset_cnt != nullptr && b == 0 && threadIdx.x == 0) reset_cnt[0] = 0u;
-    __shared__ uint32_t wsh[IPB][WPC];
-    extern __shared__ uint32_t sfb[];  // PACKED: (np + 31) / 32 flag words
-    // PACKED: per individual of the workgroup, the float offsets from x0 of
-    // its target row, its three donor rows and its output row, and jrand,
-    // worked out once by one lane instead of by every lane of every pass
-    __shared__ uint64_t soff[PACKED ? IPB : 1][5];
-    __shared__ int sjr[PACKED ? IPB : 1];
-    int4 dr[PACKED ? 1 : R];
-    bool act[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) act[r] = i0 + r * IPG < np && j0 < D;
-    const uint32_t np32 = static_cast<uint32_t>(np), ldx24 = static_cast<uint32_t>(pv.ldx) & 0xFFFFFFu;
-    // PACKED: float offset of row r of buffer (flag of r) ^ flip from x0
-    auto packed_row = [&](int64_t r, uint32_t flip) -> uint64_t {
-        const uint32_t rr = static_cast<uint32_t>(r);
-        const uint32_t b = ((sfb[rr >> 5] >> (rr & 31u)) & 1u) ^ flip;
-        const uint32_t row = (rr + b * np32) & 0xFFFFFFu;
-        return static_cast<uint64_t>(row) * ldx24;
-    };
-    if constexpr (PACKED) {
-        // lane t < IPB loads the draws of individual gi IPB + t; the load is
-        // in flight while the flags are staged
-        const int64_t ip = static_cast<int64_t>(gi) * IPB + t;
-        int4 d4 = make_int4(0, 0, 0, 0);
-        if (t < IPB) d4 = draws[ip < np ? ip : np - 1];
-        for (int k = t; k < static_cast<int>((np + 31) / 32); k += 256) sfb[k] = fbits[k];
-        __syncthreads();
-        if (t < IPB && ip < np) {
-            soff[t][0] = packed_row(ip, 0u);
-            soff[t][1] = packed_row(d4.x, 0u);
-            soff[t][2] = packed_row(d4.y, 0u);
-            soff[t][3] = packed_row(d4.z, 0u);
-            soff[t][4] = packed_row(ip, 1u);
-            sjr[t] = d4.w;
+    // (the entry point passes no draws: each workgroup draws for its own);
+    // the load is in flight while the flags are staged
+    constexpr int IPB = 4 * IPW * R;
+    int4 d = make_int4(0, 0, 0, 0);
+    if (threadIdx.x < IPB) {
+        const int64_t ip = min(static_cast<int64_t>(gi) * IPB + threadIdx.x, np - 1);
+        d = draws ? draws[ip] : de_draw(ip, np, D, g, inst, k0, k1);
+    }
+    if constexpr (STAGED) {
+        if (fbits != nullptr) {
+            for (int w = threadIdx.x; w < static_cast<int>((np + 31) / 32); w += 256) sfb[w] = fbits[w];
+            __syncthreads();
         }
-        __syncthreads();
+        de_rows<IPW, R, uint32_t>(
+            pv, gi, c, Fg, cr_max, g, inst, k0, k1, bits, ld, store_genes != 0, d,
+            [&](int r) -> bool { return fbits != nullptr && ((sfb[r >> 5] >> (r & 31)) & 1u) != 0u; });
     } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t i = i0 + r * IPG;
-            dr[r] = draws[i < np ? i : np - 1];
-        }
-    }
-    auto second = [&](int64_t r) -> bool { return pv.flags != nullptr && pv.flags[r] != 0u; };
-    auto src = [&](int64_t r) -> const float * { return (second(r) ? pv.x1 : pv.x0) + r * pv.ldx; };
-    // two row buffers used alternately by the passes (the pass loop is
-    // unrolled, so each pass names its buffers statically and the next
-    // pass's rows load without a register copy)
-    float4 buf0[4], buf1[4];
-    auto load = [&](int r, float4 *v) {
-        if (act[r]) {
-            if constexpr (PACKED) {
-                const uint64_t *o = soff[r * IPG + local];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) v[m] = *reinterpret_cast<const float4 *>(pv.x0 + o[m] + j0);
-            } else {
-                const int64_t i = i0 + r * IPG;
-                v[0] = *reinterpret_cast<const float4 *>(src(i) + j0);
-                v[1] = *reinterpret_cast<const float4 *>(src(dr[r].x) + j0);
-                v[2] = *reinterpret_cast<const float4 *>(src(dr[r].y) + j0);
-                v[3] = *reinterpret_cast<const float4 *>(src(dr[r].z) + j0);
-            }
-        }
-    };
-    load(0, buf0);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float4 *cur = (r & 1) ? buf1 : buf0;
-        if (r + 1 < R) load(r + 1, (r & 1) ? buf0 : buf1);
-        uint32_t nib = 0;
-        if (act[r]) {
-            const int64_t i = i0 + r * IPG;
-            int jrand;
-            if constexpr (PACKED)
-                jrand = sjr[r * IPG + local];
-            else
-                jrand = dr[r].w;
-            const float4 uv = de_quad(cur[0], cur[1], cur[2], cur[3], j0, jrand, static_cast<uint32_t>(i), g, inst, k0,
-                                      k1, Fg, cr_max);
-            if (store_genes) {
-                float *dst;
-                if constexpr (PACKED)
-                    dst = pv.out0 + soff[r * IPG + local][4];
-                else
-                    dst = (second(i) ? pv.out0 : pv.out1) + i * pv.ldx;
-                store_quad_nt(dst, j0, D, uv);
-            }
-            nib = quad_nibble(uv, j0, D);
-        }
-        // merge the nibbles of 8 neighbouring lanes (32 genes) into one word
-        const uint32_t w = or8_into_last(nib << (4 * (t & 7)));
-        if ((t & 7) == 7) wsh[r * IPG + local][li >> 3] = w;
-    }
-    __syncthreads();
-    // the IPB consecutive individuals of this workgroup share each bit row:
-    // one contiguous store of IPB words per chunk word
-    if (t < IPB * WPC) {
-        const int wd = t / IPB, ii = t % IPB;
-        const int64_t row = static_cast<int64_t>(gi) * IPB + ii;
-        const int64_t wg = static_cast<int64_t>(c) * WPC + wd;
-        if (row < np && wg * 32 < D) bits[wg * ld + row] = wsh[ii][wd];
+        de_rows<IPW, R, uint64_t>(
+            pv, gi, c, Fg, cr_max, g, inst, k0, k1, bits, ld, store_genes != 0, d,
+            [&](int r) -> bool { return pv.flags != nullptr && pv.flags[r] != 0u; });
     }
 }
 
@@ -506,48 +415,51 @@ qpm_status launch_init(int64_t np, int64_t D, int64_t ldx, uint64_t seed, uint32
 }
 
 qpm_status launch_de(const PopView &pv, float F, float CR, uint64_t seed, const uint32_t *gen_dev, uint32_t gen,
-                     uint32_t inst, uint32_t *bits, int64_t ld, int4 *draws, bool compute_draws, hipStream_t s,
+                     uint32_t inst, uint32_t *bits, int64_t ld, const int4 *draws, hipStream_t s,
                      int ipw_req, int passes, const uint32_t *fbits, const float *F_tab, bool store_genes,
                      uint32_t *reset_cnt)
 {
     QPM_REQUIRE(F_tab == nullptr || gen_dev != nullptr, QPM_EINVAL, "an F table needs the device generation");
     QPM_REQUIRE(store_genes || fbits != nullptr, QPM_EINVAL, "trials that are not stored need the packed flags");
-    // the packed-flag path: one allocation for both buffers, flags staged
-    // in LDS (at most 65536 individuals, 8 KB), 24-bit row arithmetic
-    const bool packed = fbits != nullptr && pv.np <= 65536 && pv.ldx < (int64_t(1) << 24) &&
-                        pv.x1 == pv.x0 + pv.np * pv.ldx && pv.out0 == pv.x0 && pv.out1 == pv.x1;
-    const size_t lds = packed ? sizeof(uint32_t) * static_cast<size_t>((pv.np + 31) / 32) : 0;
+    // flags (if any) staged in LDS: at most 65536 individuals, 8 KB
+    // and 32-bit byte offsets of the rows over both buffers
+    const bool staged = (pv.flags == nullptr || (fbits != nullptr && pv.np <= 65536)) && pv.x1 >= pv.x0 &&
+                        pv.x1 - pv.x0 <= pv.np * pv.ldx && pv.out1 >= pv.out0 &&
+                        pv.out1 - pv.out0 <= pv.np * pv.ldx && pv.np * pv.ldx < (int64_t(1) << 29);
+    const size_t lds = fbits != nullptr && staged ? sizeof(uint32_t) * static_cast<size_t>((pv.np + 31) / 32) : 0;
     const uint32_t cr_max = cr_threshold(CR);
     const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
-    if (compute_draws)
-        de_draws_kernel<<<static_cast<unsigned>((pv.np + 255) / 256), 256, 0, s>>>(pv.np, pv.D, k0, k1, gen_dev,
-                                                                                   gen, inst, draws);
     // individuals per wave so that one chunk of the population fits in 2 MB
     const int64_t row_bytes = 2 * 1024 * 1024 / pv.np;
     const int ipw_auto = row_bytes >= 1024 ? 1 : (row_bytes >= 512 ? 2 : 4);
     const int ipw = (ipw_req == 1 || ipw_req == 2 || ipw_req == 4) ? ipw_req : ipw_auto;
-    const int R = (passes == 2 || passes == 4) ? passes : 1;
     const int64_t cw = 256 / ipw;
     const int64_t chunks = (pv.D + cw - 1) / cw;
+    const int R = (passes == 1 || passes == 2 || passes == 4)
+                      ? passes
+                      : de_passes((pv.np + 4 * ipw - 1) / (4 * ipw) * chunks);
     const int64_t groups = (pv.np + 4 * ipw * R - 1) / (4 * ipw * R);
     const int64_t blocks = 8 * ((chunks + 7) / 8) * groups;
     QPM_REQUIRE(blocks < (int64_t(1) << 31), QPM_ERANGE, "population too large for one DE launch");
     const int gr = static_cast<int>(groups), ch = static_cast<int>(chunks);
     const unsigned nb = static_cast<unsigned>(blocks);
 #define QPM_DE(I, P)                                                                                            \
-    if (packed)                                                                                                 \
+    if (staged)                                                                                                 \
         de_kernel<I, P, true><<<nb, 256, lds, s>>>(pv, draws, fbits, F, F_tab, cr_max, k0, k1, gen_dev, gen,     \
                                                    inst, bits, ld, gr, ch, store_genes ? 1 : 0, reset_cnt);     \
     else                                                                                                        \
         de_kernel<I, P, false><<<nb, 256, 0, s>>>(pv, draws, nullptr, F, F_tab, cr_max, k0, k1, gen_dev, gen,    \
                                                   inst, bits, ld, gr, ch, store_genes ? 1 : 0, reset_cnt);
+#define QPM_DE_R(I)                                                                                             \
+    if (R == 1) { QPM_DE(I, 1) } else if (R == 2) { QPM_DE(I, 2) } else { QPM_DE(I, 4) }
     if (ipw == 1) {
-        if (R == 1) { QPM_DE(1, 1) } else if (R == 2) { QPM_DE(1, 2) } else { QPM_DE(1, 4) }
+        QPM_DE_R(1)
     } else if (ipw == 2) {
-        if (R == 1) { QPM_DE(2, 1) } else if (R == 2) { QPM_DE(2, 2) } else { QPM_DE(2, 4) }
+        QPM_DE_R(2)
     } else {
-        if (R == 1) { QPM_DE(4, 1) } else if (R == 2) { QPM_DE(4, 2) } else { QPM_DE(4, 4) }
+        QPM_DE_R(4)
     }
+#undef QPM_DE_R
 #undef QPM_DE
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
@@ -701,11 +613,7 @@ static qpm_status de_step(const float *x, int64_t np, int64_t D, int64_t ldx, fl
     QPM_REQUIRE(!overlaps(x, bytes, u, bytes), QPM_EINVAL, "x and u must not overlap");
     const PopView pv{x, x, nullptr, u, u, np, D, ldx};
     hipStream_t s = static_cast<hipStream_t>(sv);
-    int4 *draws = nullptr;
-    QPM_TRY_HIP(hipMallocAsync(reinterpret_cast<void **>(&draws), sizeof(int4) * np, s));
-    qpm_status st2 = launch_de(pv, F, CR, seed, nullptr, generation, inst, u_bits, ld, draws, true, s, ipw, passes);
-    (void)hipFreeAsync(draws, s);
-    return st2;
+    return launch_de(pv, F, CR, seed, nullptr, generation, inst, u_bits, ld, nullptr, s, ipw, passes);
 }
 
 QPM_API qpm_status qpm_de_step(const float *x, int64_t np, int64_t D, int64_t ldx, float F, float CR,
@@ -713,7 +621,7 @@ QPM_API qpm_status qpm_de_step(const float *x, int64_t np, int64_t D, int64_t ld
                                int64_t ld, qpm_stream sv)
 {
     clear_error();
-    return de_step(x, np, D, ldx, F, CR, seed, generation, inst, u, u_bits, ld, 0, 1, sv);
+    return de_step(x, np, D, ldx, F, CR, seed, generation, inst, u, u_bits, ld, 0, 0, sv);
 }
 
 QPM_API qpm_status qpm_de_step_shape(const float *x, int64_t np, int64_t D, int64_t ldx, float F, float CR,

@@ -29,6 +29,10 @@ __device__ __forceinline__ float *out_row_of(const PopView &pv, int64_t r)
 
 __device__ __forceinline__ float clamp1(float v) { return fminf(fmaxf(v, -1.0f), 1.0f); }
 
+// clamp1 in one instruction (for a NaN both give -1: the median of three
+// with a NaN is the minimum of the other two)
+__device__ __forceinline__ float clamp1_med(float v) { return __builtin_amdgcn_fmed3f(v, -1.0f, 1.0f); }
+
 // x / 3 correctly rounded, without a division: q0 = x RN(1/3), the exact
 // remainder r = x - 3 q0 by FMA, one FMA correction, and the sign of x
 // restored (only -0 would otherwise come out as +0). Checked against IEEE
@@ -149,6 +153,126 @@ __device__ __forceinline__ float4 de_quad(float4 xv, float4 a, float4 b, float4 
         us[e] = take ? v : xs[e];
     }
     return make_float4(us[0], us[1], us[2], us[3]);
+}
+
+// de_quad (the same trial, bit for bit) with the individual-free part of the
+// Philox rounds taken from h = philox10_head(j0 / 4, g, inst << 8 | DE_CR)
+// and pi = philox10_individual(i, g, k0)
+__device__ __forceinline__ float4 de_quad_shared(const PhiloxHead &h, uint64_t pi, const float4 (&v)[4], int rel,
+                                                 uint32_t k0, uint32_t k1, float F, uint32_t cr_max)
+{
+    U4 r = philox10_rest(h, pi, k0, k1);
+    // jrand lies in one quad of a row: its word is made to pass there
+    if (__any(static_cast<uint32_t>(rel) < 4u)) {
+        if (rel == 0) r.x = 0u;
+        if (rel == 1) r.y = 0u;
+        if (rel == 2) r.z = 0u;
+        if (rel == 3) r.w = 0u;
+    }
+    const float xs[4] = {v[0].x, v[0].y, v[0].z, v[0].w}, as[4] = {v[1].x, v[1].y, v[1].z, v[1].w};
+    const float bs[4] = {v[2].x, v[2].y, v[2].z, v[2].w}, cs[4] = {v[3].x, v[3].y, v[3].z, v[3].w};
+    const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
+    float us[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        us[e] = rw[e] <= cr_max ? clamp1_med(fmaf(F, bs[e] - cs[e], as[e])) : xs[e];
+    }
+    return make_float4(us[0], us[1], us[2], us[3]);
+}
+
+// bits 0 .. 3: a, b, c, d below zero (one compare and one add with carry
+// each, where the compiler's select and shift-or take two more)
+__device__ __forceinline__ uint32_t below_zero_nibble(float4 v)
+{
+    uint32_t n = 0;
+    asm("v_cmp_gt_f32_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(n) : "v"(v.w) : "vcc");
+    asm("v_cmp_gt_f32_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(n) : "v"(v.z) : "vcc");
+    asm("v_cmp_gt_f32_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(n) : "v"(v.y) : "vcc");
+    asm("v_cmp_gt_f32_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(n) : "v"(v.x) : "vcc");
+    return n;
+}
+
+// DE trials of one workgroup (256 lanes): individuals gi IPB .. + IPB - 1 (IPB
+// = 4 IPW R) of gene chunk c of CW = 256 / IPW genes; a wave covers IPW
+// individuals at a time, 64 / IPW lanes each, a lane one gene quad. `second(r)`
+// says which buffer holds row r (x0 or x1 = x0 + a constant; trials go to the
+// other one), d holds (in lane t < IPB) the draws of individual min(gi IPB +
+// t, np - 1). One lane per
+// individual first works out where its target, donor and output rows begin
+// (in bytes from x0 / out0, OFF = uint32_t below 4 GB); the passes then
+// address them with one LDS read and one add per row, as global loads with a
+// scalar base (pointers kept in LDS would make them flat loads, which the compiler waits
+// for all together). The rows of pass r + 1 are in flight while pass r is
+// computed. Rows past np and quads past D are computed on clamped addresses
+// and not stored, so a pass is straight-line code.
+template <int IPW, int R, typename OFF, typename Second>
+__device__ __forceinline__ void de_rows(const PopView &pv, int gi, int c, float F, uint32_t cr_max, uint32_t g,
+                                        uint32_t inst, uint32_t k0, uint32_t k1, uint32_t *__restrict__ bits,
+                                        int64_t ld, bool store_genes, int4 d, Second second)
+{
+    constexpr int LPI = 64 / IPW;  // lanes per individual
+    constexpr int WPC = LPI / 8;   // bit words per chunk and individual
+    constexpr int IPG = 4 * IPW;   // individuals per pass
+    constexpr int IPB = R * IPG;   // individuals per workgroup
+    static_assert(IPB * WPC <= 256, "one bit word per thread at the end");
+    struct alignas(4 * sizeof(OFF)) Rows {
+        OFF o[4];  // target, donors
+    };
+    __shared__ uint32_t wsh[IPB][WPC];
+    __shared__ Rows srow[IPB];
+    __shared__ OFF sout[IPB];
+    __shared__ int sjr[IPB];
+    const int t = threadIdx.x;
+    const int local = t / LPI, li = t % LPI;
+    const int64_t np = pv.np, D = pv.D;
+    const int64_t base = static_cast<int64_t>(gi) * IPB;
+    if (t < IPB) {
+        const int64_t ip = base + t < np ? base + t : np - 1;
+        const OFF lq = static_cast<OFF>(4 * pv.ldx), bq = static_cast<OFF>(4 * (pv.x1 - pv.x0)),
+                  bo = static_cast<OFF>(4 * (pv.out1 - pv.out0));
+        auto src = [&](int r) -> OFF { return static_cast<OFF>(r) * lq + (second(r) ? bq : OFF(0)); };
+        srow[t] = Rows{{src(static_cast<int>(ip)), src(d.x), src(d.y), src(d.z)}};
+        sout[t] = static_cast<OFF>(ip) * lq + (second(static_cast<int>(ip)) ? OFF(0) : bo);
+        sjr[t] = d.w;
+    }
+    const int64_t j0 = (static_cast<int64_t>(c) * LPI + li) * 4;
+    const uint32_t q = static_cast<uint32_t>(j0 >> 2);
+    const OFF qc = static_cast<OFF>(16 * (j0 < D ? static_cast<int64_t>(q) : (D - 1) >> 2));  // (in bounds)
+    const uint32_t live = j0 + 3 < D ? 15u : (j0 < D ? (1u << (D - j0)) - 1u : 0u);
+    const PhiloxHead h = philox10_head(q, g, (inst << 8) | kTagDeCr, k0, k1);
+    const char *const xq = reinterpret_cast<const char *>(pv.x0);
+    __syncthreads();
+    float4 buf0[4], buf1[4];  // used alternately by the unrolled passes
+    auto load = [&](int r, float4 (&v)[4]) {
+        const Rows o = srow[r * IPG + local];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) v[m] = *reinterpret_cast<const float4 *>(xq + (o.o[m] + qc));
+    };
+    load(0, buf0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        float4(&cur)[4] = (r & 1) ? buf1 : buf0;
+        if (r + 1 < R) load(r + 1, (r & 1) ? buf0 : buf1);
+        const int li_r = r * IPG + local;
+        const int64_t i = base + li_r;
+        const float4 uv = de_quad_shared(h, philox10_individual(static_cast<uint32_t>(i), g, k0), cur,
+                                         sjr[li_r] - static_cast<int>(j0), k0, k1, F, cr_max);
+        if (store_genes && i < np && j0 < D)
+            store_quad_nt(reinterpret_cast<float *>(reinterpret_cast<char *>(pv.out0) + sout[li_r]), j0, D, uv);
+        const uint32_t nib = below_zero_nibble(uv) & live;
+        // merge the nibbles of 8 neighbouring lanes (32 genes) into one word
+        const uint32_t w = or8_into_last(nib << (4 * (t & 7)));
+        if ((t & 7) == 7) wsh[li_r][li >> 3] = w;
+    }
+    __syncthreads();
+    // the IPB consecutive individuals of this workgroup share each bit row:
+    // one contiguous store of IPB words per chunk word
+    if (t < IPB * WPC) {
+        const int wd = t / IPB, ii = t % IPB;
+        const int64_t row = base + ii;
+        const int64_t wg = static_cast<int64_t>(c) * WPC + wd;
+        if (row < np && wg * 32 < D) bits[wg * ld + row] = wsh[ii][wd];
+    }
 }
 
 // Grey-wolf update of gene quad q of a non-leader: per gene e and leader k,

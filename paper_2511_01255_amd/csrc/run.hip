@@ -53,7 +53,7 @@ struct qpm_run_s {
     uint32_t *fbits_prev = nullptr;  // packed flags before the selection
     FitPlan plan;
     int de_ipw = 0;     // 0 = chosen from np
-    int de_passes = 1;  // groups of individuals per DE workgroup
+    int de_passes = 0;  // groups of individuals per DE workgroup (0 = chosen from the sizes)
     bool fused = false; // whole generations in one workgroup (fused.hip)
     hipGraph_t graph = nullptr;  // one generation
     hipGraphExec_t exec = nullptr;
@@ -177,7 +177,7 @@ static qpm_status enqueue_generation(qpm_run_s *r, hipEvent_t *ev = nullptr)
         // DE alone: trials, evaluation (which advances the counter), greedy
         // selection with the next generation's draws, and the three best
         // after it as the reported leaders
-        QPM_STEP(QPM_K_DE, launch_de(pv, c.F, c.CR, c.seed, r->gen, 0u, c.inst, r->tbits, r->ld, r->draws, false,
+        QPM_STEP(QPM_K_DE, launch_de(pv, c.F, c.CR, c.seed, r->gen, 0u, c.inst, r->tbits, r->ld, r->draws,
                                      r->st, r->de_ipw, r->de_passes, r->fbits, r->F_tab, true, nullptr))
         QPM_STEP(QPM_K_FIT_DE, eval_partials(r, r->gen))
         QPM_STEP(QPM_K_FINISH_DE, eval_finish(r, nullptr, r->leaders, r->cand, r->draws, AcceptOut{},
@@ -215,7 +215,7 @@ static qpm_status enqueue_generation(qpm_run_s *r, hipEvent_t *ev = nullptr)
         }
         return mark(QPM_K_COUNT);
     }
-    QPM_STEP(QPM_K_DE, launch_de(pv, c.F, c.CR, c.seed, r->gen, 0u, c.inst, r->tbits, r->ld, r->draws, false, r->st,
+    QPM_STEP(QPM_K_DE, launch_de(pv, c.F, c.CR, c.seed, r->gen, 0u, c.inst, r->tbits, r->ld, r->draws, r->st,
                                  r->de_ipw, r->de_passes, r->fbits, r->F_tab, !r->lazy,
                                  r->lazy ? r->acc_cnt : nullptr))
     QPM_STEP(QPM_K_FIT_DE, eval_partials(r))
@@ -438,7 +438,7 @@ static qpm_status tune_run(qpm_run_s *r)
                 for (int np_ : {1, 2, 4}) {
                     float ms = 0.0f;
                     st = time_min([&]() {
-                        return launch_de(pv, c.F, c.CR, c.seed, r->gen, 0u, c.inst, r->tbits, r->ld, r->draws, false,
+                        return launch_de(pv, c.F, c.CR, c.seed, r->gen, 0u, c.inst, r->tbits, r->ld, r->draws,
                                          r->st, cand, np_, r->fbits, nullptr, !r->lazy, nullptr);
                     },
                                &ms);
@@ -452,7 +452,7 @@ static qpm_status tune_run(qpm_run_s *r)
             tune_store(key, ipw, passes);
         }
         r->de_ipw = ipw;
-        r->de_passes = passes >= 1 ? passes : 1;
+        r->de_passes = passes;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
