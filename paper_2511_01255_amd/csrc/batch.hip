@@ -25,6 +25,7 @@
 #include "device_common.hpp"
 #include "genes.hpp"
 #include "scan.hpp"
+#include "select.hpp"
 
 namespace qpm {
 
@@ -138,127 +139,98 @@ __global__ __launch_bounds__(GW * 256) void batch_fit_tab_kernel(const uint32_t 
     o[5 * ld] = t.qi;
 }
 
-// One workgroup of 1024 threads per instance: four threads per genome fold
-// a quarter of the instance's slots each (in order), the first folds the
-// four quarters in order, then
-//   mode 0 (evaluation only): f_out[b][i] = f;
-//   mode 1 (initial): f_cur = f, leaders, DE draws of generation gen;
-//   mode 2 (after DE): select, leaders;
-//   mode 3 (after GWO): select with the leaders excluded, DE draws of the
+// The fitness of every genome from its instance's segment triples, over the
+// whole batch at once: grid x = groups of 16 genomes, y = instance, 16 ranges
+// per genome (combine_segments). Folded inside the one-workgroup-per-instance
+// selection kernel instead, this took 20-26 us at 32 and 64 designs of up to
+// 5 x 10^4 domains, against 6 us here.
+template <typename T>
+__global__ __launch_bounds__(256) void batch_combine_kernel(const double *__restrict__ part,
+                                                            const int *__restrict__ slot_ofs, int64_t ld, int64_t np,
+                                                            const InstDesc *__restrict__ inst, T *__restrict__ fit)
+{
+    __shared__ double sh[6 * 16 * 16];
+    const int b = blockIdx.y;
+    const int gl = threadIdx.x & 15, range = threadIdx.x >> 4;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 16 + gl;
+    const int s0 = slot_ofs[b];
+    const Tri t = combine_segments<16, 16>(part + static_cast<int64_t>(s0) * 6 * ld, slot_ofs[b + 1] - s0, ld, i,
+                                           i < np, range, gl, sh);
+    if (range == 0 && i < np) {
+        const double sr = t.qr + inst[b].C[0], si = t.qi + inst[b].C[1];
+        fit[static_cast<int64_t>(b) * np + i] = static_cast<T>(fma(sr, sr, si * si));
+    }
+}
+
+// The end of an evaluation in a batched run, as finish_kernel: grid x = groups
+// of 64 genomes, y = instance; 16 waves fold the group's segment triples,
+// wave 0 then
+//   mode 1 (initial): f_cur = f, leader candidates, DE draws of generation gen;
+//   mode 2 (after DE): selects, leader candidates;
+//   mode 3 (after GWO): selects with the leaders excluded, DE draws of the
 //     next generation (gen, which the evaluation kernel before this one
 //     advanced: it does not read the counter, so no cross-workgroup
 //     ordering is needed here).
+// The candidates (3 per group) are merged into the leaders by
+// batch_leaders_kernel or the accepted-trial kernel after it. (With one
+// workgroup per instance instead: 23-26 us at 32 designs of 256 genomes and
+// up to 5 x 10^4 domains, against 8 us.)
 template <typename T>
 __global__ __launch_bounds__(1024) void batch_finish_kernel(int mode, const double *__restrict__ part,
                                                            const int *__restrict__ slot_ofs, int64_t ld, int64_t np,
                                                            const InstDesc *__restrict__ inst, T *__restrict__ f_cur,
-                                                           uint32_t *__restrict__ flags, int32_t *__restrict__ leaders,
-                                                           int4 *__restrict__ draws, uint32_t *__restrict__ gen,
+                                                           uint32_t *__restrict__ flags,
+                                                           const int32_t *__restrict__ leaders,
+                                                           T *__restrict__ cand_v, int32_t *__restrict__ cand_i,
+                                                           int4 *__restrict__ draws, const uint32_t *__restrict__ gen,
                                                            uint32_t k0, uint32_t k1, uint32_t inst0,
-                                                           uint32_t *__restrict__ fbits,
-                                                           AcceptOut acc)
+                                                           uint32_t *__restrict__ fbits, AcceptOut acc)
 {
-    const int b = blockIdx.x;
-    const InstDesc id = inst[b];
-    const int s0 = slot_ofs[b], s1 = slot_ofs[b + 1];
-    T *fb = f_cur + static_cast<int64_t>(b) * np;
-    uint32_t *flb = flags ? flags + static_cast<int64_t>(b) * np : nullptr;
-    int32_t *Lb = leaders ? leaders + 3 * b : nullptr;
-    const uint32_t g = gen ? gen[0] : 0u;
-    int32_t L0 = -1, L1 = -1, L2 = -1;
-    if (mode == 3) {
-        L0 = Lb[0];
-        L1 = Lb[1];
-        L2 = Lb[2];
+    __shared__ double sh[6 * 16 * 64];
+    const int64_t b = blockIdx.y, grp = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int64_t i = grp * 64 + lane;
+    const int s0 = slot_ofs[b];
+    const Tri t = combine_segments<16, 64>(part + static_cast<int64_t>(s0) * 6 * ld, slot_ofs[b + 1] - s0, ld, i,
+                                           i < np, static_cast<int>(threadIdx.x >> 6), lane, sh);
+    if (threadIdx.x >= 64) return;
+    const double sr = t.qr + inst[b].C[0], si = t.qi + inst[b].C[1];
+    const double f = fma(sr, sr, si * si);
+    const int64_t n = inst[b].n;
+    const uint32_t instb = inst0 + static_cast<uint32_t>(b);
+    const int64_t fw = 2 * static_cast<int64_t>(gridDim.x);  // packed flag words per instance
+    T *fb = f_cur + b * np;
+    int4 *db = draws + b * np;
+    T *cv = mode <= 2 ? cand_v + b * 3 * gridDim.x : nullptr;
+    int32_t *ci = cand_i + b * 3 * gridDim.x;
+    if (mode == 1) {
+        Top3<T> tp = top3_empty<T>();
+        if (i < np) {
+            tp.v[0] = static_cast<T>(f);
+            tp.i[0] = static_cast<int>(i);
+            fb[i] = static_cast<T>(f);
+            db[i] = de_draw(i, np, n, gen[0], instb, k0, k1);
+        }
+        wave_top3(tp);
+        if (lane < 3) {
+            cv[3 * grp + lane] = lane == 0 ? tp.v[0] : (lane == 1 ? tp.v[1] : tp.v[2]);
+            ci[3 * grp + lane] = lane == 0 ? tp.i[0] : (lane == 1 ? tp.i[1] : tp.i[2]);
+        }
+        return;
     }
-    const int64_t fw = (np + 31) / 32;  // packed flag words per instance
-    const int quarter = static_cast<int>(threadIdx.x >> 8);
-    const int q0 = s0 + (s1 - s0) * quarter / 4, q1 = s0 + (s1 - s0) * (quarter + 1) / 4;
-    __shared__ double sq[3][6][256];
-    __shared__ uint32_t n_acc;  // accepted so far (their list: acc.list[b np ..])
-    if (threadIdx.x == 0) n_acc = 0u;
-    for (int64_t base = 0; base < np; base += 256) {
-        const int64_t i = base + (threadIdx.x & 255);
-        const bool valid = i < np;
-        Tri t{0, 0, 0, 0, 0, 0};
-        if (valid && q0 < q1) {
-            const double *p = part + static_cast<int64_t>(q0) * 6 * ld + i;
-            t = Tri{p[0], p[ld], p[2 * ld], p[3 * ld], p[4 * ld], p[5 * ld]};
-            for (int sg = q0 + 1; sg < q1; ++sg) {
-                const double *q = part + static_cast<int64_t>(sg) * 6 * ld + i;
-                tri_append(t, Tri{q[0], q[ld], q[2 * ld], q[3 * ld], q[4 * ld], q[5 * ld]});
-            }
-        }
-        if (quarter > 0) {
-            sq[quarter - 1][0][threadIdx.x & 255] = t.ar;
-            sq[quarter - 1][1][threadIdx.x & 255] = t.ai;
-            sq[quarter - 1][2][threadIdx.x & 255] = t.br;
-            sq[quarter - 1][3][threadIdx.x & 255] = t.bi;
-            sq[quarter - 1][4][threadIdx.x & 255] = t.qr;
-            sq[quarter - 1][5][threadIdx.x & 255] = t.qi;
-        }
-        __syncthreads();
-        uint32_t fl = 0, fl_old = 0;
-        bool accepted = false;
-        if (quarter == 0 && valid) {
-        for (int u = 0; u < 3; ++u) {
-            const int lo = s0 + (s1 - s0) * (u + 1) / 4, hi = s0 + (s1 - s0) * (u + 2) / 4;
-            if (lo < hi)
-                tri_append(t, Tri{sq[u][0][threadIdx.x], sq[u][1][threadIdx.x], sq[u][2][threadIdx.x],
-                                  sq[u][3][threadIdx.x], sq[u][4][threadIdx.x], sq[u][5][threadIdx.x]});
-        }
-        const double sr = t.qr + id.C[0], si = t.qi + id.C[1];
-        const T v = static_cast<T>(fma(sr, sr, si * si));
-        if (mode <= 1) {
-            fb[i] = v;
-        } else {
-            const bool skip = (mode == 3) && (i == L0 || i == L1 || i == L2);
-            fl = flb[i];
-            fl_old = fl;
-            if (!skip && v > fb[i]) {
-                accepted = true;
-                fb[i] = v;
-                fl ^= 1u;
-                flb[i] = fl;
-            }
-        }
-        if (mode == 1 || mode == 3)  // mode 3: the evaluation kernel already advanced gen
-            draws[static_cast<int64_t>(b) * np + i] = de_draw(i, np, id.n, g, inst0 + static_cast<uint32_t>(b), k0, k1);
-        }
-        // the packed copy of this wave's 64 flags (words (base + 64 w) / 32 and + 1)
-        if (quarter == 0 && mode >= 2 && fbits) {
-            const uint64_t m = __ballot(fl != 0u);
-            const int64_t w0 = (base + 64 * (threadIdx.x >> 6)) / 32;
-            if ((threadIdx.x & 63) == 0) {
-                if (w0 < fw) fbits[b * fw + w0] = static_cast<uint32_t>(m);
-                if (w0 + 1 < fw) fbits[b * fw + w0 + 1] = static_cast<uint32_t>(m >> 32);
-            }
-        }
-        // accepted trials or candidates listed per instance for the
-        // materialise kernels, with the flags from before the selection
-        if (quarter == 0 && mode == 2 && acc.list != nullptr) {
-            const int lane = threadIdx.x & 63;
-            const uint64_t mo = __ballot(fl_old != 0u);
-            const uint64_t am = __ballot(accepted);
-            const int64_t w0 = (base + 64 * (threadIdx.x >> 6)) / 32;
-            if (lane == 0) {
-                if (w0 < fw) acc.fbits_prev[b * fw + w0] = static_cast<uint32_t>(mo);
-                if (w0 + 1 < fw) acc.fbits_prev[b * fw + w0 + 1] = static_cast<uint32_t>(mo >> 32);
-            }
-            uint32_t basec = 0;
-            if (lane == 0 && am != 0) basec = atomicAdd(&n_acc, static_cast<uint32_t>(__popcll(am)));
-            basec = static_cast<uint32_t>(__shfl(static_cast<int>(basec), 0));
-            if (accepted)
-                acc.list[static_cast<int64_t>(b) * np + basec +
-                         static_cast<uint32_t>(__popcll(am & ((uint64_t(1) << lane) - 1)))] = static_cast<int32_t>(i);
-        }
-        __syncthreads();  // sq is refilled for the next 256 genomes
-    }
-    if (threadIdx.x == 0 && mode == 2 && acc.list != nullptr) acc.cnt[b] = n_acc;
-    if (mode == 1 || mode == 2) {
-        __syncthreads();
-        block_top3<T, 1024>(fb, np, Lb);
-    }
+    const AcceptOut accb = acc.list ? AcceptOut{acc.list + b * np, acc.cnt + b, acc.fbits_prev + b * fw} : AcceptOut{};
+    select_group<T>(f, grp, lane, np, fb, flags + b * np, fbits + b * fw, mode == 3 ? leaders + 3 * b : nullptr, cv, ci,
+                    mode == 3 ? db : nullptr, gen, n, k0, k1, instb, accb, 0u);
+}
+
+// the leaders of instance blockIdx.x from its groups' candidates
+template <typename T>
+__global__ __launch_bounds__(64) void batch_leaders_kernel(const T *__restrict__ cand_v,
+                                                           const int32_t *__restrict__ cand_i, int64_t groups,
+                                                           int32_t *__restrict__ leaders)
+{
+    const int64_t b = blockIdx.x;
+    block_top3<T, 64>(cand_v + b * 3 * groups, 3 * groups, leaders + 3 * b, cand_i + b * 3 * groups);
 }
 
 // ---------------------------------------------------------------- evolution
@@ -314,8 +286,12 @@ __global__ __launch_bounds__(256) void batch_de_kernel(BatchPop bp, const InstDe
                                                        const int4 *__restrict__ draws, float F, uint32_t cr_max,
                                                        uint32_t k0, uint32_t k1, const uint32_t *__restrict__ gen,
                                                        uint32_t inst0, uint32_t *__restrict__ bits, int64_t ld,
-                                                       const uint32_t *__restrict__ fbits, int store_genes)
+                                                       const uint32_t *__restrict__ fbits, int store_genes,
+                                                       uint32_t *__restrict__ reset_cnt, int n_inst)
 {
+    // the accepted trials' counters start at 0 for this generation
+    if (reset_cnt != nullptr && blockIdx.x == 0)
+        for (int k = threadIdx.x; k < n_inst; k += 256) reset_cnt[k] = 0u;
     constexpr int IPB = 4 * IPW * R;
     const uint32_t blk = blockIdx.x;
     const int k = static_cast<int>(blk >> 3);
@@ -327,7 +303,7 @@ __global__ __launch_bounds__(256) void batch_de_kernel(BatchPop bp, const InstDe
     const int64_t np = bp.np;
     const int t = threadIdx.x;
     __shared__ uint32_t sfb[128];
-    const int fw = static_cast<int>((np + 31) / 32);
+    const int fw = 2 * static_cast<int>((np + 63) / 64);
     int4 d = make_int4(0, 0, 0, 0);
     if (t < IPB) d = draws[tl.inst * np + min(static_cast<int64_t>(gi) * IPB + t, np - 1)];
     if (t < fw) sfb[t] = fbits[static_cast<int64_t>(tl.inst) * fw + t];
@@ -351,9 +327,22 @@ __global__ __launch_bounds__(256) void batch_materialize_kernel(BatchPop bp, con
                                                                 uint32_t cr_max, uint32_t k0, uint32_t k1,
                                                                 const uint32_t *__restrict__ gen, uint32_t inst0,
                                                                 const int32_t *__restrict__ list,
-                                                                const uint32_t *__restrict__ cnt)
+                                                                const uint32_t *__restrict__ cnt,
+                                                                const void *__restrict__ cand_v,
+                                                                const int32_t *__restrict__ cand_i, int cand_f64,
+                                                                int32_t *__restrict__ leaders)
 {
     const Tile tl = tiles[blockIdx.y];
+    // each instance's leaders from its groups' candidates, once
+    if (blockIdx.x == 0 && tl.chunk == 0) {
+        const int64_t n3 = 3 * ((bp.np + 63) / 64);
+        if (cand_f64)
+            block_top3<double, 256>(static_cast<const double *>(cand_v) + tl.inst * n3, n3, leaders + 3 * tl.inst,
+                                    cand_i + tl.inst * n3);
+        else
+            block_top3<float, 256>(static_cast<const float *>(cand_v) + tl.inst * n3, n3, leaders + 3 * tl.inst,
+                                   cand_i + tl.inst * n3);
+    }
     const int64_t np = bp.np;
     const uint32_t n_acc = min(cnt[tl.inst], static_cast<uint32_t>(np));
     if (blockIdx.x >= n_acc) return;
@@ -361,7 +350,7 @@ __global__ __launch_bounds__(256) void batch_materialize_kernel(BatchPop bp, con
     const int64_t q = static_cast<int64_t>(tl.chunk) * 256 + threadIdx.x, j0 = 4 * q;
     if (j0 >= id.n) return;
     const uint32_t g = gen[0];
-    const int64_t fw = (np + 31) / 32;
+    const int64_t fw = 2 * ((np + 63) / 64);
     const uint32_t *fo = fb_old + tl.inst * fw;
     const int32_t *lb = list + tl.inst * np;
     const int4 *db = draws + tl.inst * np;
@@ -725,20 +714,16 @@ static void free_fit_plan(FitPlanDev &d, hipStream_t s)
     d = FitPlanDev{};
 }
 
-static qpm_status launch_batch_finish(int mode, const qpm_batch_s &bt, qpm_prec p, const FitPlanDev &fp, int64_t ld,
-                                      int64_t np, void *f, uint32_t *flags, int32_t *leaders, int4 *draws,
-                                      uint32_t *gen, uint64_t seed, uint32_t inst0, hipStream_t s,
-                                      uint32_t *fbits = nullptr, AcceptOut acc = AcceptOut{})
+static qpm_status launch_batch_combine(const qpm_batch_s &bt, qpm_prec p, const FitPlanDev &fp, int64_t ld,
+                                       int64_t np, void *fit, hipStream_t s)
 {
-    const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
+    const dim3 grid(static_cast<unsigned>((np + 15) / 16), static_cast<unsigned>(bt.n_inst));
     if (p == QPM_PREC_F64)
-        batch_finish_kernel<double><<<bt.n_inst, 1024, 0, s>>>(mode, fp.part, fp.slot_ofs, ld, np, bt.dev,
-                                                             static_cast<double *>(f), flags, leaders, draws, gen, k0,
-                                                             k1, inst0, fbits, acc);
+        batch_combine_kernel<double><<<grid, 256, 0, s>>>(fp.part, fp.slot_ofs, ld, np, bt.dev,
+                                                          static_cast<double *>(fit));
     else
-        batch_finish_kernel<float><<<bt.n_inst, 1024, 0, s>>>(mode, fp.part, fp.slot_ofs, ld, np, bt.dev,
-                                                            static_cast<float *>(f), flags, leaders, draws, gen, k0,
-                                                            k1, inst0, fbits, acc);
+        batch_combine_kernel<float><<<grid, 256, 0, s>>>(fp.part, fp.slot_ofs, ld, np, bt.dev,
+                                                         static_cast<float *>(fit));
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }
@@ -800,7 +785,7 @@ static qpm_status batch_eval_plan(qpm_batch b, qpm_prec p, const uint32_t *bits,
     if (st != QPM_OK) return st;
     st = launch_batch_fit(*b, p, bits, np, ld, pl, fp.segs, fp.part, s);
     if (st == QPM_OK)
-        st = launch_batch_finish(0, *b, p, fp, ld, np, fitness, nullptr, nullptr, nullptr, nullptr, 0, 0, s);
+        st = launch_batch_combine(*b, p, fp, ld, np, fitness, s);
     free_fit_plan(fp, s);
     return st;
 }
@@ -815,8 +800,10 @@ struct qpm_batch_run_s {
     float *buf[2] = {nullptr, nullptr};  // one allocation
     size_t gene_bytes = 0;               // of each buffer
     uint32_t *flags = nullptr;
-    uint32_t *fbits = nullptr;  // flags packed one bit per individual, ceil(np / 32) words per instance
+    uint32_t *fbits = nullptr;  // flags packed one bit per individual, 2 ceil(np / 64) words per instance
     void *f_cur = nullptr;
+    void *cand_v = nullptr;      // leader candidates, 3 per instance and group of 64
+    int32_t *cand_i = nullptr;
     uint32_t *bits = nullptr;
     int32_t *leaders = nullptr;
     int4 *draws = nullptr;
@@ -859,6 +846,8 @@ static void release_batch_run(qpm_batch_run_s *r)
     (void)hipFree(r->fbits);
     (void)hipFree(r->flags);
     (void)hipFree(r->f_cur);
+    (void)hipFree(r->cand_v);
+    (void)hipFree(r->cand_i);
     (void)hipFree(r->bits);
     (void)hipFree(r->leaders);
     (void)hipFree(r->draws);
@@ -892,6 +881,7 @@ static qpm_status launch_batch_de(qpm_batch_run_s *r, int ipw, int passes)
     const unsigned nb = static_cast<unsigned>(blocks);
     const BatchPop bp = r->pop();
     const int gr = static_cast<int>(groups);
+    uint32_t *reset = r->lazy ? r->acc_cnt : nullptr;
     // byte offsets of an instance's rows over both buffers fit 32 bits
     const bool near = 2 * r->gene_bytes < (size_t(1) << 32);
 #define QPM_BDE(I, P)                                                                                           \
@@ -899,11 +889,13 @@ static qpm_status launch_batch_de(qpm_batch_run_s *r, int ipw, int passes)
         if (near)                                                                                               \
             batch_de_kernel<I, P, uint32_t><<<nb, 256, 0, r->st>>>(bp, r->inst, tiles, ntiles, gr, r->draws, c.F, \
                                                                    cr_threshold(c.CR), k0, k1, r->gen, c.inst,  \
-                                                                   r->bits, r->ld, r->fbits, r->lazy ? 0 : 1);  \
+                                                                   r->bits, r->ld, r->fbits, r->lazy ? 0 : 1, reset, \
+                                                                   r->bt->n_inst);  \
         else                                                                                                    \
             batch_de_kernel<I, P, uint64_t><<<nb, 256, 0, r->st>>>(bp, r->inst, tiles, ntiles, gr, r->draws, c.F, \
                                                                    cr_threshold(c.CR), k0, k1, r->gen, c.inst,  \
-                                                                   r->bits, r->ld, r->fbits, r->lazy ? 0 : 1);  \
+                                                                   r->bits, r->ld, r->fbits, r->lazy ? 0 : 1, reset, \
+                                                                   r->bt->n_inst);  \
     }
     if (ipw == 1) {
         if (passes == 1) QPM_BDE(1, 1) else if (passes == 2) QPM_BDE(1, 2) else QPM_BDE(1, 4)
@@ -942,6 +934,34 @@ static dim3 materialize_grid(const qpm_batch_run_s *r)
     return dim3(static_cast<unsigned>(shares), static_cast<unsigned>(r->n_gtiles));
 }
 
+// the evaluated genomes' fitness and their selection (batch_finish_kernel),
+// and the leaders (modes 1 and 2) unless the accepted-trial kernel merges them
+static qpm_status launch_batch_finish(qpm_batch_run_s *r, int mode, AcceptOut acc = AcceptOut{})
+{
+    const qpm_run_config &c = r->cfg;
+    const uint32_t k0 = static_cast<uint32_t>(c.seed), k1 = static_cast<uint32_t>(c.seed >> 32);
+    const int64_t groups = (c.np + 63) / 64;
+    const dim3 grid(static_cast<unsigned>(groups), static_cast<unsigned>(r->bt->n_inst));
+    const bool leaders = mode == 1 || (mode == 2 && acc.list == nullptr);
+#define QPM_BFIN(T)                                                                                              \
+    {                                                                                                            \
+        batch_finish_kernel<T><<<grid, 1024, 0, r->st>>>(mode, r->fdev.part, r->fdev.slot_ofs, r->ld, c.np,      \
+                                                         r->bt->dev, static_cast<T *>(r->f_cur), r->flags,       \
+                                                         r->leaders, static_cast<T *>(r->cand_v), r->cand_i,     \
+                                                         r->draws, r->gen, k0, k1, c.inst, r->fbits, acc);       \
+        if (leaders)                                                                                             \
+            batch_leaders_kernel<T><<<r->bt->n_inst, 64, 0, r->st>>>(static_cast<T *>(r->cand_v), r->cand_i,     \
+                                                                     groups, r->leaders);                        \
+    }
+    if (r->f64())
+        QPM_BFIN(double)
+    else
+        QPM_BFIN(float)
+#undef QPM_BFIN
+    QPM_TRY_HIP(hipGetLastError());
+    return QPM_OK;
+}
+
 static qpm_status batch_generation(qpm_batch_run_s *r, hipEvent_t *ev = nullptr)
 {
     const qpm_run_config &c = r->cfg;
@@ -957,23 +977,20 @@ static qpm_status batch_generation(qpm_batch_run_s *r, hipEvent_t *ev = nullptr)
     QPM_STEP(QPM_K_DE, launch_batch_de(r, r->de_ipw, r->de_passes))
     QPM_STEP(QPM_K_FIT_DE, launch_batch_fit(*r->bt, p, r->bits, c.np, r->ld, r->fplan, r->fdev.segs, r->fdev.part,
                                             r->st))
-    QPM_STEP(QPM_K_FINISH_DE, launch_batch_finish(2, *r->bt, p, r->fdev, r->ld, c.np, r->f_cur, r->flags, r->leaders,
-                                                  r->draws, r->gen, c.seed, c.inst, r->st, r->fbits,
-                                                  r->lazy ? AcceptOut{r->acc_list, r->acc_cnt, r->fbits_prev}
-                                                          : AcceptOut{}))
+    QPM_STEP(QPM_K_FINISH_DE,
+             launch_batch_finish(r, 2, r->lazy ? AcceptOut{r->acc_list, r->acc_cnt, r->fbits_prev} : AcceptOut{}))
     if (r->lazy) {  // the accepted trials' genes (timed with the finish)
         const uint32_t k0 = static_cast<uint32_t>(c.seed), k1 = static_cast<uint32_t>(c.seed >> 32);
         batch_materialize_kernel<<<materialize_grid(r), 256, 0, r->st>>>(r->pop(), r->inst, r->gtiles, r->draws,
                                                                          r->fbits_prev, c.F, cr_threshold(c.CR), k0,
-                                                                         k1, r->gen, c.inst, r->acc_list, r->acc_cnt);
+                                                                         k1, r->gen, c.inst, r->acc_list, r->acc_cnt, r->cand_v,
+                                                                         r->cand_i, r->f64() ? 1 : 0, r->leaders);
         QPM_TRY_HIP(hipGetLastError());
     }
     QPM_STEP(QPM_K_GWO, launch_batch_gwo(r))
     QPM_STEP(QPM_K_FIT_GWO, launch_batch_fit(*r->bt, p, r->bits, c.np, r->ld, r->fplan, r->fdev.segs, r->fdev.part,
                                              r->st, r->gen))
-    QPM_STEP(QPM_K_FINISH_GWO, launch_batch_finish(3, *r->bt, p, r->fdev, r->ld, c.np, r->f_cur, r->flags,
-                                                   r->leaders, r->draws, r->gen, c.seed, c.inst, r->st,
-                                                   r->fbits))
+    QPM_STEP(QPM_K_FINISH_GWO, launch_batch_finish(r, 3))
 #undef QPM_STEP
     return mark(QPM_K_COUNT);
 }
@@ -1178,20 +1195,23 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
     }
     r->n_gtiles = static_cast<int>(gt.size());
     for (int v = 0; v < 3; ++v) r->n_dtiles[v] = static_cast<int>(dt[v].size());
+    const int64_t groups = (c.np + 63) / 64;  // of 64 genomes, per instance
     hipError_t e = hipStreamCreateWithFlags(&r->st, hipStreamNonBlocking);
     // both gene buffers in one allocation: row offsets count from the first
     if (e == hipSuccess) e = hipMalloc(&r->buf[0], 2 * gene_bytes);
     if (e == hipSuccess) r->buf[1] = r->buf[0] + xofs;
     r->gene_bytes = gene_bytes;
     if (e == hipSuccess) e = hipMalloc(&r->flags, sizeof(uint32_t) * n_inst * c.np);
-    if (e == hipSuccess) e = hipMalloc(&r->fbits, sizeof(uint32_t) * n_inst * ((c.np + 31) / 32));
+    if (e == hipSuccess) e = hipMalloc(&r->fbits, sizeof(uint32_t) * n_inst * 2 * groups);
     if (e == hipSuccess) e = hipMalloc(&r->f_cur, (r->f64() ? 8 : 4) * n_inst * c.np);
+    if (e == hipSuccess) e = hipMalloc(&r->cand_v, (r->f64() ? 8 : 4) * 3 * n_inst * groups);
+    if (e == hipSuccess) e = hipMalloc(&r->cand_i, sizeof(int32_t) * 3 * n_inst * groups);
     if (e == hipSuccess) e = hipMalloc(&r->bits, sizeof(uint32_t) * b->total_words * r->ld);
     if (e == hipSuccess) e = hipMalloc(&r->leaders, sizeof(int32_t) * 3 * n_inst);
     if (e == hipSuccess) e = hipMalloc(&r->draws, sizeof(int4) * n_inst * c.np);
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_list, sizeof(int32_t) * n_inst * c.np);
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_cnt, sizeof(uint32_t) * n_inst);
-    if (e == hipSuccess && r->lazy) e = hipMalloc(&r->fbits_prev, sizeof(uint32_t) * n_inst * ((c.np + 31) / 32));
+    if (e == hipSuccess && r->lazy) e = hipMalloc(&r->fbits_prev, sizeof(uint32_t) * n_inst * 2 * groups);
     if (e == hipSuccess) e = hipMalloc(&r->gen, sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc(&r->a_tab, sizeof(float) * c.generations);
     if (e == hipSuccess) e = hipMalloc(&r->inst, sizeof(InstDesc) * n_inst);
@@ -1220,7 +1240,7 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
             e = hipMemcpyAsync(r->dtiles[v], dt[v].data(), sizeof(Tile) * dt[v].size(), hipMemcpyHostToDevice,
                                r->st);
     if (e == hipSuccess) e = hipMemsetAsync(r->flags, 0, sizeof(uint32_t) * n_inst * c.np, r->st);
-    if (e == hipSuccess) e = hipMemsetAsync(r->fbits, 0, sizeof(uint32_t) * n_inst * ((c.np + 31) / 32), r->st);
+    if (e == hipSuccess) e = hipMemsetAsync(r->fbits, 0, sizeof(uint32_t) * n_inst * 2 * groups, r->st);
     if (e == hipSuccess) e = hipMemsetAsync(r->gen, 0, sizeof(uint32_t), r->st);
     if (e == hipSuccess) e = hipMemsetAsync(r->bits, 0, sizeof(uint32_t) * b->total_words * r->ld, r->st);
     if (e == hipSuccess) e = hipStreamSynchronize(r->st);
@@ -1257,9 +1277,7 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
     if (st == QPM_OK) st = upload_fit_plan(r->fplan, r->ld, r->st, &r->fdev);
     const qpm_prec p = static_cast<qpm_prec>(c.prec);
     if (st == QPM_OK) st = launch_batch_fit(*b, p, r->bits, c.np, r->ld, r->fplan, r->fdev.segs, r->fdev.part, r->st);
-    if (st == QPM_OK)
-        st = launch_batch_finish(1, *b, p, r->fdev, r->ld, c.np, r->f_cur, r->flags, r->leaders, r->draws, r->gen,
-                                 c.seed, c.inst, r->st);
+    if (st == QPM_OK) st = launch_batch_finish(r, 1);
     // the DE shape: the trial launches of the tuner write only the other
     // gene buffer and the bit rows, which the first generation overwrites
     if (st == QPM_OK && tune) st = tune_de(r);

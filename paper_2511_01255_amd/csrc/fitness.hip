@@ -77,14 +77,19 @@ __global__ __launch_bounds__(WAVES * 64) void fit_seg_kernel(const uint32_t *__r
     }
 }
 
-// 64 genomes per workgroup of 4 waves (see combine_segments)
+// 256 threads: 16 ranges of 16 genomes (a 128-byte line of each component) or
+// 4 ranges of 64 genomes (see combine_segments)
+template <int NR>
 __global__ __launch_bounds__(256) void fit_combine_kernel(const double *__restrict__ part, int gy, int64_t ld,
                                                           int64_t np, const double *__restrict__ C,
                                                           void *__restrict__ fit, int out_f64)
 {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63);
-    const Tri t = combine_segments<4>(part, gy, ld, i, i < np);
-    if (threadIdx.x < 64 && i < np) store_fitness(fit, out_f64, i, t, C);
+    constexpr int NG = 256 / NR;
+    __shared__ double sh[6 * NR * NG];
+    const int gl = static_cast<int>(threadIdx.x) % NG, range = static_cast<int>(threadIdx.x) / NG;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * NG + gl;
+    const Tri t = combine_segments<NR, NG>(part, gy, ld, i, i < np, range, gl, sh);
+    if (range == 0 && i < np) store_fitness(fit, out_f64, i, t, C);
 }
 
 // The per-individual scheme: one lane walks its whole genome; no segment
@@ -314,8 +319,12 @@ qpm_status launch_fitness(const Design &d, qpm_prec p, const uint32_t *bits, int
                                    : launch_seg<false>(d, pl, bits, np, ld, part, fit, out_f64, true, s);
         if (st != QPM_OK) return st;
         if (pl.gy > 1) {
-            const unsigned blocks = static_cast<unsigned>((np + 63) / 64);
-            fit_combine_kernel<<<blocks, 256, 0, s>>>(part, pl.gy, ld, np, d.Cdev, fit, out_f64);
+            if (combine_ranges(pl.gy) == kMaxRanges)
+                fit_combine_kernel<kMaxRanges><<<static_cast<unsigned>((np + 15) / 16), 256, 0, s>>>(
+                    part, pl.gy, ld, np, d.Cdev, fit, out_f64);
+            else
+                fit_combine_kernel<4><<<static_cast<unsigned>((np + 63) / 64), 256, 0, s>>>(part, pl.gy, ld, np,
+                                                                                           d.Cdev, fit, out_f64);
         }
     }
     QPM_TRY_HIP(hipGetLastError());

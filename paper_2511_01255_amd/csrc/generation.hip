@@ -11,8 +11,9 @@
 
 namespace qpm {
 
-// Workgroup = 4 waves over 64 consecutive individuals (lane = individual):
-// the waves fold the segment triples (combine_segments), wave 0 selects,
+// Workgroup = NR waves (combine_ranges) over 64 consecutive individuals (lane
+// = individual): the waves fold the segment triples (combine_segments), wave
+// 0 selects,
 // keeps the packed copy of the buffer flags (bit i % 32 of word i / 32)
 // that the DE kernel stages in LDS, and, when leaders are wanted, leaves
 // its own three best in cand (3 per workgroup). The global steps (merging
@@ -20,8 +21,8 @@ namespace qpm {
 // finish_tail_kernel after it: a kernel boundary orders them, which costs
 // less here than an agent-scope release (an L2 write-back) in every
 // workgroup.
-template <typename T>
-__global__ __launch_bounds__(256) void finish_kernel(const double *__restrict__ part, int gy, int64_t ld, int64_t np,
+template <typename T, int NR>
+__global__ __launch_bounds__(64 * NR) void finish_kernel(const double *__restrict__ part, int gy, int64_t ld, int64_t np,
                                                      const double *__restrict__ C, T *__restrict__ f_cur,
                                                      uint32_t *__restrict__ flags, uint32_t *__restrict__ fbits,
                                                      const int32_t *__restrict__ skip3, T *__restrict__ cand_v,
@@ -32,7 +33,8 @@ __global__ __launch_bounds__(256) void finish_kernel(const double *__restrict__ 
 {
     const int lane = threadIdx.x & 63;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + lane;
-    const Tri t = combine_segments<4>(part, gy, ld, i, i < np);
+    __shared__ double sh[6 * NR * 64];
+    const Tri t = combine_segments<NR, 64>(part, gy, ld, i, i < np, static_cast<int>(threadIdx.x >> 6), lane, sh);
     if (threadIdx.x < 64) {
         const double sr = t.qr + C[0], si = t.qi + C[1];
         select_group<T>(fma(sr, sr, si * si), blockIdx.x, lane, np, f_cur, flags, fbits, skip3, cand_v, cand_i,
@@ -42,7 +44,7 @@ __global__ __launch_bounds__(256) void finish_kernel(const double *__restrict__ 
     // candidates, as the tail kernel would take them, without that launch
     if (top3_direct != nullptr) {
         __syncthreads();
-        block_top3<T, 256>(cand_v, 3, top3_direct, cand_i);
+        block_top3<T, 64 * NR>(cand_v, 3, top3_direct, cand_i);
     }
 }
 
@@ -146,21 +148,26 @@ qpm_status launch_finish(const double *part, int gy, int64_t ld, int64_t np, con
     const bool tail = (top3_out != nullptr && !mode.defer_leaders && direct == nullptr) || advance;
     int32_t *tail_top3 = mode.defer_leaders || direct != nullptr ? nullptr : top3_out;
     // cand: 3 values per workgroup (T) followed by 3 slots per workgroup (int32)
-    if (f64) {
-        double *cv = top3_out ? static_cast<double *>(cand) : nullptr;
-        int32_t *ci = cv ? reinterpret_cast<int32_t *>(cv + 3 * static_cast<size_t>(blocks)) : nullptr;
-        finish_kernel<double><<<blocks, 256, 0, s>>>(part, gy, ld, np, C, static_cast<double *>(f_cur), flags, fbits,
-                                                     skip3, cv, ci, draws_next, gen, D, k0, k1, inst, acc, next_off,
-                                                     direct, mode.replace_all ? 1 : 0);
-        if (tail) finish_tail_kernel<double><<<1, 256, 0, s>>>(cv, ci, blocks, tail_top3, gen, advance);
-    } else {
-        float *cv = top3_out ? static_cast<float *>(cand) : nullptr;
-        int32_t *ci = cv ? reinterpret_cast<int32_t *>(cv + 3 * static_cast<size_t>(blocks)) : nullptr;
-        finish_kernel<float><<<blocks, 256, 0, s>>>(part, gy, ld, np, C, static_cast<float *>(f_cur), flags, fbits,
-                                                    skip3, cv, ci, draws_next, gen, D, k0, k1, inst, acc, next_off,
-                                                    direct, mode.replace_all ? 1 : 0);
-        if (tail) finish_tail_kernel<float><<<1, 256, 0, s>>>(cv, ci, blocks, tail_top3, gen, advance);
+#define QPM_FINISH(T, NR)                                                                                        \
+    finish_kernel<T, NR><<<blocks, 64 * NR, 0, s>>>(part, gy, ld, np, C, static_cast<T *>(f_cur), flags, fbits,  \
+                                                    skip3, cv, ci, draws_next, gen, D, k0, k1, inst, acc,       \
+                                                    next_off, direct, mode.replace_all ? 1 : 0)
+#define QPM_FINISH_T(T)                                                                                          \
+    {                                                                                                            \
+        T *cv = top3_out ? static_cast<T *>(cand) : nullptr;                                                     \
+        int32_t *ci = cv ? reinterpret_cast<int32_t *>(cv + 3 * static_cast<size_t>(blocks)) : nullptr;         \
+        if (combine_ranges(gy) == kMaxRanges)                                                                    \
+            QPM_FINISH(T, kMaxRanges);                                                                           \
+        else                                                                                                     \
+            QPM_FINISH(T, 4);                                                                                    \
+        if (tail) finish_tail_kernel<T><<<1, 256, 0, s>>>(cv, ci, blocks, tail_top3, gen, advance);              \
     }
+    if (f64)
+        QPM_FINISH_T(double)
+    else
+        QPM_FINISH_T(float)
+#undef QPM_FINISH_T
+#undef QPM_FINISH
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }

@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
 }
 
 // A of genome i over the gy segments of one design (part: [gy][2][ld]),
-// split in NW ranges folded in order as combine_segments_in does for
+// split in NW ranges folded in order as combine_segments does for
 // triples; valid in wave 0.
 template <int NW>
 __device__ __forceinline__ void combine_a_in(const double *__restrict__ part, int gy, int64_t ld, int64_t i,
@@ -185,8 +185,8 @@ __device__ double obj_value(const ObjTabs &tabs, int K, double scale, double G0,
     for (int k = 0; k < K; ++k) {
         double re, im;
         if constexpr (THG) {
-            const Tri t = combine_segments_in<4>(part + static_cast<int64_t>(k) * gy * 6 * ld, gy, ld, i, valid,
-                                                 wave, lane, sh);
+            const Tri t = combine_segments<4, 64>(part + static_cast<int64_t>(k) * gy * 6 * ld, gy, ld, i, valid,
+                                                  wave, lane, sh);
             re = t.qr + tabs.C[k][0];
             im = t.qi + tabs.C[k][1];
         } else {

@@ -43,59 +43,79 @@ __device__ __forceinline__ void tri_append(Tri &t, const Tri &u)
 }
 
 // Segment triples of genome i are stored as part[s][6][ld] (A, B, Q real
-// and imaginary parts). The gy segments are split into NW contiguous
-// ranges, range w = [gy w / NW, gy (w+1) / NW) folded in order by wave w of
-// the workgroup (lane = genome); wave 0 then folds the NW range triples in
-// order. Every caller uses this one association, so a genome's fitness has
-// the same bits whichever kernel combines it. Call from every lane (the
-// workgroup synchronises); the result is valid in wave 0.
-template <int NW>
-__device__ __forceinline__ Tri combine_segments_in(const double *__restrict__ part, int gy, int64_t ld, int64_t i,
-                                                   bool valid, int wave, int lane, double *sh)
+// and imaginary parts). The gy segments are split into NR contiguous ranges,
+// range r = [gy r / NR, gy (r+1) / NR) folded in order by one thread; the NR
+// range triples are then folded in order. NR follows from gy alone
+// (combine_ranges), so a genome's fitness has the same bits whichever kernel
+// combines it. What the fold waits for is the latency of a range's loads, one
+// after the other: N = 5 x 10^4 (196 segments) took 18-19 us in 4 ranges for
+// 256 or 1001 genomes, longer than the evaluation itself, and takes 6.6-7 us
+// in 16 ranges with 8 segments (48 loads) in flight; 98 segments 10.7 and 5 us,
+// 40 segments 4.0-5.9 and 4.8 us, 20 segments 3.8 and 4.7 us (the longer
+// fold of the ranges and more code), so 4 ranges stay below 48 segments.
+constexpr int kMaxRanges = 16;
+__host__ __device__ inline int combine_ranges(int gy) { return gy >= 48 ? kMaxRanges : 4; }
+
+// t <- the segments [s0, s1) of genome i in order, U at a time (every load of
+// a batch goes out before the first is used; those past s1 repeat the last)
+template <int U>
+__device__ __forceinline__ void fold_segments(Tri &t, const double *__restrict__ part, int64_t ld, int64_t i, int s0,
+                                              int s1)
 {
-    const int s0 = static_cast<int>((static_cast<int64_t>(gy) * wave) / NW);
-    const int s1 = static_cast<int>((static_cast<int64_t>(gy) * (wave + 1)) / NW);
-    Tri t{0, 0, 0, 0, 0, 0};
-    if (valid && s0 < s1) {
-        const double *p = part + static_cast<int64_t>(s0) * 6 * ld + i;
-        t = Tri{p[0], p[ld], p[2 * ld], p[3 * ld], p[4 * ld], p[5 * ld]};
-#pragma unroll 4
-        for (int sg = s0 + 1; sg < s1; ++sg) {
-            const double *q = part + static_cast<int64_t>(sg) * 6 * ld + i;
-            tri_append(t, Tri{q[0], q[ld], q[2 * ld], q[3 * ld], q[4 * ld], q[5 * ld]});
-        }
-    }
-    if constexpr (NW > 1) {
-        // sh: [6][NW][64] doubles of this group
+    for (int sg = s0; sg < s1; sg += U) {
+        double v[U][6];
 #pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            const double v = c == 0 ? t.ar : c == 1 ? t.ai : c == 2 ? t.br : c == 3 ? t.bi : c == 4 ? t.qr : t.qi;
-            sh[(c * NW + wave) * 64 + lane] = v;
+        for (int k = 0; k < U; ++k) {
+            const double *q = part + static_cast<int64_t>(min(sg + k, s1 - 1)) * 6 * ld + i;
+#pragma unroll
+            for (int c = 0; c < 6; ++c) v[k][c] = q[c * ld];
         }
-        __syncthreads();
-        if (wave == 0) {
-            for (int w = 1; w < NW; ++w) {
-                const int a = static_cast<int>((static_cast<int64_t>(gy) * w) / NW);
-                const int b = static_cast<int>((static_cast<int64_t>(gy) * (w + 1)) / NW);
-                if (a < b)
-                    tri_append(t, Tri{sh[(0 * NW + w) * 64 + lane], sh[(1 * NW + w) * 64 + lane],
-                                      sh[(2 * NW + w) * 64 + lane], sh[(3 * NW + w) * 64 + lane],
-                                      sh[(4 * NW + w) * 64 + lane], sh[(5 * NW + w) * 64 + lane]});
-            }
-        }
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (sg + k < s1) tri_append(t, Tri{v[k][0], v[k][1], v[k][2], v[k][3], v[k][4], v[k][5]});
     }
-    return t;
 }
 
-// combine_segments_in for a workgroup of NW waves over one group of 64
-// genomes (wave = threadIdx.x / 64)
-template <int NW>
+// A workgroup of NR x NG threads over NG genomes: thread (range, gl) folds
+// the range's segments of genome i; the result is valid in range 0. sh: [6][NR][NG]
+// doubles. Call from every thread (the workgroup synchronises).
+template <int NR, int NG>
 __device__ __forceinline__ Tri combine_segments(const double *__restrict__ part, int gy, int64_t ld, int64_t i,
-                                                bool valid)
+                                                bool valid, int range, int gl, double *sh)
 {
-    __shared__ double sh[6 * NW * 64];
-    return combine_segments_in<NW>(part, gy, ld, i, valid, static_cast<int>(threadIdx.x >> 6),
-                                   static_cast<int>(threadIdx.x & 63), sh);
+    const int s0 = static_cast<int>((static_cast<int64_t>(gy) * range) / NR);
+    const int s1 = static_cast<int>((static_cast<int64_t>(gy) * (range + 1)) / NR);
+    Tri t{0, 0, 0, 0, 0, 0};
+    if (valid) {
+        if constexpr (NR == 4) {
+            if (s0 < s1) {
+                const double *p = part + static_cast<int64_t>(s0) * 6 * ld + i;
+                t = Tri{p[0], p[ld], p[2 * ld], p[3 * ld], p[4 * ld], p[5 * ld]};
+#pragma unroll 4
+                for (int sg = s0 + 1; sg < s1; ++sg) {
+                    const double *q = part + static_cast<int64_t>(sg) * 6 * ld + i;
+                    tri_append(t, Tri{q[0], q[ld], q[2 * ld], q[3 * ld], q[4 * ld], q[5 * ld]});
+                }
+            }
+        } else if (gy <= 2 * NR) {
+            fold_segments<2>(t, part, ld, i, s0, s1);
+        } else {
+            fold_segments<8>(t, part, ld, i, s0, s1);
+        }
+    }
+    const double v[6] = {t.ar, t.ai, t.br, t.bi, t.qr, t.qi};
+#pragma unroll
+    for (int c = 0; c < 6; ++c) sh[(c * NR + range) * NG + gl] = v[c];
+    __syncthreads();
+    if (range == 0) {
+#pragma unroll 4
+        for (int r = 1; r < NR; ++r)
+            if (static_cast<int64_t>(gy) * r / NR < static_cast<int64_t>(gy) * (r + 1) / NR)
+                tri_append(t, Tri{sh[(0 * NR + r) * NG + gl], sh[(1 * NR + r) * NG + gl], sh[(2 * NR + r) * NG + gl],
+                                  sh[(3 * NR + r) * NG + gl], sh[(4 * NR + r) * NG + gl],
+                                  sh[(5 * NR + r) * NG + gl]});
+    }
+    return t;
 }
 
 __device__ __forceinline__ void store_fitness(void *fit, int out_f64, int64_t i, const Tri &t,

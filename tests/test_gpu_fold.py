@@ -1,0 +1,66 @@
+"""The fold of the segments at 47 and 48 segments (4 and 16 ranges), 32 and 33
+(batched) and many more, with partial groups of 16 and 64 genomes; a run whose
+finish step folds 16 ranges. Tolerances are the fitness's own (FP64 1e-12, FP32
+1e-5, plain or against 1 % of the median below it)."""
+import numpy as np
+import pytest
+
+from paper_2511_01255_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = {0: 1e-5, 1: 1e-12}
+
+
+@pytest.fixture(scope="module")
+def q():
+    import torch
+    assert torch.cuda.is_available(), "a GPU is required"
+    from paper_2511_01255_amd import qpm
+    qpm.lib()
+    return qpm
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,npop", [(12032, 17), (12033, 17), (12033, 130), (49153, 15), (98305, 3)])
+def test_fold_matches_oracle(q, orc, n, npop, prec):
+    import torch
+    z = inputs.jittered_boundaries(n, 2.0, 0.2, seed=n)
+    d = inputs.random_signs(npop, n, seed=npop)
+    some = np.unique(np.linspace(0, npop - 1, 24).astype(int))  # (the oracle walks a few of a large population)
+    _, fo = orc.Design(z, inputs.DK1, inputs.DK2).fitness(d[some])
+    D = q.precompute_phases(z, inputs.DK1, inputs.DK2)
+    bits = torch.from_numpy(inputs.pack_bits(d).view(np.int32)).cuda()
+    f = q.eval_fitness(D, bits, npop, prec).double().cpu().numpy()
+    assert np.max(np.abs(f[some] - fo) / np.maximum(fo, 1e-2 * np.median(fo))) <= TOL[prec]
+    # every genome against the per-domain kernel, which the oracle checks elsewhere
+    g = q.eval_fitness(D, bits, npop, 1, kernel=q.FIT_SEGMENTED).cpu().numpy()
+    assert np.max(np.abs(f - g) / np.maximum(g, 1e-2 * np.median(g))) <= 2 * TOL[prec]
+
+
+def test_run_with_sixteen_ranges_equals_oracle(q, orc):
+    n, npop, G = 12065, 70, 3
+    z = inputs.uniform_boundaries(n, 2.0)
+    xo, fo, _ = orc.Design(z, inputs.DK1, inputs.DK2).hwsda_run(npop, G, 0.5, 0.9, 0)
+    D = q.precompute_phases(z, inputs.DK1, inputs.DK2)
+    R = q.Run(D, npop, G, seed=0, prec=q.PREC_F64)
+    R.advance(G)
+    x, f, _, _ = R.read()
+    assert np.array_equal(x.cpu().numpy(), xo)
+    assert np.max(np.abs(f.cpu().numpy() - fo) / fo) <= 1e-12
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("ns,npop", [([2000, 1, 33], 64), ([1000] * 7, 100), ([49153, 70, 4100], 257),
+                                     ([12033] * 9, 330)])
+def test_batch_fold_equals_single(q, ns, npop, prec):
+    import torch
+    zs = [inputs.jittered_boundaries(n, 2.0, 0.2, seed=k) for k, n in enumerate(ns)]
+    B = q.precompute_phases_batched(zs, [inputs.DK1] * len(ns), [inputs.DK2] * len(ns))
+    bits = [torch.from_numpy(inputs.pack_bits(inputs.random_signs(npop, n, seed=k)).view(np.int32)).cuda()
+            for k, n in enumerate(ns)]
+    f = q.batch_eval_fitness(B, torch.cat(bits), npop, prec).double().cpu().numpy()
+    for k, z in enumerate(zs):
+        D = q.precompute_phases(z, inputs.DK1, inputs.DK2)
+        g = q.eval_fitness(D, bits[k], npop, 1, kernel=q.FIT_SEGMENTED).cpu().numpy()
+        assert np.max(np.abs(f[k] - g) / np.maximum(g, 1e-2 * np.median(g))) <= 2 * TOL[prec]
