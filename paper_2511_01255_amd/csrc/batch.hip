@@ -461,10 +461,20 @@ static BatchFitPlan make_tab_plan(const std::vector<InstDesc> &h, int gw, int wp
     return p;
 }
 
-static void default_tab_shape(int64_t np, bool f32, int *gw, int *wpw)
+// Launch shape of the batched table kernel from the work, in waves' words (64-
+// genome groups x words of all instances): as for single designs, small work
+// takes small workgroups. Kernel + combine, us, shape / shape:
+//   FP32  16 designs of 72 words, NP = 100 (1920): 1/2 8.6, 1/4 9.9
+//         10 designs, NP = 400 (3122): 1/2 8.9, 4/4 12.0
+//         32 designs, NP = 256 (94204): 4/5 39.8, 4/4 40.0;  64 (188920): 4/5 66.4, 4/4 69.1
+//   FP64  10 designs, NP = 400: 2/2 9.4, 4/2 10.1;  64, NP = 256: 4/2 108, 2/2 121
+static void default_tab_shape(int64_t np, int64_t words, bool f32, int *gw, int *wpw)
 {
-    *gw = np >= 256 ? 4 : (np >= 128 ? 2 : 1);
-    *wpw = f32 ? 4 : 2;
+    const int64_t groups = (np + 63) / 64;
+    const bool large = groups * words > 12000;
+    const int most = large ? 4 : (f32 ? 1 : 2);
+    *gw = groups >= 4 ? most : (groups >= 2 ? std::min(most, 2) : 1);
+    *wpw = f32 ? (large ? 5 : 2) : 2;
 }
 
 static void default_fit_shape(const std::vector<InstDesc> &h, int64_t np, int *waves, int *wpw)
@@ -747,7 +757,7 @@ QPM_API qpm_status qpm_batch_eval_fitness(qpm_batch b, qpm_prec p, const uint32_
     BatchFitPlan pl;
     if (waves_per_group == 0 && words_per_wave == 0) {
         int gw, wpw;
-        default_tab_shape(np, p == QPM_PREC_F32, &gw, &wpw);
+        default_tab_shape(np, b->total_words, p == QPM_PREC_F32, &gw, &wpw);
         pl = make_tab_plan(b->host, gw, wpw);
     } else {
         int waves, wpw;
@@ -1018,7 +1028,7 @@ static qpm_status tune_fitness(qpm_batch_run_s *r)
     QPM_TRY_HIP(hipEventCreate(&e1));
     float best = 1e30f;
     std::pair<int, int> pick{1, 1};
-    default_tab_shape(c.np, p == QPM_PREC_F32, &pick.first, &pick.second);
+    default_tab_shape(c.np, r->bt->total_words, p == QPM_PREC_F32, &pick.first, &pick.second);
     for (auto cand : cands) {
         BatchFitPlan pl = make_tab_plan(r->bt->host, cand.first, cand.second);
         if (pl.segs.size() > 65535) continue;
@@ -1267,7 +1277,7 @@ QPM_API qpm_status qpm_batch_run_create(qpm_batch b, const qpm_run_config *cfg, 
         st = tune_fitness(r);
     } else {
         int gw, wpw;
-        default_tab_shape(c.np, c.prec == QPM_PREC_F32, &gw, &wpw);
+        default_tab_shape(c.np, b->total_words, c.prec == QPM_PREC_F32, &gw, &wpw);
         r->fplan = make_tab_plan(b->host, gw, wpw);
     }
     if (st == QPM_OK && r->fplan.segs.size() > 65535) {

@@ -246,6 +246,30 @@ FitPlan plan_fitness_table(const Design &d, qpm_prec p, int gw, int wpw)
     return pl;
 }
 
+// Launch shape of the table kernel (genome groups per workgroup, words per
+// wave) from the work, in waves' words: 64-genome groups x words. Small work
+// takes small workgroups (a wave walks its words one after the other, and
+// few large ones leave CUs idle); large work takes large ones, which stage
+// each table for more genomes. Kernel + combine, us, shape / shape:
+//   FP32  N = 1000, NP = 256 (128): 1/2 6.3, 2/4 7.2
+//         10^4, 1024 (5008): 1/4 9.4, 4/4 11.8;  3000, 5000 (7426): 1/4 9.6, 4/4 10.8
+//         6600, 5000 (16353): 4/5 13.0, 4/4 16.4, 1/4 16.3
+//         10^4, 4096 (20032): 4/5 14.9, 4/4 17.1;  5 x 10^4, 1001 (25008): 4/5 19.3, 2/4 20.9
+//   FP64  10^4, 1024: 1/2 10.4, 4/2 12.3;  5 x 10^4, 256 (6252): 2/2 13.6, 1/2 16.6
+//         3000, 5000: 2/2 10.3, 1/2 11.7;  10^4, 4096: 2/2 19.4, 4/2 20.5
+static void table_shape(bool f32, int64_t np, int64_t words, int *gw, int *wpw)
+{
+    const int64_t groups = (np + 63) / 64, work = groups * words;
+    if (f32) {
+        const bool large = work > 12000;
+        *gw = large ? (groups >= 16 ? 4 : (groups >= 8 ? 2 : 1)) : 1;
+        *wpw = large ? 5 : (work > 256 ? 4 : 2);
+    } else {
+        *gw = work > 6000 && groups >= 2 ? 2 : 1;
+        *wpw = 2;
+    }
+}
+
 FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
 {
     FitPlan pl;
@@ -255,9 +279,8 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
         return pl;
     }
     if (kernel == QPM_FIT_AUTO || kernel == QPM_FIT_TABLE) {
-        // 48 KB of tables per workgroup: 4 wpw words of 3 KB (FP32) or 6 KB
-        const int wpw = p == QPM_PREC_F32 ? 4 : 2;
-        const int gw = np >= 1024 ? 4 : (np >= 256 ? 2 : 1);
+        int gw, wpw;
+        table_shape(p == QPM_PREC_F32, np, d.words, &gw, &wpw);
         return plan_fitness_table(d, p, gw, wpw);
     }
     pl.kind = QPM_FIT_SEGMENTED;

@@ -1,0 +1,54 @@
+"""The default launch shapes of the table fitness at the sizes where they change:
+256 and 12,000 wave words of work, 6,000 in FP64, 8 and 16 genome groups.
+Tolerances are the fitness's own (FP64 1e-12, FP32 1e-5, plain or against 1 % of
+the median below it)."""
+import numpy as np
+import pytest
+
+from paper_2511_01255_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = {0: 1e-5, 1: 1e-12}
+
+
+@pytest.fixture(scope="module")
+def q():
+    import torch
+    assert torch.cuda.is_available(), "a GPU is required"
+    from paper_2511_01255_amd import qpm
+    qpm.lib()
+    return qpm
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,npop", [(8192, 64), (8193, 64), (24000, 1024), (24064, 1024), (48001, 511),
+                                    (48001, 513)])
+def test_default_shape_matches_oracle(q, orc, n, npop, prec):
+    import torch
+    z = inputs.jittered_boundaries(n, 2.0, 0.2, seed=n)
+    d = inputs.random_signs(npop, n, seed=npop)
+    some = np.unique(np.linspace(0, npop - 1, 24).astype(int))  # (the oracle walks a few of a large population)
+    _, fo = orc.Design(z, inputs.DK1, inputs.DK2).fitness(d[some])
+    D = q.precompute_phases(z, inputs.DK1, inputs.DK2)
+    bits = torch.from_numpy(inputs.pack_bits(d).view(np.int32)).cuda()
+    f = q.eval_fitness(D, bits, npop, prec).double().cpu().numpy()
+    assert np.max(np.abs(f[some] - fo) / np.maximum(fo, 1e-2 * np.median(fo))) <= TOL[prec]
+    # every genome against the per-domain kernel, which the oracle checks elsewhere
+    g = q.eval_fitness(D, bits, npop, 1, kernel=q.FIT_SEGMENTED).cpu().numpy()
+    assert np.max(np.abs(f - g) / np.maximum(g, 1e-2 * np.median(g))) <= 2 * TOL[prec]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("ns,npop", [([1000] * 7, 100), ([32000, 32000, 32000], 256), ([32000, 32000, 32033], 256)])
+def test_batch_default_shape_equals_single(q, ns, npop, prec):
+    import torch
+    zs = [inputs.jittered_boundaries(n, 2.0, 0.2, seed=k) for k, n in enumerate(ns)]
+    B = q.precompute_phases_batched(zs, [inputs.DK1] * len(ns), [inputs.DK2] * len(ns))
+    bits = [torch.from_numpy(inputs.pack_bits(inputs.random_signs(npop, n, seed=k)).view(np.int32)).cuda()
+            for k, n in enumerate(ns)]
+    f = q.batch_eval_fitness(B, torch.cat(bits), npop, prec).double().cpu().numpy()
+    for k, z in enumerate(zs):
+        D = q.precompute_phases(z, inputs.DK1, inputs.DK2)
+        g = q.eval_fitness(D, bits[k], npop, 1, kernel=q.FIT_SEGMENTED).cpu().numpy()
+        assert np.max(np.abs(f[k] - g) / np.maximum(g, 1e-2 * np.median(g))) <= 2 * TOL[prec]
