@@ -10,6 +10,7 @@
 // workgroup's words to LDS and walks the words again from registers. SHG
 // needs only the A row of each table (sum d a of a 4-domain block), THG
 // the whole (A, B, Q) triple.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -145,93 +146,143 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
     }
 }
 
-// A of genome i over the gy segments of one design (part: [gy][2][ld]),
-// split in NW ranges folded in order as combine_segments does for
-// triples; valid in wave 0.
-template <int NW>
-__device__ __forceinline__ void combine_a_in(const double *__restrict__ part, int gy, int64_t ld, int64_t i,
-                                             bool valid, int wave, int lane, double *sh, double &ar, double &ai)
-{
-    const int s0 = static_cast<int>((static_cast<int64_t>(gy) * wave) / NW);
-    const int s1 = static_cast<int>((static_cast<int64_t>(gy) * (wave + 1)) / NW);
-    ar = 0.0;
-    ai = 0.0;
-    if (valid)
-        for (int sg = s0; sg < s1; ++sg) {
-            const double *q = part + static_cast<int64_t>(sg) * 2 * ld + i;
-            ar += q[0];
-            ai += q[ld];
-        }
-    sh[(0 * NW + wave) * 64 + lane] = ar;
-    sh[(1 * NW + wave) * 64 + lane] = ai;
-    __syncthreads();
-    if (wave == 0)
-        for (int w = 1; w < NW; ++w) {
-            ar += sh[(0 * NW + w) * 64 + lane];
-            ai += sh[(1 * NW + w) * 64 + lane];
-        }
-}
-
-// -h of genome i from the K designs' segment partials; valid in wave 0
-// (every thread of the 4-wave workgroup calls it). G (optional): G_k at
-// G[k ldG + i].
-template <bool THG>
-__device__ double obj_value(const ObjTabs &tabs, int K, double scale, double G0, double beta,
+// -h of the NG genomes of a workgroup from the K designs' segment partials,
+// for a workgroup of 256 threads or more (a multiple of NG). The segments of a
+// design are split in 4 ranges folded in order by one thread each; the
+// (design, range) pairs of a genome are spread over the workgroup's threads, so
+// their loads overlap (one design after the other, with 64 genomes per
+// workgroup, took 12.6 us for 24 segments of 5 SHG designs at NP = 5000 and
+// 37.7 us for 104 segments at NP = 1500, against 6.4 and 23.4 us), in batches
+// of kb designs (kb NC 4 NG doubles of LDS);
+// then one thread per genome and design folds the 4 ranges in order, and one
+// per genome takes the objective. Valid in the first NG threads (gl =
+// threadIdx.x). G (optional): G_k at G[k ldG + i]. sh: kb 4 NC NG doubles, gk: K
+// NG doubles.
+template <bool THG, int NG>
+__device__ double obj_value(const ObjTabs &tabs, int K, int kb, double scale, double G0, double beta,
                             const double *__restrict__ part, int gy, int64_t ld, int64_t i, bool valid, double *G,
-                            int64_t ldG, double *sh)
+                            int64_t ldG, double *sh, double *gk)
 {
-    const int wave = static_cast<int>(threadIdx.x >> 6), lane = static_cast<int>(threadIdx.x & 63);
-    double sum = 0.0, gmax = 0.0, gmin = 0.0;
-    for (int k = 0; k < K; ++k) {
-        double re, im;
-        if constexpr (THG) {
-            const Tri t = combine_segments<4, 64>(part + static_cast<int64_t>(k) * gy * 6 * ld, gy, ld, i, valid,
-                                                  wave, lane, sh);
-            re = t.qr + tabs.C[k][0];
-            im = t.qi + tabs.C[k][1];
-        } else {
-            combine_a_in<4>(part + static_cast<int64_t>(k) * gy * 2 * ld, gy, ld, i, valid, wave, lane, sh, re, im);
+    constexpr int NC = ObjShape<THG>::NC;
+    constexpr int NR = 4;
+    const int gl = static_cast<int>(threadIdx.x) % NG, slot = static_cast<int>(threadIdx.x) / NG;
+    const int slots = static_cast<int>(blockDim.x) / NG;
+    for (int k0 = 0; k0 < K; k0 += kb) {
+        const int kn = min(kb, K - k0);
+        for (int task = slot; task < NR * kn; task += slots) {
+            const int kd = task / NR, r = task % NR;
+            const int s0 = static_cast<int>((static_cast<int64_t>(gy) * r) / NR);
+            const int s1 = static_cast<int>((static_cast<int64_t>(gy) * (r + 1)) / NR);
+            const double *pk = part + static_cast<int64_t>(k0 + kd) * gy * NC * ld + i;
+            double v[NC] = {};
+            if (valid) {
+                if constexpr (THG) {
+                    Tri t{0, 0, 0, 0, 0, 0};
+#pragma unroll 4
+                    for (int sg = s0; sg < s1; ++sg) {
+                        const double *q = pk + static_cast<int64_t>(sg) * 6 * ld;
+                        tri_append(t, Tri{q[0], q[ld], q[2 * ld], q[3 * ld], q[4 * ld], q[5 * ld]});
+                    }
+                    v[0] = t.ar;
+                    v[1] = t.ai;
+                    v[2] = t.br;
+                    v[3] = t.bi;
+                    v[4] = t.qr;
+                    v[5] = t.qi;
+                } else {
+#pragma unroll 8
+                    for (int sg = s0; sg < s1; ++sg) {
+                        const double *q = pk + static_cast<int64_t>(sg) * 2 * ld;
+                        v[0] += q[0];
+                        v[1] += q[ld];
+                    }
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) sh[((kd * NC + c) * NR + r) * NG + gl] = v[c];
         }
-        __syncthreads();  // sh is reused by the next design
-        const double Gk = sqrt(fma(re, re, im * im)) * scale;
-        if (G && wave == 0 && valid) G[k * ldG + i] = Gk;
-        sum += fabs(G0 - Gk);
-        gmax = k == 0 ? Gk : fmax(gmax, Gk);
-        gmin = k == 0 ? Gk : fmin(gmin, Gk);
+        __syncthreads();
+        for (int kd = slot; kd < kn; kd += slots) {
+            auto at = [&](int c, int r) -> double { return sh[((kd * NC + c) * NR + r) * NG + gl]; };
+            double re, im;
+            if constexpr (THG) {
+                Tri t{at(0, 0), at(1, 0), at(2, 0), at(3, 0), at(4, 0), at(5, 0)};
+#pragma unroll
+                for (int r = 1; r < NR; ++r)
+                    tri_append(t, Tri{at(0, r), at(1, r), at(2, r), at(3, r), at(4, r), at(5, r)});
+                re = t.qr + tabs.C[k0 + kd][0];
+                im = t.qi + tabs.C[k0 + kd][1];
+            } else {
+                re = ((at(0, 0) + at(0, 1)) + at(0, 2)) + at(0, 3);
+                im = ((at(1, 0) + at(1, 1)) + at(1, 2)) + at(1, 3);
+            }
+            const double Gk = sqrt(fma(re, re, im * im)) * scale;
+            gk[(k0 + kd) * NG + gl] = Gk;
+            if (G && valid) G[(k0 + kd) * ldG + i] = Gk;
+        }
+        __syncthreads();
+    }
+    double sum = 0.0, gmax = 0.0, gmin = 0.0;
+    if (slot == 0) {
+        for (int k = 0; k < K; ++k) {
+            const double Gk = gk[k * NG + gl];
+            sum += fabs(G0 - Gk);
+            gmax = k == 0 ? Gk : fmax(gmax, Gk);
+            gmin = k == 0 ? Gk : fmin(gmin, Gk);
+        }
     }
     return -(sum + beta * (gmax - gmin));
 }
 
-template <typename T, bool THG>
-__global__ __launch_bounds__(256) void obj_values_kernel(ObjTabs tabs, int K, double scale, double G0, double beta,
-                                                         const double *__restrict__ part, int gy, int64_t ld,
-                                                         int64_t np, T *__restrict__ fit, double *__restrict__ G,
-                                                         int64_t ldG)
+// designs folded together by obj_value, and its LDS
+template <bool THG, int NG>
+int obj_value_batch(int K)
 {
-    __shared__ double sh[6 * 4 * 64];
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63);
+    const int per = ObjShape<THG>::NC * 4 * NG * static_cast<int>(sizeof(double));
+    return std::min(K, std::max(1, (48 << 10) / per));
+}
+template <bool THG, int NG>
+size_t obj_value_lds(int K)
+{
+    return sizeof(double) * NG *
+           (static_cast<size_t>(ObjShape<THG>::NC) * 4 * obj_value_batch<THG, NG>(K) + static_cast<size_t>(K));
+}
+
+// 16 genomes per workgroup (a 128-byte line of each component) x 16 slots
+constexpr int kObjGenomes = 16;
+template <typename T, bool THG>
+__global__ __launch_bounds__(256) void obj_values_kernel(ObjTabs tabs, int K, int kb, double scale, double G0,
+                                                         double beta, const double *__restrict__ part, int gy,
+                                                         int64_t ld, int64_t np, T *__restrict__ fit,
+                                                         double *__restrict__ G, int64_t ldG)
+{
+    extern __shared__ double osh[];
+    constexpr int NG = kObjGenomes;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * NG + threadIdx.x % NG;
     const bool valid = i < np;
-    const double v = obj_value<THG>(tabs, K, scale, G0, beta, part, gy, ld, i, valid, G, ldG, sh);
-    if (threadIdx.x < 64 && valid) fit[i] = static_cast<T>(v);
+    const double v = obj_value<THG, NG>(tabs, K, kb, scale, G0, beta, part, gy, ld, i, valid, G, ldG, osh,
+                                        osh + ObjShape<THG>::NC * 4 * kb * NG);
+    if (threadIdx.x < NG && valid) fit[i] = static_cast<T>(v);
 }
 
 // the run's finish step on the objective: as finish_kernel, with the
-// fitness -h
+// fitness -h (64 genomes x 16 slots)
 template <typename T, bool THG>
-__global__ __launch_bounds__(256) void obj_finish_kernel(ObjTabs tabs, int K, double scale, double G0, double beta,
-                                                         const double *__restrict__ part, int gy, int64_t ld,
-                                                         int64_t np, T *__restrict__ f_cur,
-                                                         uint32_t *__restrict__ flags, uint32_t *__restrict__ fbits,
-                                                         const int32_t *__restrict__ skip3, T *__restrict__ cand_v,
-                                                         int32_t *__restrict__ cand_i, int4 *__restrict__ draws_next,
-                                                         const uint32_t *__restrict__ gen, int64_t D, uint32_t k0,
-                                                         uint32_t k1, uint32_t inst, AcceptOut acc, uint32_t next_off,
-                                                         int replace_all)
+__global__ __launch_bounds__(1024) void obj_finish_kernel(ObjTabs tabs, int K, int kb, double scale, double G0,
+                                                          double beta, const double *__restrict__ part, int gy,
+                                                          int64_t ld, int64_t np, T *__restrict__ f_cur,
+                                                          uint32_t *__restrict__ flags, uint32_t *__restrict__ fbits,
+                                                          const int32_t *__restrict__ skip3, T *__restrict__ cand_v,
+                                                          int32_t *__restrict__ cand_i, int4 *__restrict__ draws_next,
+                                                          const uint32_t *__restrict__ gen, int64_t D, uint32_t k0,
+                                                          uint32_t k1, uint32_t inst, AcceptOut acc, uint32_t next_off,
+                                                          int replace_all)
 {
-    __shared__ double sh[6 * 4 * 64];
+    extern __shared__ double osh[];
     const int lane = threadIdx.x & 63;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + lane;
-    const double v = obj_value<THG>(tabs, K, scale, G0, beta, part, gy, ld, i, i < np, nullptr, 0, sh);
+    const double v = obj_value<THG, 64>(tabs, K, kb, scale, G0, beta, part, gy, ld, i, i < np, nullptr, 0, osh,
+                                        osh + ObjShape<THG>::NC * 4 * kb * 64);
     if (threadIdx.x < 64)
         select_group<T>(v, blockIdx.x, lane, np, f_cur, flags, fbits, skip3, cand_v, cand_i, draws_next, gen, D, k0,
                         k1, inst, acc, next_off, replace_all != 0);
@@ -247,13 +298,18 @@ ObjPlan plan_objective_shape(const Objective &o, int wpw)
 
 ObjPlan plan_objective(const Objective &o, qpm_prec p, int64_t np)
 {
-    // the most words per wave (fewest partials) that still gives about
-    // 2048 workgroups (8 per CU, so staging and walking overlap across
-    // workgroups), at most the register limit of the word cache
+    // the most words per wave (fewest partials to write and fold) that still
+    // leaves 400 workgroups, or 256 for 2 words, at most the register limit of
+    // the word cache. Partials + values, us, by words per wave: 3000 x 5000, 5
+    // SHG wavelengths FP32: 1 13.3 + 6.4, 2 10.4 + 4.4, 4 10.8 + 3.9, 5 12.3 +
+    // 3.9; 13200 x 1500: 1 14.5 + 23.4, 2 11.2 + 12.3, 5 12.3 + 6.1 (THG, 3
+    // designs: 1 19.9 + 12.6, 2 16.6 + 7.4, 5 18.9 + 4.7); 6000 x 1000 THG, 2
+    // designs: 1 7.6 + 8.3, 2 8.1 + 4.6, 3 8.9 + 4.0; 1000 x 300: 1 4.9 + 3.2, 2
+    // 5.4 + 2.9.
     const bool f32 = p == QPM_PREC_F32;
     const int64_t groups = (np + 63) / 64;
     int wpw = table_max_wpw(f32);
-    while (wpw > 1 && groups * ((o.words + 4 * wpw - 1) / (4 * wpw)) < 2048) --wpw;
+    while (wpw > 1 && groups * ((o.words + 4 * wpw - 1) / (4 * wpw)) < (wpw > 2 ? 400 : 256)) --wpw;
     while (wpw < table_max_wpw(f32) && (o.words + 4 * wpw - 1) / (4 * wpw) > 65535) ++wpw;
     return plan_objective_shape(o, wpw);
 }
@@ -291,11 +347,12 @@ qpm_status launch_objective_partials(const Objective &o, qpm_prec p, const uint3
 qpm_status launch_objective_values(const Objective &o, const ObjPlan &pl, const double *part, int64_t ld, int64_t np,
                                    void *fitness, bool f64, double *G, int64_t ldG, hipStream_t s)
 {
-    const unsigned blocks = static_cast<unsigned>((np + 63) / 64);
+    const unsigned blocks = static_cast<unsigned>((np + kObjGenomes - 1) / kObjGenomes);
     const bool thg = o.kind == QPM_OBJ_THG;
 #define QPM_OV(T, H)                                                                                             \
-    obj_values_kernel<T, H><<<blocks, 256, 0, s>>>(o.tabs, o.K, o.scale, o.G0, o.beta, part, pl.gy, ld, np,     \
-                                                   static_cast<T *>(fitness), G, ldG)
+    obj_values_kernel<T, H><<<blocks, 256, obj_value_lds<H, kObjGenomes>(o.K), s>>>(                             \
+        o.tabs, o.K, obj_value_batch<H, kObjGenomes>(o.K), o.scale, o.G0, o.beta, part, pl.gy, ld, np,           \
+        static_cast<T *>(fitness), G, ldG)
     if (f64) {
         if (thg) QPM_OV(double, true); else QPM_OV(double, false);
     } else {
@@ -324,10 +381,10 @@ qpm_status launch_objective_finish(const Objective &o, const ObjPlan &pl, const 
     {                                                                                                             \
         T *cv = top3_out ? static_cast<T *>(cand) : nullptr;                                                      \
         int32_t *ci = cv ? reinterpret_cast<int32_t *>(cv + 3 * static_cast<size_t>(blocks)) : nullptr;          \
-        obj_finish_kernel<T, H><<<blocks, 256, 0, s>>>(o.tabs, o.K, o.scale, o.G0, o.beta, part, pl.gy, ld, np,  \
-                                                       static_cast<T *>(f_cur), flags, fbits, skip3, cv, ci,     \
-                                                       draws_next, gen, D, k0, k1, inst, acc, next_off,          \
-                                                       mode.replace_all ? 1 : 0);                                 \
+        obj_finish_kernel<T, H><<<blocks, 1024, obj_value_lds<H, 64>(o.K), s>>>(                                 \
+            o.tabs, o.K, obj_value_batch<H, 64>(o.K), o.scale, o.G0, o.beta, part, pl.gy, ld, np,                \
+            static_cast<T *>(f_cur), flags, fbits, skip3, cv, ci, draws_next, gen, D, k0, k1, inst, acc,         \
+            next_off, mode.replace_all ? 1 : 0);                                                                 \
         if (tail) finish_tail_kernel<T><<<1, 256, 0, s>>>(cv, ci, blocks, tail_top3, gen, advance);               \
     }
     if (f64) {
