@@ -214,6 +214,15 @@ qpm_status qpm_de_step_shape(const float *x, int64_t np, int64_t D, int64_t ldx,
                              int32_t passes, qpm_stream s);
 
 /*
+ * qpm_de_step_whole -- qpm_de_step, and genes D .. ldx - 1 of u and bit
+ * columns np .. ld - 1 of u_bits (which qpm_de_step leaves alone) are set to
+ * 0, so neither needs clearing first. Errors: as qpm_de_step.
+ */
+qpm_status qpm_de_step_whole(const float *x, int64_t np, int64_t D, int64_t ldx, float F, float CR,
+                             uint64_t seed, uint32_t generation, uint32_t inst, float *u,
+                             uint32_t *u_bits, int64_t ld, qpm_stream s);
+
+/*
  * qpm_gwo_step -- grey-wolf update of the omega wolves (paper Sec. 2.2.2):
  * per gene j of a non-leader i and leader k in (alpha, beta, delta), with
  * r1 = lo16(u) 2^-16 and r2 = hi16(u) 2^-16 of one Philox word,
@@ -257,6 +266,17 @@ qpm_status qpm_gwo_step(const float *x, int64_t np, int64_t D, int64_t ldx,
                         const int32_t *leaders, float a, uint64_t seed, uint32_t generation,
                         uint32_t inst, int32_t variant, float *y, uint32_t *y_bits, int64_t ld,
                         qpm_stream s);
+/*
+ * qpm_gwo_step_whole -- qpm_gwo_step, and what it leaves untouched is
+ * written too: the leader rows of y and genes D .. ldx - 1 of every row are
+ * those of x, the leaders' bit columns and columns np .. ld - 1 of y_bits are
+ * 0. y needs no copy of x and y_bits no clearing first. Errors: as
+ * qpm_gwo_step.
+ */
+qpm_status qpm_gwo_step_whole(const float *x, int64_t np, int64_t D, int64_t ldx,
+                              const int32_t *leaders, float a, uint64_t seed, uint32_t generation,
+                              uint32_t inst, int32_t variant, float *y, uint32_t *y_bits, int64_t ld,
+                              qpm_stream s);
 
 /*
  * qpm_relax_forward -- the relaxation d = tanh(theta) of a design (not in

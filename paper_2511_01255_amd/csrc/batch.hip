@@ -308,8 +308,9 @@ __global__ __launch_bounds__(256) void batch_de_kernel(BatchPop bp, const InstDe
     if (t < IPB) d = draws[tl.inst * np + min(static_cast<int64_t>(gi) * IPB + t, np - 1)];
     if (t < fw) sfb[t] = fbits[static_cast<int64_t>(tl.inst) * fw + t];
     __syncthreads();
-    de_rows<IPW, R, OFF>(view_of(bp, id, tl.inst), gi, tl.chunk, F, cr_max, gen[0],
-                         inst0 + static_cast<uint32_t>(tl.inst), k0, k1, bits + id.wofs * ld, ld, store_genes != 0, d,
+    const PopView pv = view_of(bp, id, tl.inst);
+    de_rows<IPW, R, OFF>(pv, gi, tl.chunk, F, cr_max, gen[0], inst0 + static_cast<uint32_t>(tl.inst), k0, k1,
+                         bits + id.wofs * ld, ld, store_genes != 0, pv.D, pv.np, d,
                          [&](int r) -> bool { return ((sfb[r >> 5] >> (r & 31)) & 1u) != 0u; });
 }
 

@@ -263,11 +263,13 @@ inline int de_passes(int64_t pairs) { return pairs >= 4096 ? 4 : (pairs >= 1024 
 // (each workgroup then draws for its own); ipw: individuals per wave of the
 // DE kernel (1, 2 or 4; 0 = chosen from np); passes: groups of individuals
 // per workgroup (1, 2 or 4; 0 = chosen from the sizes); fbits: optional
-// packed copy of pv.flags (bit i % 32 of word i / 32)
+// packed copy of pv.flags (bit i % 32 of word i / 32); whole: genes D .. ldx - 1
+// of the trials and bit columns np .. ld - 1 are written as 0
 qpm_status launch_de(const PopView &pv, float F, float CR, uint64_t seed, const uint32_t *gen_dev,
                      uint32_t gen, uint32_t inst, uint32_t *bits, int64_t ld, const int4 *draws,
                      hipStream_t s, int ipw = 0, int passes = 0, const uint32_t *fbits = nullptr,
-                     const float *F_tab = nullptr, bool store_genes = true, uint32_t *reset_cnt = nullptr);
+                     const float *F_tab = nullptr, bool store_genes = true, uint32_t *reset_cnt = nullptr,
+                     bool whole = false);
 // store_genes = false: the DE kernel writes the trials' bits only (and
 // zeroes reset_cnt); launch_materialize then writes the genes of the
 // accepted trials listed by the finish step (list, *cnt), reading the
@@ -289,10 +291,13 @@ size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw);
 // DE draws of generation *gen_dev for every individual
 qpm_status launch_draws(int64_t np, int64_t D, uint64_t seed, const uint32_t *gen_dev, uint32_t inst, int4 *draws,
                         hipStream_t s);
-// leaders: device int32[3], or nullptr and the three by value in lead_c
+// leaders: device int32[3], or nullptr and the three by value in lead_c;
+// whole: leader rows and genes D .. ldx - 1 are copied, the leaders' bit
+// columns and columns np .. ld - 1 written as 0
 qpm_status launch_gwo(const PopView &pv, const int32_t *leaders, const float *a_tab, float a,
                       uint64_t seed, const uint32_t *gen_dev, uint32_t gen, uint32_t inst,
-                      int variant, uint32_t *bits, int64_t ld, hipStream_t s, int4 lead_c = int4{});
+                      int variant, uint32_t *bits, int64_t ld, hipStream_t s, int4 lead_c = int4{},
+                      bool whole = false);
 // the improved discrete four-leader step (leaders: 4 slots, the first three
 // kept, on the device or by value in lead_c; par_tab[g] or
 // par = {t, 1 - 2 eps, eps, lambda})

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void de_kernel(PopView pv, const int4 *__restr
                                                  uint32_t k0, uint32_t k1, const uint32_t *__restrict__ gen_dev,
                                                  uint32_t gen_c, uint32_t inst, uint32_t *__restrict__ bits,
                                                  int64_t ld, int groups, int chunks, int store_genes,
-                                                 uint32_t *__restrict__ reset_cnt)
+                                                 int64_t cols, int64_t rows, uint32_t *__restrict__ reset_cnt)
 {
     extern __shared__ uint32_t sfb[];  // STAGED with flags: (np + 31) / 32 flag words
     const uint32_t b = blockIdx.x;
@@ -110,11 +110,11 @@ __global__ __launch_bounds__(256) void de_kernel(PopView pv, const int4 *__restr
             __syncthreads();
         }
         de_rows<IPW, R, uint32_t>(
-            pv, gi, c, Fg, cr_max, g, inst, k0, k1, bits, ld, store_genes != 0, d,
+            pv, gi, c, Fg, cr_max, g, inst, k0, k1, bits, ld, store_genes != 0, cols, rows, d,
             [&](int r) -> bool { return fbits != nullptr && ((sfb[r >> 5] >> (r & 31)) & 1u) != 0u; });
     } else {
         de_rows<IPW, R, uint64_t>(
-            pv, gi, c, Fg, cr_max, g, inst, k0, k1, bits, ld, store_genes != 0, d,
+            pv, gi, c, Fg, cr_max, g, inst, k0, k1, bits, ld, store_genes != 0, cols, rows, d,
             [&](int r) -> bool { return pv.flags != nullptr && pv.flags[r] != 0u; });
     }
 }
@@ -223,38 +223,46 @@ qpm_status launch_materialize(const PopView &pv, const int4 *draws, const uint32
 // (x mod 8) ceil(np / 8) + x / 8. Each XCD thus owns a contiguous range of
 // individuals and the 32-bit bit words of neighbouring individuals, which
 // share cache lines, are written from one L2 instead of eight.
+// `whole`: what the update leaves alone is written too (leader rows and genes
+// past D as they are in x, 0 in the leaders' bit columns and in those past
+// np), so that the caller needs no copy of x and no cleared words first: at
+// 5000 x 6600 genes the copy and the clear took 54 us beside 62 for the step.
 template <int VARIANT>
 __global__ __launch_bounds__(256) void gwo_kernel(PopView pv, const int32_t *__restrict__ leaders, int4 lead_c,
                                                   const float *__restrict__ a_tab, float a_c, uint32_t k0, uint32_t k1,
                                                   const uint32_t *__restrict__ gen_dev, uint32_t gen_c, uint32_t inst,
-                                                  uint32_t *__restrict__ bits, int64_t ld, int64_t per_xcd)
+                                                  uint32_t *__restrict__ bits, int64_t ld, int64_t per_xcd,
+                                                  int whole)
 {
     const int64_t np = pv.np, D = pv.D;
     const int64_t i = static_cast<int64_t>(blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
-    if (i >= np) return;
+    if (i >= (whole ? ld : np)) return;
     // leaders from the device (runs) or by value (the entry point)
     const int64_t L0 = leaders ? leaders[0] : lead_c.x, L1 = leaders ? leaders[1] : lead_c.y,
                   L2 = leaders ? leaders[2] : lead_c.z;
     // leaders keep their positions; indices outside the population make
     // the launch a no-op instead of an out-of-bounds read
-    if (i == L0 || i == L1 || i == L2) return;
+    const bool kept = i == L0 || i == L1 || i == L2 || i >= np;
+    if (kept && !whole) return;
     if (L0 < 0 || L0 >= np || L1 < 0 || L1 >= np || L2 < 0 || L2 >= np) return;
     const uint32_t g = gen_dev ? gen_dev[0] : gen_c;
     const float a = a_tab ? a_tab[g] : a_c;
     const float two_a = 2.0f * a;
 
     const int64_t q = static_cast<int64_t>(blockIdx.y) * 256 + threadIdx.x;
-    const int64_t j0 = 4 * q;
-    const bool valid = j0 < D;
+    const int64_t j0 = 4 * q, cols = whole ? pv.ldx : D;
     uint32_t nib = 0;
-    if (valid) {
+    if (kept || j0 >= D) {
+        if (i < np && j0 < cols)
+            store_quad_nt(out_row_of(pv, i), j0, cols, *reinterpret_cast<const float4 *>(row_of(pv, i) + j0));
+    } else {
         const float4 xv = *reinterpret_cast<const float4 *>(row_of(pv, i) + j0);
         const float4 X0 = *reinterpret_cast<const float4 *>(row_of(pv, L0) + j0);
         const float4 X1 = *reinterpret_cast<const float4 *>(row_of(pv, L1) + j0);
         const float4 X2 = *reinterpret_cast<const float4 *>(row_of(pv, L2) + j0);
         const float4 yv4 = gwo_quad<VARIANT>(xv, X0, X1, X2, static_cast<uint32_t>(q), static_cast<uint32_t>(i), g,
                                              inst, k0, k1, a, two_a);
-        store_quad_nt(out_row_of(pv, i), j0, D, yv4);
+        store_quad_nt(out_row_of(pv, i), j0, D, cols, yv4, xv);
         nib = quad_nibble(yv4, j0, D);
     }
     store_word(nib, q, D, bits, ld, i);
@@ -417,7 +425,7 @@ qpm_status launch_init(int64_t np, int64_t D, int64_t ldx, uint64_t seed, uint32
 qpm_status launch_de(const PopView &pv, float F, float CR, uint64_t seed, const uint32_t *gen_dev, uint32_t gen,
                      uint32_t inst, uint32_t *bits, int64_t ld, const int4 *draws, hipStream_t s,
                      int ipw_req, int passes, const uint32_t *fbits, const float *F_tab, bool store_genes,
-                     uint32_t *reset_cnt)
+                     uint32_t *reset_cnt, bool whole)
 {
     QPM_REQUIRE(F_tab == nullptr || gen_dev != nullptr, QPM_EINVAL, "an F table needs the device generation");
     QPM_REQUIRE(store_genes || fbits != nullptr, QPM_EINVAL, "trials that are not stored need the packed flags");
@@ -434,11 +442,14 @@ qpm_status launch_de(const PopView &pv, float F, float CR, uint64_t seed, const 
     const int ipw_auto = row_bytes >= 1024 ? 1 : (row_bytes >= 512 ? 2 : 4);
     const int ipw = (ipw_req == 1 || ipw_req == 2 || ipw_req == 4) ? ipw_req : ipw_auto;
     const int64_t cw = 256 / ipw;
-    const int64_t chunks = (pv.D + cw - 1) / cw;
+    // whole rows: the padding costs part of a chunk and of a row group, where
+    // clearing u and its words first cost a pass (10000 x 4096: 21 us beside 87)
+    const int64_t cols = whole ? pv.ldx : pv.D, rows = whole ? ld : pv.np;
+    const int64_t chunks = (cols + cw - 1) / cw;
     const int R = (passes == 1 || passes == 2 || passes == 4)
                       ? passes
                       : de_passes((pv.np + 4 * ipw - 1) / (4 * ipw) * chunks);
-    const int64_t groups = (pv.np + 4 * ipw * R - 1) / (4 * ipw * R);
+    const int64_t groups = (rows + 4 * ipw * R - 1) / (4 * ipw * R);
     const int64_t blocks = 8 * ((chunks + 7) / 8) * groups;
     QPM_REQUIRE(blocks < (int64_t(1) << 31), QPM_ERANGE, "population too large for one DE launch");
     const int gr = static_cast<int>(groups), ch = static_cast<int>(chunks);
@@ -446,10 +457,12 @@ qpm_status launch_de(const PopView &pv, float F, float CR, uint64_t seed, const 
 #define QPM_DE(I, P)                                                                                            \
     if (staged)                                                                                                 \
         de_kernel<I, P, true><<<nb, 256, lds, s>>>(pv, draws, fbits, F, F_tab, cr_max, k0, k1, gen_dev, gen,     \
-                                                   inst, bits, ld, gr, ch, store_genes ? 1 : 0, reset_cnt);     \
+                                                   inst, bits, ld, gr, ch, store_genes ? 1 : 0, cols, rows,     \
+                                                   reset_cnt);                                                  \
     else                                                                                                        \
         de_kernel<I, P, false><<<nb, 256, 0, s>>>(pv, draws, nullptr, F, F_tab, cr_max, k0, k1, gen_dev, gen,    \
-                                                  inst, bits, ld, gr, ch, store_genes ? 1 : 0, reset_cnt);
+                                                  inst, bits, ld, gr, ch, store_genes ? 1 : 0, cols, rows,      \
+                                                  reset_cnt);
 #define QPM_DE_R(I)                                                                                             \
     if (R == 1) { QPM_DE(I, 1) } else if (R == 2) { QPM_DE(I, 2) } else { QPM_DE(I, 4) }
     if (ipw == 1) {
@@ -491,18 +504,20 @@ qpm_status launch_fourth(const void *f, int64_t np, bool f64, int32_t *leaders, 
 
 qpm_status launch_gwo(const PopView &pv, const int32_t *leaders, const float *a_tab, float a, uint64_t seed,
                       const uint32_t *gen_dev, uint32_t gen, uint32_t inst, int variant, uint32_t *bits, int64_t ld,
-                      hipStream_t s, int4 lead_c)
+                      hipStream_t s, int4 lead_c, bool whole)
 {
-    const int64_t per_xcd = (pv.np + 7) / 8;
-    const qpm_status st = check_quad_grid(pv.D, 8 * per_xcd);
+    const int64_t per_xcd = ((whole ? ld : pv.np) + 7) / 8, cols = whole ? pv.ldx : pv.D;
+    const qpm_status st = check_quad_grid(cols, 8 * per_xcd);
     if (st != QPM_OK) return st;
-    const dim3 grid(static_cast<unsigned>(8 * per_xcd), quad_grid(pv.D, pv.np).y);
+    const dim3 grid(static_cast<unsigned>(8 * per_xcd), quad_grid(cols, pv.np).y);
     if (variant == 1)
         gwo_kernel<1><<<grid, 256, 0, s>>>(pv, leaders, lead_c, a_tab, a, static_cast<uint32_t>(seed),
-                                           static_cast<uint32_t>(seed >> 32), gen_dev, gen, inst, bits, ld, per_xcd);
+                                           static_cast<uint32_t>(seed >> 32), gen_dev, gen, inst, bits, ld, per_xcd,
+                                           whole ? 1 : 0);
     else
         gwo_kernel<0><<<grid, 256, 0, s>>>(pv, leaders, lead_c, a_tab, a, static_cast<uint32_t>(seed),
-                                           static_cast<uint32_t>(seed >> 32), gen_dev, gen, inst, bits, ld, per_xcd);
+                                           static_cast<uint32_t>(seed >> 32), gen_dev, gen, inst, bits, ld, per_xcd,
+                                           whole ? 1 : 0);
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }
@@ -597,7 +612,7 @@ QPM_API qpm_status qpm_init_population(int64_t np, int64_t D, int64_t ldx, uint6
 
 static qpm_status de_step(const float *x, int64_t np, int64_t D, int64_t ldx, float F, float CR, uint64_t seed,
                           uint32_t generation, uint32_t inst, float *u, uint32_t *u_bits, int64_t ld, int ipw,
-                          int passes, qpm_stream sv)
+                          int passes, bool whole, qpm_stream sv)
 {
     qpm_status st = check_rows(x, np, D, ldx, "x");
     if (st != QPM_OK) return st;
@@ -613,7 +628,8 @@ static qpm_status de_step(const float *x, int64_t np, int64_t D, int64_t ldx, fl
     QPM_REQUIRE(!overlaps(x, bytes, u, bytes), QPM_EINVAL, "x and u must not overlap");
     const PopView pv{x, x, nullptr, u, u, np, D, ldx};
     hipStream_t s = static_cast<hipStream_t>(sv);
-    return launch_de(pv, F, CR, seed, nullptr, generation, inst, u_bits, ld, nullptr, s, ipw, passes);
+    return launch_de(pv, F, CR, seed, nullptr, generation, inst, u_bits, ld, nullptr, s, ipw, passes,
+                     nullptr, nullptr, true, nullptr, whole);
 }
 
 QPM_API qpm_status qpm_de_step(const float *x, int64_t np, int64_t D, int64_t ldx, float F, float CR,
@@ -621,7 +637,15 @@ QPM_API qpm_status qpm_de_step(const float *x, int64_t np, int64_t D, int64_t ld
                                int64_t ld, qpm_stream sv)
 {
     clear_error();
-    return de_step(x, np, D, ldx, F, CR, seed, generation, inst, u, u_bits, ld, 0, 0, sv);
+    return de_step(x, np, D, ldx, F, CR, seed, generation, inst, u, u_bits, ld, 0, 0, false, sv);
+}
+
+QPM_API qpm_status qpm_de_step_whole(const float *x, int64_t np, int64_t D, int64_t ldx, float F, float CR,
+                                     uint64_t seed, uint32_t generation, uint32_t inst, float *u, uint32_t *u_bits,
+                                     int64_t ld, qpm_stream sv)
+{
+    clear_error();
+    return de_step(x, np, D, ldx, F, CR, seed, generation, inst, u, u_bits, ld, 0, 0, true, sv);
 }
 
 QPM_API qpm_status qpm_de_step_shape(const float *x, int64_t np, int64_t D, int64_t ldx, float F, float CR,
@@ -634,14 +658,14 @@ QPM_API qpm_status qpm_de_step_shape(const float *x, int64_t np, int64_t D, int6
                 QPM_EINVAL, "individuals_per_wave must be 0, 1, 2 or 4 (got %d)", (int)individuals_per_wave);
     QPM_REQUIRE(passes == 1 || passes == 2 || passes == 4, QPM_EINVAL, "passes must be 1, 2 or 4 (got %d)",
                 (int)passes);
-    return de_step(x, np, D, ldx, F, CR, seed, generation, inst, u, u_bits, ld, individuals_per_wave, passes, sv);
+    return de_step(x, np, D, ldx, F, CR, seed, generation, inst, u, u_bits, ld, individuals_per_wave, passes, false,
+                   sv);
 }
 
-QPM_API qpm_status qpm_gwo_step(const float *x, int64_t np, int64_t D, int64_t ldx, const int32_t *leaders, float a,
-                                uint64_t seed, uint32_t generation, uint32_t inst, int32_t variant, float *y,
-                                uint32_t *y_bits, int64_t ld, qpm_stream sv)
+static qpm_status gwo_step(const float *x, int64_t np, int64_t D, int64_t ldx, const int32_t *leaders, float a,
+                           uint64_t seed, uint32_t generation, uint32_t inst, int32_t variant, float *y,
+                           uint32_t *y_bits, int64_t ld, bool whole, qpm_stream sv)
 {
-    clear_error();
     qpm_status st = check_rows(x, np, D, ldx, "x");
     if (st != QPM_OK) return st;
     st = check_rows(y, np, D, ldx, "y");
@@ -663,7 +687,23 @@ QPM_API qpm_status qpm_gwo_step(const float *x, int64_t np, int64_t D, int64_t l
     QPM_REQUIRE(L[0] != L[1] && L[0] != L[2] && L[1] != L[2], QPM_EINVAL, "leaders must be distinct");
     const PopView pv{x, x, nullptr, y, y, np, D, ldx};
     return launch_gwo(pv, nullptr, nullptr, a, seed, nullptr, generation, inst, variant, y_bits, ld, s,
-                      make_int4(L[0], L[1], L[2], 0));
+                      make_int4(L[0], L[1], L[2], 0), whole);
+}
+
+QPM_API qpm_status qpm_gwo_step(const float *x, int64_t np, int64_t D, int64_t ldx, const int32_t *leaders,
+                                float a, uint64_t seed, uint32_t generation, uint32_t inst, int32_t variant,
+                                float *y, uint32_t *y_bits, int64_t ld, qpm_stream sv)
+{
+    clear_error();
+    return gwo_step(x, np, D, ldx, leaders, a, seed, generation, inst, variant, y, y_bits, ld, false, sv);
+}
+
+QPM_API qpm_status qpm_gwo_step_whole(const float *x, int64_t np, int64_t D, int64_t ldx, const int32_t *leaders,
+                                      float a, uint64_t seed, uint32_t generation, uint32_t inst, int32_t variant,
+                                      float *y, uint32_t *y_bits, int64_t ld, qpm_stream sv)
+{
+    clear_error();
+    return gwo_step(x, np, D, ldx, leaders, a, seed, generation, inst, variant, y, y_bits, ld, true, sv);
 }
 
 QPM_API qpm_status qpm_dgwo_step(const float *x, int64_t np, int64_t D, int64_t ldx, const int32_t *leaders,

@@ -100,6 +100,20 @@ __device__ __forceinline__ void store_quad_nt(float *dst, int64_t j0, int64_t D,
     }
 }
 
+// the same for rows that are written up to cols >= D (a multiple of 4 where it
+// is larger): genes from D on are those of `pad`
+__device__ __forceinline__ void store_quad_nt(float *dst, int64_t j0, int64_t D, int64_t cols, float4 v, float4 pad)
+{
+    if (j0 + 3 < D) {
+        store_quad_nt(dst, j0, D, v);
+    } else {
+        const float vs[4] = {v.x, v.y, v.z, v.w}, ps[4] = {pad.x, pad.y, pad.z, pad.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (j0 + e < cols) dst[j0 + e] = j0 + e < D ? vs[e] : ps[e];
+    }
+}
+
 __device__ __forceinline__ uint32_t quad_nibble(float4 v, int64_t j0, int64_t D)
 {
     uint32_t n = 0;
@@ -204,11 +218,14 @@ __device__ __forceinline__ uint32_t below_zero_nibble(float4 v)
 // scalar base (pointers kept in LDS would make them flat loads, which the compiler waits
 // for all together). The rows of pass r + 1 are in flight while pass r is
 // computed. Rows past np and quads past D are computed on clamped addresses
-// and not stored, so a pass is straight-line code.
+// and not stored, so a pass is straight-line code. `cols` and `rows` are D and
+// np, or ldx and ld where the caller wants whole rows: genes D .. cols - 1 and
+// bit columns np .. rows - 1 are then written as 0.
 template <int IPW, int R, typename OFF, typename Second>
 __device__ __forceinline__ void de_rows(const PopView &pv, int gi, int c, float F, uint32_t cr_max, uint32_t g,
                                         uint32_t inst, uint32_t k0, uint32_t k1, uint32_t *__restrict__ bits,
-                                        int64_t ld, bool store_genes, int4 d, Second second)
+                                        int64_t ld, bool store_genes, int64_t cols, int64_t rows, int4 d,
+                                        Second second)
 {
     constexpr int LPI = 64 / IPW;  // lanes per individual
     constexpr int WPC = LPI / 8;   // bit words per chunk and individual
@@ -257,8 +274,9 @@ __device__ __forceinline__ void de_rows(const PopView &pv, int gi, int c, float 
         const int64_t i = base + li_r;
         const float4 uv = de_quad_shared(h, philox10_individual(static_cast<uint32_t>(i), g, k0), cur,
                                          sjr[li_r] - static_cast<int>(j0), k0, k1, F, cr_max);
-        if (store_genes && i < np && j0 < D)
-            store_quad_nt(reinterpret_cast<float *>(reinterpret_cast<char *>(pv.out0) + sout[li_r]), j0, D, uv);
+        if (store_genes && i < np && j0 < cols)
+            store_quad_nt(reinterpret_cast<float *>(reinterpret_cast<char *>(pv.out0) + sout[li_r]), j0, D, cols, uv,
+                          make_float4(0.0f, 0.0f, 0.0f, 0.0f));
         const uint32_t nib = below_zero_nibble(uv) & live;
         // merge the nibbles of 8 neighbouring lanes (32 genes) into one word
         const uint32_t w = or8_into_last(nib << (4 * (t & 7)));
@@ -271,7 +289,7 @@ __device__ __forceinline__ void de_rows(const PopView &pv, int gi, int c, float 
         const int wd = t / IPB, ii = t % IPB;
         const int64_t row = base + ii;
         const int64_t wg = static_cast<int64_t>(c) * WPC + wd;
-        if (row < np && wg * 32 < D) bits[wg * ld + row] = wsh[ii][wd];
+        if (row < rows && wg * 32 < D) bits[wg * ld + row] = row < np ? wsh[ii][wd] : 0u;
     }
 }
 

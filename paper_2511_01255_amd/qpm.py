@@ -73,8 +73,10 @@ _SIGS = {
     "qpm_eval_fitness_table_shape": (_I32, [_P, _I32, _P, _I64, _I64, _P, _I32, _I32, _P]),
     "qpm_init_population": (_I32, [_I64, _I64, _I64, _U64, _U32, _P, _P, _I64, _P]),
     "qpm_de_step": (_I32, [_P, _I64, _I64, _I64, _F, _F, _U64, _U32, _U32, _P, _P, _I64, _P]),
+    "qpm_de_step_whole": (_I32, [_P, _I64, _I64, _I64, _F, _F, _U64, _U32, _U32, _P, _P, _I64, _P]),
     "qpm_de_step_shape": (_I32, [_P, _I64, _I64, _I64, _F, _F, _U64, _U32, _U32, _P, _P, _I64, _I32, _I32, _P]),
     "qpm_gwo_step": (_I32, [_P, _I64, _I64, _I64, _P, _F, _U64, _U32, _U32, _I32, _P, _P, _I64, _P]),
+    "qpm_gwo_step_whole": (_I32, [_P, _I64, _I64, _I64, _P, _F, _U64, _U32, _U32, _I32, _P, _P, _I64, _P]),
     "qpm_dgwo_step": (_I32, [_P, _I64, _I64, _I64, _P, _P, _U64, _U32, _U32, _P, _P, _I64, _P]),
     "qpm_relax_forward": (_I32, [_P, _I32, _P, _I64, _I64, _P, _P, _P, _P]),
     "qpm_relax_edges_size": (_I32, [_P, _I32, _I64, _P]),
@@ -290,12 +292,27 @@ def init_population(np_, D, seed, inst=0, ldx=None, device="cuda", stream=None):
     return x, bits
 
 
+def _whole_rows(x, D):
+    """Whether a step may write every element of its results itself, so that
+    they need no clearing or copying first: a plain population of the usual
+    row length. Other layouts keep the cleared and copied results."""
+    import torch
+    return (type(x) is torch.Tensor and x.dtype == torch.float32 and x.is_contiguous() and not x.requires_grad
+            and x.shape[1] == ldx_for(D))
+
+
 def de_step(x, D, F, CR, seed, generation, inst=0, stream=None, shape=None):
     """x: float32 CUDA tensor (np, ldx) -> (u, u_bits). shape: optional
     (individuals_per_wave, passes) launch shape."""
     import torch
     np_, ldx = x.shape
     ld = ld_for(np_)
+    if shape is None and _whole_rows(x, D):
+        u = torch.empty_like(x)
+        ub = torch.empty((words(D), ld), dtype=torch.int32, device=x.device)
+        _check(lib().qpm_de_step_whole(_ptr(x), np_, D, ldx, F, CR, seed, generation, inst, _ptr(u), _ptr(ub), ld,
+                                       _stream(stream)))
+        return u, ub
     u = torch.zeros_like(x)
     ub = torch.zeros((words(D), ld), dtype=torch.int32, device=x.device)
     if shape is None:
@@ -325,6 +342,13 @@ def gwo_step(x, D, leaders, a, seed, generation, inst=0, variant=0, stream=None)
     import torch
     np_, ldx = x.shape
     ld = ld_for(np_)
+    if _whole_rows(x, D):
+        y = torch.empty_like(x)
+        yb = torch.empty((words(D), ld), dtype=torch.int32, device=x.device)
+        L = _host_leaders(leaders, 3)
+        _check(lib().qpm_gwo_step_whole(_ptr(x), np_, D, ldx, L.ctypes.data, a, seed, generation, inst, variant,
+                                        _ptr(y), _ptr(yb), ld, _stream(stream)))
+        return y, yb
     y = x.clone()
     yb = torch.zeros((words(D), ld), dtype=torch.int32, device=x.device)
     L = _host_leaders(leaders, 3)
