@@ -341,10 +341,14 @@ struct FusedRun {
     uint64_t seed;
     uint32_t inst;
     int variant, algo;
+    void *words;     // workspace of fused_words_bytes(np, D, words_gens)
+    int words_gens;  // most generations per launch
 };
 // the population fits the kernel's LDS (np <= 64)
 bool fused_eligible(int64_t np, int64_t D);
-// gens generations from the run state (rows through flags, f, the counter);
+// bytes of the random numbers of gens generations
+size_t fused_words_bytes(int64_t np, int64_t D, int gens);
+// gens (<= words_gens) generations from the run state (rows through flags, f, the counter);
 // writes back every row to x0 with its flag cleared, f, the leaders of the
 // last generation and the advanced counter
 qpm_status launch_fused_generations(const FusedRun &fr, int gens, hipStream_t s);

@@ -299,16 +299,9 @@ __device__ __forceinline__ void de_rows(const PopView &pv, int gi, int c, float 
 // D_k = |fmaf(C, X_k, -x)|, Y_k = fmaf(-A, D_k, X_k); then the weighted
 // combination (variant 0) or the mean (variant 1), divided by 3, clamped.
 template <int VARIANT>
-__device__ __forceinline__ float4 gwo_quad(float4 xv, float4 X0, float4 X1, float4 X2, uint32_t q, uint32_t i,
-                                           uint32_t g, uint32_t inst, uint32_t k0, uint32_t k1, float a, float two_a)
+__device__ __forceinline__ float4 gwo_quad_coef(float4 xv, float4 X0, float4 X1, float4 X2, const float (&A)[12],
+                                                const float (&Cc)[12])
 {
-    const uint32_t c3 = (inst << 8) | kTagGwo;
-    const uint32_t cq = 3u * q;
-    const float two_a_s = two_a * 0x1p-16f;
-    const U4 wa = philox10(cq, i, g, c3, k0, k1);
-    const U4 wb = philox10(cq + 1u, i, g, c3, k0, k1);
-    const U4 wc = philox10(cq + 2u, i, g, c3, k0, k1);
-    const uint32_t wrd[12] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w, wc.x, wc.y, wc.z, wc.w};
     const float xs[4] = {xv.x, xv.y, xv.z, xv.w};
     const float Xs[3][4] = {{X0.x, X0.y, X0.z, X0.w}, {X1.x, X1.y, X1.z, X1.w}, {X2.x, X2.y, X2.z, X2.w}};
     float ys[4], ss[4], ns[4];
@@ -317,14 +310,8 @@ __device__ __forceinline__ float4 gwo_quad(float4 xv, float4 X0, float4 X1, floa
         float Y[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const uint32_t o = wrd[3 * e + k];
-            // A = fmaf(2a, lo16 2^-16, -a) with the power of two moved onto
-            // 2a: the product is the same real number (both scalings are
-            // exact for a = 0 or a >= 2^-100), so A is the same float
-            const float A = fmaf(two_a_s, static_cast<float>(o & 0xFFFFu), -a);
-            const float Cc = static_cast<float>(o >> 16) * 0x1p-15f;  // = 2 r2, exactly
-            const float Dk = fabsf(fmaf(Cc, Xs[k][e], -xs[e]));
-            Y[k] = fmaf(-A, Dk, Xs[k][e]);
+            const float Dk = fabsf(fmaf(Cc[3 * e + k], Xs[k][e], -xs[e]));
+            Y[k] = fmaf(-A[3 * e + k], Dk, Xs[k][e]);
         }
         if constexpr (VARIANT == 1) {
             ys[e] = clamp1(div3((Y[0] + Y[1]) + Y[2]));
@@ -355,6 +342,36 @@ __device__ __forceinline__ float4 gwo_quad(float4 xv, float4 X0, float4 X1, floa
         }
     }
     return make_float4(ys[0], ys[1], ys[2], ys[3]);
+}
+
+// A and C of gene quad q of individual i from its 12 words
+__device__ __forceinline__ void gwo_coef(uint32_t q, uint32_t i, uint32_t g, uint32_t inst, uint32_t k0, uint32_t k1,
+                                         float a, float two_a, float (&A)[12], float (&Cc)[12])
+{
+    const uint32_t c3 = (inst << 8) | kTagGwo;
+    const uint32_t cq = 3u * q;
+    const float two_a_s = two_a * 0x1p-16f;
+    const U4 wa = philox10(cq, i, g, c3, k0, k1);
+    const U4 wb = philox10(cq + 1u, i, g, c3, k0, k1);
+    const U4 wc = philox10(cq + 2u, i, g, c3, k0, k1);
+    const uint32_t wrd[12] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w, wc.x, wc.y, wc.z, wc.w};
+#pragma unroll
+    for (int t = 0; t < 12; ++t) {
+        // A = fmaf(2a, lo16 2^-16, -a) with the power of two moved onto
+        // 2a: the product is the same real number (both scalings are
+        // exact for a = 0 or a >= 2^-100), so A is the same float
+        A[t] = fmaf(two_a_s, static_cast<float>(wrd[t] & 0xFFFFu), -a);
+        Cc[t] = static_cast<float>(wrd[t] >> 16) * 0x1p-15f;  // = 2 r2, exactly
+    }
+}
+
+template <int VARIANT>
+__device__ __forceinline__ float4 gwo_quad(float4 xv, float4 X0, float4 X1, float4 X2, uint32_t q, uint32_t i,
+                                           uint32_t g, uint32_t inst, uint32_t k0, uint32_t k1, float a, float two_a)
+{
+    float A[12], Cc[12];
+    gwo_coef(q, i, g, inst, k0, k1, a, two_a, A, Cc);
+    return gwo_quad_coef<VARIANT>(xv, X0, X1, X2, A, Cc);
 }
 
 // Improved discrete four-leader step (paper Sec. 3.1.2, as read here: the

@@ -55,6 +55,8 @@ struct qpm_run_s {
     int de_ipw = 0;     // 0 = chosen from np
     int de_passes = 0;  // groups of individuals per DE workgroup (0 = chosen from the sizes)
     bool fused = false; // whole generations in one workgroup (fused.hip)
+    void *words = nullptr;  // fused: the random numbers of words_gens generations
+    int words_gens = 0;
     hipGraph_t graph = nullptr;  // one generation
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph_k = nullptr;  // kGraphGens generations back to back
@@ -104,6 +106,7 @@ static void release(qpm_run_s *r)
     (void)hipFree(r->F_base);
     (void)hipFree(r->fws);
     (void)hipFree(r->draws);
+    (void)hipFree(r->words);
     (void)hipFree(r->acc_list);
     (void)hipFree(r->acc_cnt);
     (void)hipFree(r->fbits_prev);
@@ -255,6 +258,9 @@ static qpm_status enqueue_generation(qpm_run_s *r, hipEvent_t *ev = nullptr)
 // one graph; advancing by whole multiples of kGraphGens replays the long
 // graph, which saves the gaps between graph launches.
 constexpr int64_t kGraphGens = 8;
+// generations per launch of the fused kernel: 100 KB of random numbers each at
+// 256 x 32 (at most 250 KB), and about 10 us per launch to fill LDS again
+constexpr int64_t kFusedGens = 64;
 
 static qpm_status capture_generations(qpm_run_s *r, int64_t gens, hipGraph_t *graph, hipGraphExec_t *exec)
 {
@@ -550,6 +556,16 @@ static qpm_status create_run(const Design *d, const Objective *obj, const qpm_ru
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_list, sizeof(int32_t) * c.np);
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_cnt, sizeof(uint32_t));
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->fbits_prev, sizeof(uint32_t) * 2 * ((c.np + 63) / 64));
+    if (e == hipSuccess && r->fused) {
+        // (fewer generations per launch where the memory is short)
+        r->words_gens = static_cast<int>(std::min<int64_t>(kFusedGens, c.generations));
+        while (true) {
+            e = hipMalloc(&r->words, fused_words_bytes(c.np, r->D, r->words_gens));
+            if (e != hipErrorOutOfMemory || r->words_gens == 1) break;
+            (void)hipGetLastError();
+            r->words_gens = (r->words_gens + 1) / 2;
+        }
+    }
     if (e != hipSuccess) {
         set_error("run allocation failed: %s", hipGetErrorString(e));
         release(r);
@@ -664,13 +680,14 @@ QPM_API qpm_status qpm_run_advance(qpm_run_handle r, int64_t generations)
                 (long long)r->cfg.generations, (long long)r->done);
     int64_t g = 0;
     if (!r->timing && r->fused && generations > 0) {
-        // whole generations in one workgroup, in launches of at most 1000
+        // whole generations in one workgroup, as many per launch as the
+        // workspace holds random numbers for
         const qpm_run_config &c = r->cfg;
         FusedRun fr{r->buf[0], r->buf[1], r->flags, r->fbits, r->f_cur, c.prec == QPM_PREC_F32, r->leaders, r->gen,
                     r->a_tab, r->F_tab, r->d->tab64, r->d->Cdev, c.np, r->D, r->ldx, c.CR, c.seed, c.inst,
-                    c.gwo_variant, c.algo};
+                    c.gwo_variant, c.algo, r->words, r->words_gens};
         for (; g < generations;) {
-            const int k = static_cast<int>(std::min<int64_t>(1000, generations - g));
+            const int k = static_cast<int>(std::min<int64_t>(r->words_gens, generations - g));
             qpm_status st = launch_fused_generations(fr, k, r->st);
             if (st != QPM_OK) return st;
             g += k;
