@@ -148,23 +148,23 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
 
 // -h of the NG genomes of a workgroup from the K designs' segment partials,
 // for a workgroup of 256 threads or more (a multiple of NG). The segments of a
-// design are split in 4 ranges folded in order by one thread each; the
-// (design, range) pairs of a genome are spread over the workgroup's threads, so
+// design are split in NR ranges (combine_ranges) folded in order by one thread
+// each; the (design, range) pairs of a genome are spread over the workgroup's threads, so
 // their loads overlap (one design after the other, with 64 genomes per
 // workgroup, took 12.6 us for 24 segments of 5 SHG designs at NP = 5000 and
 // 37.7 us for 104 segments at NP = 1500, against 6.4 and 23.4 us), in batches
-// of kb designs (kb NC 4 NG doubles of LDS);
-// then one thread per genome and design folds the 4 ranges in order, and one
+// of kb designs (kb NC NR NG doubles of LDS);
+// then one thread per genome and design folds the ranges in order, and one
 // per genome takes the objective. Valid in the first NG threads (gl =
-// threadIdx.x). G (optional): G_k at G[k ldG + i]. sh: kb 4 NC NG doubles, gk: K
-// NG doubles.
-template <bool THG, int NG>
+// threadIdx.x). G (optional): G_k at G[k ldG + i]. sh: kb NR NC NG doubles, gk: K
+// NG doubles. (With 4 ranges whatever the segments, one design of 78 segments
+// took 10.9 us.)
+template <bool THG, int NG, int NR>
 __device__ double obj_value(const ObjTabs &tabs, int K, int kb, double scale, double G0, double beta,
                             const double *__restrict__ part, int gy, int64_t ld, int64_t i, bool valid, double *G,
                             int64_t ldG, double *sh, double *gk)
 {
     constexpr int NC = ObjShape<THG>::NC;
-    constexpr int NR = 4;
     const int gl = static_cast<int>(threadIdx.x) % NG, slot = static_cast<int>(threadIdx.x) / NG;
     const int slots = static_cast<int>(blockDim.x) / NG;
     for (int k0 = 0; k0 < K; k0 += kb) {
@@ -178,11 +178,7 @@ __device__ double obj_value(const ObjTabs &tabs, int K, int kb, double scale, do
             if (valid) {
                 if constexpr (THG) {
                     Tri t{0, 0, 0, 0, 0, 0};
-#pragma unroll 4
-                    for (int sg = s0; sg < s1; ++sg) {
-                        const double *q = pk + static_cast<int64_t>(sg) * 6 * ld;
-                        tri_append(t, Tri{q[0], q[ld], q[2 * ld], q[3 * ld], q[4 * ld], q[5 * ld]});
-                    }
+                    fold_segments<4>(t, pk - i, ld, i, s0, s1);
                     v[0] = t.ar;
                     v[1] = t.ai;
                     v[2] = t.br;
@@ -190,11 +186,22 @@ __device__ double obj_value(const ObjTabs &tabs, int K, int kb, double scale, do
                     v[4] = t.qr;
                     v[5] = t.qi;
                 } else {
-#pragma unroll 8
-                    for (int sg = s0; sg < s1; ++sg) {
-                        const double *q = pk + static_cast<int64_t>(sg) * 2 * ld;
-                        v[0] += q[0];
-                        v[1] += q[ld];
+                    constexpr int U = NR == 4 ? 4 : 8;  // (in flight together, as in fold_segments)
+                    for (int sg = s0; sg < s1; sg += U) {
+                        double re[U], im[U];
+#pragma unroll
+                        for (int k = 0; k < U; ++k) {
+                            const double *q = pk + static_cast<int64_t>(min(sg + k, s1 - 1)) * 2 * ld;
+                            re[k] = q[0];
+                            im[k] = q[ld];
+                        }
+#pragma unroll
+                        for (int k = 0; k < U; ++k) {
+                            if (sg + k < s1) {
+                                v[0] += re[k];
+                                v[1] += im[k];
+                            }
+                        }
                     }
                 }
             }
@@ -213,8 +220,13 @@ __device__ double obj_value(const ObjTabs &tabs, int K, int kb, double scale, do
                 re = t.qr + tabs.C[k0 + kd][0];
                 im = t.qi + tabs.C[k0 + kd][1];
             } else {
-                re = ((at(0, 0) + at(0, 1)) + at(0, 2)) + at(0, 3);
-                im = ((at(1, 0) + at(1, 1)) + at(1, 2)) + at(1, 3);
+                re = at(0, 0);
+                im = at(1, 0);
+#pragma unroll
+                for (int r = 1; r < NR; ++r) {
+                    re += at(0, r);
+                    im += at(1, r);
+                }
             }
             const double Gk = sqrt(fma(re, re, im * im)) * scale;
             gk[(k0 + kd) * NG + gl] = Gk;
@@ -236,21 +248,22 @@ __device__ double obj_value(const ObjTabs &tabs, int K, int kb, double scale, do
 
 // designs folded together by obj_value, and its LDS
 template <bool THG, int NG>
-int obj_value_batch(int K)
+int obj_value_batch(int K, int gy)
 {
-    const int per = ObjShape<THG>::NC * 4 * NG * static_cast<int>(sizeof(double));
+    const int per = ObjShape<THG>::NC * combine_ranges(gy) * NG * static_cast<int>(sizeof(double));
     return std::min(K, std::max(1, (48 << 10) / per));
 }
 template <bool THG, int NG>
-size_t obj_value_lds(int K)
+size_t obj_value_lds(int K, int gy)
 {
     return sizeof(double) * NG *
-           (static_cast<size_t>(ObjShape<THG>::NC) * 4 * obj_value_batch<THG, NG>(K) + static_cast<size_t>(K));
+           (static_cast<size_t>(ObjShape<THG>::NC) * combine_ranges(gy) * obj_value_batch<THG, NG>(K, gy) +
+            static_cast<size_t>(K));
 }
 
 // 16 genomes per workgroup (a 128-byte line of each component) x 16 slots
 constexpr int kObjGenomes = 16;
-template <typename T, bool THG>
+template <typename T, bool THG, int NR>
 __global__ __launch_bounds__(256) void obj_values_kernel(ObjTabs tabs, int K, int kb, double scale, double G0,
                                                          double beta, const double *__restrict__ part, int gy,
                                                          int64_t ld, int64_t np, T *__restrict__ fit,
@@ -260,14 +273,14 @@ __global__ __launch_bounds__(256) void obj_values_kernel(ObjTabs tabs, int K, in
     constexpr int NG = kObjGenomes;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * NG + threadIdx.x % NG;
     const bool valid = i < np;
-    const double v = obj_value<THG, NG>(tabs, K, kb, scale, G0, beta, part, gy, ld, i, valid, G, ldG, osh,
-                                        osh + ObjShape<THG>::NC * 4 * kb * NG);
+    const double v = obj_value<THG, NG, NR>(tabs, K, kb, scale, G0, beta, part, gy, ld, i, valid, G, ldG, osh,
+                                            osh + ObjShape<THG>::NC * NR * kb * NG);
     if (threadIdx.x < NG && valid) fit[i] = static_cast<T>(v);
 }
 
 // the run's finish step on the objective: as finish_kernel, with the
 // fitness -h (64 genomes x 16 slots)
-template <typename T, bool THG>
+template <typename T, bool THG, int NR>
 __global__ __launch_bounds__(1024) void obj_finish_kernel(ObjTabs tabs, int K, int kb, double scale, double G0,
                                                           double beta, const double *__restrict__ part, int gy,
                                                           int64_t ld, int64_t np, T *__restrict__ f_cur,
@@ -281,8 +294,8 @@ __global__ __launch_bounds__(1024) void obj_finish_kernel(ObjTabs tabs, int K, i
     extern __shared__ double osh[];
     const int lane = threadIdx.x & 63;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + lane;
-    const double v = obj_value<THG, 64>(tabs, K, kb, scale, G0, beta, part, gy, ld, i, i < np, nullptr, 0, osh,
-                                        osh + ObjShape<THG>::NC * 4 * kb * 64);
+    const double v = obj_value<THG, 64, NR>(tabs, K, kb, scale, G0, beta, part, gy, ld, i, i < np, nullptr, 0, osh,
+                                            osh + ObjShape<THG>::NC * NR * kb * 64);
     if (threadIdx.x < 64)
         select_group<T>(v, blockIdx.x, lane, np, f_cur, flags, fbits, skip3, cand_v, cand_i, draws_next, gen, D, k0,
                         k1, inst, acc, next_off, replace_all != 0);
@@ -349,15 +362,26 @@ qpm_status launch_objective_values(const Objective &o, const ObjPlan &pl, const 
 {
     const unsigned blocks = static_cast<unsigned>((np + kObjGenomes - 1) / kObjGenomes);
     const bool thg = o.kind == QPM_OBJ_THG;
-#define QPM_OV(T, H)                                                                                             \
-    obj_values_kernel<T, H><<<blocks, 256, obj_value_lds<H, kObjGenomes>(o.K), s>>>(                             \
-        o.tabs, o.K, obj_value_batch<H, kObjGenomes>(o.K), o.scale, o.G0, o.beta, part, pl.gy, ld, np,           \
+    const bool many = combine_ranges(pl.gy) == kMaxRanges;
+#define QPM_OV(T, H, N)                                                                                          \
+    obj_values_kernel<T, H, N><<<blocks, 256, obj_value_lds<H, kObjGenomes>(o.K, pl.gy), s>>>(                   \
+        o.tabs, o.K, obj_value_batch<H, kObjGenomes>(o.K, pl.gy), o.scale, o.G0, o.beta, part, pl.gy, ld, np,    \
         static_cast<T *>(fitness), G, ldG)
-    if (f64) {
-        if (thg) QPM_OV(double, true); else QPM_OV(double, false);
+#define QPM_OV_N(T, H)                                                                                           \
+    if (many)                                                                                                    \
+        QPM_OV(T, H, kMaxRanges);                                                                                \
+    else                                                                                                         \
+        QPM_OV(T, H, 4);
+    if (f64 && thg) {
+        QPM_OV_N(double, true)
+    } else if (f64) {
+        QPM_OV_N(double, false)
+    } else if (thg) {
+        QPM_OV_N(float, true)
     } else {
-        if (thg) QPM_OV(float, true); else QPM_OV(float, false);
+        QPM_OV_N(float, false)
     }
+#undef QPM_OV_N
 #undef QPM_OV
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
@@ -376,22 +400,32 @@ qpm_status launch_objective_finish(const Objective &o, const ObjPlan &pl, const 
     const bool tail = (top3_out != nullptr && !mode.defer_leaders) || advance;
     int32_t *tail_top3 = mode.defer_leaders ? nullptr : top3_out;
     const bool thg = o.kind == QPM_OBJ_THG;
+    const bool many = combine_ranges(pl.gy) == kMaxRanges;
     // cand: 3 values per workgroup (T) followed by 3 slots per workgroup
-#define QPM_OF(T, H)                                                                                              \
-    {                                                                                                             \
-        T *cv = top3_out ? static_cast<T *>(cand) : nullptr;                                                      \
-        int32_t *ci = cv ? reinterpret_cast<int32_t *>(cv + 3 * static_cast<size_t>(blocks)) : nullptr;          \
-        obj_finish_kernel<T, H><<<blocks, 1024, obj_value_lds<H, 64>(o.K), s>>>(                                 \
-            o.tabs, o.K, obj_value_batch<H, 64>(o.K), o.scale, o.G0, o.beta, part, pl.gy, ld, np,                \
-            static_cast<T *>(f_cur), flags, fbits, skip3, cv, ci, draws_next, gen, D, k0, k1, inst, acc,         \
-            next_off, mode.replace_all ? 1 : 0);                                                                 \
-        if (tail) finish_tail_kernel<T><<<1, 256, 0, s>>>(cv, ci, blocks, tail_top3, gen, advance);               \
+#define QPM_OF(T, H, N)                                                                                          \
+    obj_finish_kernel<T, H, N><<<blocks, 1024, obj_value_lds<H, 64>(o.K, pl.gy), s>>>(                           \
+        o.tabs, o.K, obj_value_batch<H, 64>(o.K, pl.gy), o.scale, o.G0, o.beta, part, pl.gy, ld, np,             \
+        static_cast<T *>(f_cur), flags, fbits, skip3, cv, ci, draws_next, gen, D, k0, k1, inst, acc, next_off,   \
+        mode.replace_all ? 1 : 0)
+#define QPM_OF_N(T, H)                                                                                           \
+    {                                                                                                            \
+        T *cv = top3_out ? static_cast<T *>(cand) : nullptr;                                                     \
+        int32_t *ci = cv ? reinterpret_cast<int32_t *>(cv + 3 * static_cast<size_t>(blocks)) : nullptr;         \
+        if (many)                                                                                                \
+            QPM_OF(T, H, kMaxRanges);                                                                            \
+        else                                                                                                     \
+            QPM_OF(T, H, 4);                                                                                     \
+        if (tail) finish_tail_kernel<T><<<1, 256, 0, s>>>(cv, ci, blocks, tail_top3, gen, advance);              \
     }
-    if (f64) {
-        if (thg) QPM_OF(double, true) else QPM_OF(double, false)
-    } else {
-        if (thg) QPM_OF(float, true) else QPM_OF(float, false)
-    }
+    if (f64 && thg)
+        QPM_OF_N(double, true)
+    else if (f64)
+        QPM_OF_N(double, false)
+    else if (thg)
+        QPM_OF_N(float, true)
+    else
+        QPM_OF_N(float, false)
+#undef QPM_OF_N
 #undef QPM_OF
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;

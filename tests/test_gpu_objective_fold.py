@@ -1,7 +1,7 @@
 """The fold of the objective's segments where its batches of designs and its
 default launch shape change: 1, 4, 5 and 8 designs in runs (FP64, every decision
-the oracle's) and evaluations on both sides of 256 and 400 workgroups, with
-partial groups of 16 and 64 genomes."""
+the oracle's), evaluations on both sides of 256 and 400 workgroups and of 48
+segments, with partial groups of 16 and 64 genomes."""
 import numpy as np
 import pytest
 
@@ -28,9 +28,9 @@ def _pair(q, orc, z, K, kind):
 
 
 @pytest.mark.parametrize("kind", [0, 1])
-@pytest.mark.parametrize("K,npop", [(1, 65), (4, 17), (5, 70), (8, 33)])
-def test_run_equals_oracle(q, orc, K, npop, kind):
-    n, G = 1300, 4
+@pytest.mark.parametrize("K,npop,n,G", [(1, 65, 1300, 4), (4, 17, 1300, 4), (5, 70, 1300, 4), (8, 33, 1300, 4),
+                                        (1, 66, 6200, 2), (3, 20, 6017, 2)])  # (49 and 47 segments or more)
+def test_run_equals_oracle(q, orc, K, npop, n, G, kind):
     O, Oo = _pair(q, orc, inputs.uniform_boundaries(n, 2.0), K, kind)
     xo, fo, _, _ = Oo.hwsda_run(npop, G, 0.5, 0.9, 2)
     R = q.Run(O, npop, G, seed=2, prec=q.PREC_F64)
@@ -43,7 +43,8 @@ def test_run_equals_oracle(q, orc, K, npop, kind):
 
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("kind", [0, 1])
-@pytest.mark.parametrize("n,npop,K", [(2048, 1985, 2), (2049, 2049, 3), (6400, 1990, 2), (12801, 1000, 1)])
+@pytest.mark.parametrize("n,npop,K", [(2048, 1985, 2), (2049, 2049, 3), (6400, 1990, 2), (12801, 1000, 1), (9894, 89, 1),
+                                      (12000, 80, 2), (6145, 100, 3), (6144, 100, 3)])
 def test_default_shape_matches_oracle(q, orc, n, npop, K, kind, prec):
     import torch
     O, Oo = _pair(q, orc, inputs.jittered_boundaries(n, 2.0, 0.3, seed=n), K, kind)
