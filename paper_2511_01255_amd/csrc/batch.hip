@@ -204,18 +204,12 @@ __global__ __launch_bounds__(1024) void batch_finish_kernel(int mode, const doub
     T *cv = mode <= 2 ? cand_v + b * 3 * gridDim.x : nullptr;
     int32_t *ci = cand_i + b * 3 * gridDim.x;
     if (mode == 1) {
-        Top3<T> tp = top3_empty<T>();
         if (i < np) {
-            tp.v[0] = static_cast<T>(f);
-            tp.i[0] = static_cast<int>(i);
             fb[i] = static_cast<T>(f);
             db[i] = de_draw(i, np, n, gen[0], instb, k0, k1);
         }
-        wave_top3(tp);
-        if (lane < 3) {
-            cv[3 * grp + lane] = lane == 0 ? tp.v[0] : (lane == 1 ? tp.v[1] : tp.v[2]);
-            ci[3 * grp + lane] = lane == 0 ? tp.i[0] : (lane == 1 ? tp.i[1] : tp.i[2]);
-        }
+        group_best3(i < np ? static_cast<T>(f) : static_cast<T>(-INFINITY), i < np ? static_cast<int>(i) : INT_MAX,
+                    lane, cv + 3 * grp, ci + 3 * grp);
         return;
     }
     const AcceptOut accb = acc.list ? AcceptOut{acc.list + b * np, acc.cnt + b, acc.fbits_prev + b * fw} : AcceptOut{};
@@ -230,7 +224,7 @@ __global__ __launch_bounds__(64) void batch_leaders_kernel(const T *__restrict__
                                                            int32_t *__restrict__ leaders)
 {
     const int64_t b = blockIdx.x;
-    block_top3<T, 64>(cand_v + b * 3 * groups, 3 * groups, leaders + 3 * b, cand_i + b * 3 * groups);
+    merge_leaders<T, 64>(cand_v + b * 3 * groups, cand_i + b * 3 * groups, 3 * groups, leaders + 3 * b);
 }
 
 // ---------------------------------------------------------------- evolution
@@ -338,11 +332,11 @@ __global__ __launch_bounds__(256) void batch_materialize_kernel(BatchPop bp, con
     if (blockIdx.x == 0 && tl.chunk == 0) {
         const int64_t n3 = 3 * ((bp.np + 63) / 64);
         if (cand_f64)
-            block_top3<double, 256>(static_cast<const double *>(cand_v) + tl.inst * n3, n3, leaders + 3 * tl.inst,
-                                    cand_i + tl.inst * n3);
+            merge_leaders<double, 256>(static_cast<const double *>(cand_v) + tl.inst * n3, cand_i + tl.inst * n3, n3,
+                                       leaders + 3 * tl.inst);
         else
-            block_top3<float, 256>(static_cast<const float *>(cand_v) + tl.inst * n3, n3, leaders + 3 * tl.inst,
-                                   cand_i + tl.inst * n3);
+            merge_leaders<float, 256>(static_cast<const float *>(cand_v) + tl.inst * n3, cand_i + tl.inst * n3, n3,
+                                      leaders + 3 * tl.inst);
     }
     const int64_t np = bp.np;
     const uint32_t n_acc = min(cnt[tl.inst], static_cast<uint32_t>(np));

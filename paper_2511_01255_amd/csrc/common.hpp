@@ -156,7 +156,7 @@ struct AcceptOut {
 // gen_advanced: the counter was already advanced by the evaluation kernel,
 // so the next draws are for gen[0] itself and no tail advances it;
 // defer_leaders: the candidates are left in `cand` for launch_materialize
-// to merge into top3_out (no tail kernel); replace_all: every genome
+// or launch_gwo to merge into the leaders (no tail kernel); replace_all: every genome
 // outside skip3 takes its new value (no greedy selection).
 struct FinishMode {
     bool gen_advanced = false;
@@ -294,10 +294,14 @@ qpm_status launch_draws(int64_t np, int64_t D, uint64_t seed, const uint32_t *ge
 // leaders: device int32[3], or nullptr and the three by value in lead_c;
 // whole: leader rows and genes D .. ldx - 1 are copied, the leaders' bit
 // columns and columns np .. ld - 1 written as 0
-qpm_status launch_gwo(const PopView &pv, const int32_t *leaders, const float *a_tab, float a,
+// cand: take the leaders from a finish step's candidates (defer_leaders; double
+// values with cand_f64) and store them in `leaders` (when merges_leaders)
+constexpr int64_t kMergeGroups = 3000;
+bool merges_leaders(int64_t np, int64_t D);
+qpm_status launch_gwo(const PopView &pv, int32_t *leaders, const float *a_tab, float a,
                       uint64_t seed, const uint32_t *gen_dev, uint32_t gen, uint32_t inst,
                       int variant, uint32_t *bits, int64_t ld, hipStream_t s, int4 lead_c = int4{},
-                      bool whole = false);
+                      bool whole = false, const void *cand = nullptr, bool cand_f64 = false);
 // the improved discrete four-leader step (leaders: 4 slots, the first three
 // kept, on the device or by value in lead_c; par_tab[g] or
 // par = {t, 1 - 2 eps, eps, lambda})

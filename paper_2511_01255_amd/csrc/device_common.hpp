@@ -80,29 +80,107 @@ __device__ __forceinline__ Top3<T> top3_empty()
     return t;
 }
 
-// merge the lists of the 64 lanes of a wave (every lane ends with the
-// wave's three best)
-template <typename T>
-__device__ __forceinline__ void wave_top3(Top3<T> &t)
+// the value of the lane a DPP control names, or the lane's own where that lane
+// does not exist
+template <int CTRL>
+__device__ __forceinline__ float dpp_take(float v)
 {
-    for (int off = 32; off >= 1; off >>= 1) {
-        T ov[3];
-        int oi[3];
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_take(double v)
+{
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false),
+                            __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_take(int v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
+}
+__device__ __forceinline__ float lane63(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ double lane63(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+__device__ __forceinline__ int lane63(int v) { return __builtin_amdgcn_readlane(v, 63); }
+
+// op over the 64 lanes of a wave, in every lane: prefixes within the 16-lane
+// rows, then across the rows (a lane without a source keeps its own value, so
+// op must be idempotent)
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op)
+{
+    v = op(v, dpp_take<0x111>(v));  // row_shr 1, 2, 4, 8
+    v = op(v, dpp_take<0x112>(v));
+    v = op(v, dpp_take<0x114>(v));
+    v = op(v, dpp_take<0x118>(v));
+    v = op(v, dpp_take<0x142>(v));  // row_bcast 15, 31
+    v = op(v, dpp_take<0x143>(v));
+    return lane63(v);
+}
+
+// The three best of the 64 U (value, slot) pairs of a wave, f descending, slot
+// ascending: their slots in lanes 0 .. 2 (INT_MAX where there are fewer), their
+// values too with `vals`. Three rounds of a maximum and a minimum over the
+// wave; values that are not a number never lead. The pairs are used up.
+template <typename T, int U>
+__device__ __forceinline__ int wave_best3(T (&v)[U], int (&ix)[U], int lane, T *vals = nullptr)
+{
+    int best = INT_MAX;
+    T bv = static_cast<T>(-INFINITY);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            ov[k] = __shfl_xor(t.v[k], off);
-            oi[k] = __shfl_xor(t.i[k], off);
+    for (int k = 0; k < 3; ++k) {
+        T m = static_cast<T>(-INFINITY);
+#pragma unroll
+        for (int u = 0; u < U; ++u) m = v[u] > m ? v[u] : m;
+        m = wave_reduce(m, [](T a, T b) { return b > a ? b : a; });
+        int c = INT_MAX;
+#pragma unroll
+        for (int u = 0; u < U; ++u) c = v[u] == m ? min(c, ix[u]) : c;
+        c = wave_reduce(c, [](int a, int b) { return min(a, b); });
+        best = lane == k ? c : best;
+        bv = lane == k ? m : bv;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool gone = ix[u] == c;
+            v[u] = gone ? static_cast<T>(-INFINITY) : v[u];
+            ix[u] = gone ? INT_MAX : ix[u];
         }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) top3_insert(t, ov[k], oi[k]);
     }
+    if (vals != nullptr) *vals = bv;
+    return best;
+}
+
+// the same of the n <= 64 U candidates (cv[j], ci[j])
+template <typename T, int U>
+__device__ __forceinline__ int wave_best3_of(const T *__restrict__ cv, const int32_t *__restrict__ ci, int n, int lane)
+{
+    T v[U];
+    int ix[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int j = lane + 64 * u, jj = j < n ? j : n - 1;
+        const T fv = cv[jj];
+        const int iv = ci[jj];
+        v[u] = j < n ? fv : static_cast<T>(-INFINITY);
+        ix[u] = j < n ? iv : INT_MAX;
+    }
+    return wave_best3<T, U>(v, ix, lane);
 }
 
 // The three best of the n candidates (f[j], idx ? idx[j] : j) over one
 // workgroup of NT lanes (NT a multiple of 64, <= 1024). (f descending,
 // slot ascending) is a strict total order, so the result is unique
-// whatever the merge order. Loads are issued four at a time. Written by
-// lane 0.
+// whatever the merge order. Loads are issued four at a time. Each wave's
+// three and then the workgroup's come from wave_best3 (lists merged lane by
+// lane took 3.4 us more in a kernel of one workgroup).
 template <typename T, int NT>
 __device__ void block_top3(const T *__restrict__ f, int64_t n, int32_t *__restrict__ out,
                            const int32_t *__restrict__ idx = nullptr)
@@ -123,25 +201,34 @@ __device__ void block_top3(const T *__restrict__ f, int64_t n, int32_t *__restri
 #pragma unroll
         for (int u = 0; u < 4; ++u) top3_insert(t, v[u], ix[u]);
     }
-    wave_top3(t);
-    __shared__ T sv[NT / 64][3];
-    __shared__ int si[NT / 64][3];
+    __shared__ T sv[3 * (NT / 64)];
+    __shared__ int si[3 * (NT / 64)];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            sv[wave][k] = t.v[k];
-            si[wave][k] = t.i[k];
-        }
+    T bv;
+    const int b = wave_best3<T, 3>(t.v, t.i, lane, &bv);
+    if (lane < 3) {
+        sv[3 * wave + lane] = bv;
+        si[3 * wave + lane] = b;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        Top3<T> r = t;
-        for (int w = 1; w < NT / 64; ++w)
-            for (int k = 0; k < 3; ++k) top3_insert(r, sv[w][k], si[w][k]);
-        out[0] = r.i[0];
-        out[1] = r.i[1];
-        out[2] = r.i[2];
+    if (wave == 0) {
+        const int b3 = wave_best3_of<T, 1>(sv, si, 3 * (NT / 64), lane);
+        if (lane < 3) out[lane] = b3;
+    }
+}
+
+// The leaders from n candidates (cv[j], ci[j]), by a workgroup of NT lanes: up
+// to 256 of them by its first wave alone.
+template <typename T, int NT>
+__device__ __forceinline__ void merge_leaders(const T *__restrict__ cv, const int32_t *__restrict__ ci, int64_t n,
+                                              int32_t *__restrict__ out)
+{
+    if (n > 256) {
+        block_top3<T, NT>(cv, n, out, ci);
+    } else if (threadIdx.x < 64) {
+        const int lane = static_cast<int>(threadIdx.x), m = static_cast<int>(n);
+        const int b = m <= 64 ? wave_best3_of<T, 1>(cv, ci, m, lane) : wave_best3_of<T, 4>(cv, ci, m, lane);
+        if (lane < 3) out[lane] = b;
     }
 }
 

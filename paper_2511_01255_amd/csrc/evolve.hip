@@ -146,10 +146,10 @@ __global__ __launch_bounds__(256) void materialize_kernel(PopView pv, const int4
         // cand: 3 values per group (T) followed by 3 slots per group
         if (cand_f64) {
             const double *cv = static_cast<const double *>(cand);
-            block_top3<double, 256>(cv, 3 * ngroups, top3_out, reinterpret_cast<const int32_t *>(cv + 3 * ngroups));
+            merge_leaders<double, 256>(cv, reinterpret_cast<const int32_t *>(cv + 3 * ngroups), 3 * ngroups, top3_out);
         } else {
             const float *cv = static_cast<const float *>(cand);
-            block_top3<float, 256>(cv, 3 * ngroups, top3_out, reinterpret_cast<const int32_t *>(cv + 3 * ngroups));
+            merge_leaders<float, 256>(cv, reinterpret_cast<const int32_t *>(cv + 3 * ngroups), 3 * ngroups, top3_out);
         }
     }
     const int64_t np = pv.np, D = pv.D;
@@ -218,6 +218,21 @@ qpm_status launch_materialize(const PopView &pv, const int4 *draws, const uint32
 
 // ------------------------------------------------------------ grey-wolf update
 
+// row_of and out_row_of; merging, by offsets between the buffers (there, a
+// choice between the pointers of `pv` would keep `pv` in memory)
+template <int MERGE>
+__device__ __forceinline__ const float *gwo_row(const PopView &pv, int64_t r)
+{
+    if constexpr (MERGE == 0) return row_of(pv, r);
+    return pv.x0 + (r * pv.ldx + (pv.flags[r] != 0u ? pv.x1 - pv.x0 : 0));
+}
+template <int MERGE>
+__device__ __forceinline__ float *gwo_out_row(const PopView &pv, int64_t r)
+{
+    if constexpr (MERGE == 0) return out_row_of(pv, r);
+    return pv.out0 + (r * pv.ldx + (pv.flags[r] != 0u ? 0 : pv.out1 - pv.out0));
+}
+
 // Grid x = 8 ceil(np / 8): workgroup x runs on XCD x mod 8 (gridDim.x is a
 // multiple of 8, so this holds for every y) and takes individual
 // (x mod 8) ceil(np / 8) + x / 8. Each XCD thus owns a contiguous range of
@@ -227,19 +242,59 @@ qpm_status launch_materialize(const PopView &pv, const int4 *draws, const uint32
 // past D as they are in x, 0 in the leaders' bit columns and in those past
 // np), so that the caller needs no copy of x and no cleared words first: at
 // 5000 x 6600 genes the copy and the clear took 54 us beside 62 for the step.
-template <int VARIANT>
-__global__ __launch_bounds__(256) void gwo_kernel(PopView pv, const int32_t *__restrict__ leaders, int4 lead_c,
+// MERGE (a run; T = MergeT<MERGE>): the leaders are not known yet; each
+// workgroup takes them from the selection's candidates (ncand <= 256 values
+// cand, then their slots) and the first one stores them. That is one wave's
+// three reductions per workgroup instead of a kernel of one workgroup between
+// the selection and this step (see merges_leaders).
+template <int MERGE>
+struct MergeT {
+    using T = float;
+};
+template <>
+struct MergeT<2> {
+    using T = double;
+};
+template <int VARIANT, int MERGE>
+__global__ __launch_bounds__(256) void gwo_kernel(PopView pv, int32_t *__restrict__ leaders, int4 lead_c,
                                                   const float *__restrict__ a_tab, float a_c, uint32_t k0, uint32_t k1,
                                                   const uint32_t *__restrict__ gen_dev, uint32_t gen_c, uint32_t inst,
                                                   uint32_t *__restrict__ bits, int64_t ld, int64_t per_xcd,
-                                                  int whole)
+                                                  int whole, const void *__restrict__ cand, int ncand)
 {
     const int64_t np = pv.np, D = pv.D;
     const int64_t i = static_cast<int64_t>(blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (i >= (whole ? ld : np)) return;
-    // leaders from the device (runs) or by value (the entry point)
-    const int64_t L0 = leaders ? leaders[0] : lead_c.x, L1 = leaders ? leaders[1] : lead_c.y,
-                  L2 = leaders ? leaders[2] : lead_c.z;
+    const int64_t q = static_cast<int64_t>(blockIdx.y) * 256 + threadIdx.x;
+    const int64_t j0 = 4 * q, cols = whole ? pv.ldx : D;
+    // merging, the wolf's own genes are loaded before its leaders are known
+    float4 own = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if constexpr (MERGE != 0) {
+        if (j0 < D) own = *reinterpret_cast<const float4 *>(gwo_row<MERGE>(pv, i) + j0);
+    }
+    int64_t L0, L1, L2;
+    if constexpr (MERGE != 0) {
+        using T = typename MergeT<MERGE>::T;
+        __shared__ int lead[3];
+        if (threadIdx.x < 64) {
+            const T *cv = static_cast<const T *>(cand);
+            const int32_t *ci = reinterpret_cast<const int32_t *>(cv + ncand);
+            const int lane = static_cast<int>(threadIdx.x);
+            const int b = ncand <= 64 ? wave_best3_of<T, 1>(cv, ci, ncand, lane) : wave_best3_of<T, 4>(cv, ci, ncand, lane);
+            if (lane < 3) {
+                lead[lane] = b;
+                if (blockIdx.x == 0 && blockIdx.y == 0) leaders[lane] = b;
+            }
+        }
+        __syncthreads();
+        L0 = __builtin_amdgcn_readfirstlane(lead[0]);
+        L1 = __builtin_amdgcn_readfirstlane(lead[1]);
+        L2 = __builtin_amdgcn_readfirstlane(lead[2]);
+    } else {
+        L0 = leaders ? leaders[0] : lead_c.x;
+        L1 = leaders ? leaders[1] : lead_c.y;
+        L2 = leaders ? leaders[2] : lead_c.z;
+    }
     // leaders keep their positions; indices outside the population make
     // the launch a no-op instead of an out-of-bounds read
     const bool kept = i == L0 || i == L1 || i == L2 || i >= np;
@@ -249,20 +304,18 @@ __global__ __launch_bounds__(256) void gwo_kernel(PopView pv, const int32_t *__r
     const float a = a_tab ? a_tab[g] : a_c;
     const float two_a = 2.0f * a;
 
-    const int64_t q = static_cast<int64_t>(blockIdx.y) * 256 + threadIdx.x;
-    const int64_t j0 = 4 * q, cols = whole ? pv.ldx : D;
     uint32_t nib = 0;
     if (kept || j0 >= D) {
         if (i < np && j0 < cols)
-            store_quad_nt(out_row_of(pv, i), j0, cols, *reinterpret_cast<const float4 *>(row_of(pv, i) + j0));
+            store_quad_nt(gwo_out_row<MERGE>(pv, i), j0, cols, *reinterpret_cast<const float4 *>(gwo_row<MERGE>(pv, i) + j0));
     } else {
-        const float4 xv = *reinterpret_cast<const float4 *>(row_of(pv, i) + j0);
-        const float4 X0 = *reinterpret_cast<const float4 *>(row_of(pv, L0) + j0);
-        const float4 X1 = *reinterpret_cast<const float4 *>(row_of(pv, L1) + j0);
-        const float4 X2 = *reinterpret_cast<const float4 *>(row_of(pv, L2) + j0);
+        const float4 xv = MERGE != 0 ? own : *reinterpret_cast<const float4 *>(gwo_row<MERGE>(pv, i) + j0);
+        const float4 X0 = *reinterpret_cast<const float4 *>(gwo_row<MERGE>(pv, L0) + j0);
+        const float4 X1 = *reinterpret_cast<const float4 *>(gwo_row<MERGE>(pv, L1) + j0);
+        const float4 X2 = *reinterpret_cast<const float4 *>(gwo_row<MERGE>(pv, L2) + j0);
         const float4 yv4 = gwo_quad<VARIANT>(xv, X0, X1, X2, static_cast<uint32_t>(q), static_cast<uint32_t>(i), g,
                                              inst, k0, k1, a, two_a);
-        store_quad_nt(out_row_of(pv, i), j0, D, cols, yv4, xv);
+        store_quad_nt(gwo_out_row<MERGE>(pv, i), j0, D, cols, yv4, xv);
         nib = quad_nibble(yv4, j0, D);
     }
     store_word(nib, q, D, bits, ld, i);
@@ -502,22 +555,45 @@ qpm_status launch_fourth(const void *f, int64_t np, bool f64, int32_t *leaders, 
     return QPM_OK;
 }
 
-qpm_status launch_gwo(const PopView &pv, const int32_t *leaders, const float *a_tab, float a, uint64_t seed,
+// One wave's reductions in every workgroup against a kernel of one workgroup:
+// the step merges the leaders itself up to kMergeGroups workgroups and 256
+// candidates (np 5461). A generation, us, merged / by the kernel: 2000 x 500
+// (1000 workgroups) 26.4 / 27.7, 1000 x 2000 (2000) 31.5 / 32.9, 4000 x 1000
+// (4000) 38.7 / 38.6, 8000 x 1000 (8000) 55.9 / 53.9.
+bool merges_leaders(int64_t np, int64_t D)
+{
+    return 3 * ((np + 63) / 64) <= 256 && np * ((D + 1023) / 1024) <= kMergeGroups;
+}
+
+qpm_status launch_gwo(const PopView &pv, int32_t *leaders, const float *a_tab, float a, uint64_t seed,
                       const uint32_t *gen_dev, uint32_t gen, uint32_t inst, int variant, uint32_t *bits, int64_t ld,
-                      hipStream_t s, int4 lead_c, bool whole)
+                      hipStream_t s, int4 lead_c, bool whole, const void *cand, bool cand_f64)
 {
     const int64_t per_xcd = ((whole ? ld : pv.np) + 7) / 8, cols = whole ? pv.ldx : pv.D;
     const qpm_status st = check_quad_grid(cols, 8 * per_xcd);
     if (st != QPM_OK) return st;
     const dim3 grid(static_cast<unsigned>(8 * per_xcd), quad_grid(cols, pv.np).y);
-    if (variant == 1)
-        gwo_kernel<1><<<grid, 256, 0, s>>>(pv, leaders, lead_c, a_tab, a, static_cast<uint32_t>(seed),
-                                           static_cast<uint32_t>(seed >> 32), gen_dev, gen, inst, bits, ld, per_xcd,
-                                           whole ? 1 : 0);
-    else
-        gwo_kernel<0><<<grid, 256, 0, s>>>(pv, leaders, lead_c, a_tab, a, static_cast<uint32_t>(seed),
-                                           static_cast<uint32_t>(seed >> 32), gen_dev, gen, inst, bits, ld, per_xcd,
-                                           whole ? 1 : 0);
+    const int64_t ncand = 3 * ((pv.np + 63) / 64);
+    QPM_REQUIRE(cand == nullptr || (leaders != nullptr && ncand <= 256), QPM_EINVAL,
+                "merging leaders needs their buffer and at most 256 candidates");
+#define QPM_GWO(V, M)                                                                                             \
+    gwo_kernel<V, M><<<grid, 256, 0, s>>>(pv, leaders, lead_c, a_tab, a, static_cast<uint32_t>(seed),             \
+                                          static_cast<uint32_t>(seed >> 32), gen_dev, gen, inst, bits, ld,        \
+                                          per_xcd, whole ? 1 : 0, cand, static_cast<int>(ncand))
+#define QPM_GWO_M(M)                                                                                              \
+    if (variant == 1)                                                                                             \
+        QPM_GWO(1, M);                                                                                            \
+    else                                                                                                          \
+        QPM_GWO(0, M);
+    if (cand == nullptr) {
+        QPM_GWO_M(0)
+    } else if (cand_f64) {
+        QPM_GWO_M(2)
+    } else {
+        QPM_GWO_M(1)
+    }
+#undef QPM_GWO_M
+#undef QPM_GWO
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }

@@ -223,10 +223,12 @@ static qpm_status enqueue_generation(qpm_run_s *r, hipEvent_t *ev = nullptr)
                                  r->lazy ? r->acc_cnt : nullptr))
     QPM_STEP(QPM_K_FIT_DE, eval_partials(r))
     // with accepted-only trials the materialise kernel also merges the
-    // leader candidates (no separate one-workgroup kernel)
+    // leader candidates, otherwise the grey-wolf step where it has few
+    // workgroups (no separate one-workgroup kernel)
+    const bool merge = !r->lazy && c.gwo_variant != 2 && merges_leaders(c.np, r->D);
     QPM_STEP(QPM_K_FINISH_DE, eval_finish(r, nullptr, r->leaders, r->cand, nullptr,
                                           r->lazy ? AcceptOut{r->acc_list, r->acc_cnt, r->fbits_prev} : AcceptOut{},
-                                          FinishMode{false, r->lazy}))
+                                          FinishMode{false, r->lazy || merge}))
     if (r->lazy) {  // the accepted trials' genes (timed with the finish)
         st = launch_materialize(pv, r->draws, r->fbits_prev, c.F, r->F_tab, c.CR, c.seed, r->gen, c.inst,
                                 r->acc_list, r->acc_cnt, r->st, r->cand, (c.np + 63) / 64, r->f64(), r->leaders);
@@ -239,7 +241,7 @@ static qpm_status enqueue_generation(qpm_run_s *r, hipEvent_t *ev = nullptr)
         if (st != QPM_OK) return st;
     } else {
         QPM_STEP(QPM_K_GWO, launch_gwo(pv, r->leaders, r->a_tab, 0.0f, c.seed, r->gen, 0u, c.inst, c.gwo_variant,
-                                       r->tbits, r->ld, r->st))
+                                       r->tbits, r->ld, r->st, int4{}, false, merge ? r->cand : nullptr, r->f64()))
     }
     // the evaluation kernel advances the generation counter (it does not
     // read it), so the finish step needs no one-workgroup kernel after it

@@ -10,6 +10,20 @@
 
 namespace qpm {
 
+// a group's leader candidates, from each lane's value and slot
+template <typename T>
+__device__ __forceinline__ void group_best3(T value, int slot, int lane, T *__restrict__ cand_v,
+                                            int32_t *__restrict__ cand_i)
+{
+    T v[1] = {value}, bv;
+    int ix[1] = {slot};
+    const int b = wave_best3<T, 1>(v, ix, lane, &bv);
+    if (lane < 3) {
+        cand_v[lane] = bv;
+        cand_i[lane] = b;
+    }
+}
+
 // Selection for the 64 genomes of group grp (i = 64 grp + lane), from their
 // fitness `value` (rounded to T here); called by one whole wave. Writes
 // f_cur, flags, the group's two packed flag words, the DE draws of
@@ -67,14 +81,7 @@ __device__ __forceinline__ void select_group(double value, int64_t grp, int lane
             acc.list[base + static_cast<uint32_t>(__popcll(am & ((uint64_t(1) << lane) - 1)))] = static_cast<int32_t>(i);
     }
     if (cand_v) {
-        Top3<T> tp = top3_empty<T>();
-        tp.v[0] = fv;
-        tp.i[0] = valid ? static_cast<int>(i) : INT_MAX;
-        wave_top3(tp);
-        if (lane < 3) {
-            cand_v[3 * grp + lane] = lane == 0 ? tp.v[0] : (lane == 1 ? tp.v[1] : tp.v[2]);
-            cand_i[3 * grp + lane] = lane == 0 ? tp.i[0] : (lane == 1 ? tp.i[1] : tp.i[2]);
-        }
+        group_best3(fv, valid ? static_cast<int>(i) : INT_MAX, lane, cand_v + 3 * grp, cand_i + 3 * grp);
     }
 }
 
@@ -86,7 +93,7 @@ __global__ __launch_bounds__(256) void finish_tail_kernel(const T *__restrict__ 
                                                           int32_t *__restrict__ top3_out, uint32_t *__restrict__ gen,
                                                           int advance)
 {
-    if (top3_out) block_top3<T, 256>(cand_v, 3 * ngroups, top3_out, cand_i);
+    if (top3_out) merge_leaders<T, 256>(cand_v, cand_i, 3 * ngroups, top3_out);
     if (advance && threadIdx.x == 0) gen[0] += 1u;
 }
 
