@@ -12,11 +12,13 @@
 // consecutive sub-segments of one 128-domain segment (short sub-segments:
 // about 6 waves per SIMD at 256 rows x 5 x 10^4 domains). The rows' theta of
 // a 16-domain chunk is loaded coalesced (four lanes per row, 16 bytes each),
-// transposed through LDS, and each lane walks its row's domains in order;
-// the coefficients of a domain are the same for every lane (LDS
-// broadcasts).
-// A lane's sub-segment reduces to (A, B, Q, Dg) = (sum d a, sum d b,
-// sum_n d_n b_n (A before n), sum c d^2) with no exchange between lanes; the
+// transposed through LDS, and each lane walks its row's domains in order; the
+// coefficients of a domain are the same for every lane (LDS broadcasts; as
+// scalar loads, whose latency every step then waits for, the forward pass took
+// 25.7 us instead of 21.3 at 256 rows x 5 x 10^4 domains, with two rows per
+// lane to halve the broadcasts 25.4).
+// A lane's sub-segment reduces to (A, B, Q) = (sum d a, sum d b,
+// sum_n d_n (b_n A before n + c_n d_n)) with no exchange between lanes; the
 // workgroup folds its 4 sub-segments per row in order through LDS, the
 // segments of a row combine in order in a small per-row pass that also
 // forms, for the adjoint, the prefix A before and the sum of B from every
@@ -40,9 +42,8 @@ constexpr int kRelaxSub = 32;                 // domains per wave tile
 constexpr int kRelaxSeg = 4 * kRelaxSub;      // domains per workgroup (4 waves)
 constexpr int kRelaxChunk = 16;               // domains per transposed chunk
 
-static RelaxPlan plan_relax(int64_t n, int64_t B, bool f32)
+static RelaxPlan plan_relax(int64_t n, int64_t B)
 {
-    (void)f32;
     RelaxPlan p;
     p.nseg = static_cast<int>((n + kRelaxSeg - 1) / kRelaxSeg);
     p.nsub = 4 * p.nseg;
@@ -86,12 +87,51 @@ __device__ __forceinline__ float tanh_t<float>(float x)
     const float small = fmaf(-x2 * (1.0f / 3.0f), x, x);
     return fabsf(x) < 0.015625f ? small : big;
 }
+// FP64: tanh |x| = E / (E + 2) with E = e^y - 1, y = 2 |x|: y = k ln 2 + r, |r| <=
+// ln 2 / 2, e^r - 1 by its Taylor series (the next term, r^15 / 15!, is below
+// 2^-61 of the sum), E = 2^k (e^r - 1) + (2^k - 1), the quotient by two Newton
+// steps on the hardware reciprocal and a residual correction. 1 from |x| = 20 on
+// (1 - tanh 20 < 2^-56); NaN stays NaN. (The library's tanh takes twice
+// the vector instructions.)
 template <>
-__device__ __forceinline__ double tanh_t<double>(double x) { return tanh(x); }
+__device__ __forceinline__ double tanh_t<double>(double x)
+{
+    const double ax = fabs(x);
+    const double y = 2.0 * fmin(ax, 20.0);
+    const double k = rint(y * 1.4426950408889634);
+    double r = fma(k, -0x1.62e42fefa39efp-1, y);  // ln 2 in two parts
+    r = fma(k, -0x1.abc9e3b39803fp-56, r);
+    double p = 1.0 / 87178291200.0;
+    p = fma(p, r, 1.0 / 6227020800.0);
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p * r, r, r);  // e^r - 1
+    const double two_k = ldexp(1.0, static_cast<int>(k));
+    // E and E + 2 as sums of two parts (two_k - 1 is exact, and larger than the
+    // other term unless it is 0)
+    const double m = two_k - 1.0;
+    const double E = fma(two_k, p, m), E_lo = fma(two_k, p, m - E);
+    const double D = E + 2.0, D_lo = (2.0 - D) + E + E_lo;
+    double q = __builtin_amdgcn_rcp(D);
+    q = fma(fma(-D, q, 1.0), q, q);
+    q = fma(fma(-D, q, 1.0), q, q);
+    double t = E * q;
+    t = fma(fma(-D, t, E) + fma(-D_lo, t, E_lo), q, t);
+    return ax != ax ? x : copysign(t, x);
+}
 
-// the triple of a stretch of domains plus its diagonal sum
+// the triple of a stretch of domains
 struct RTri {
-    double ar, ai, br, bi, qr, qi, gr, gi;
+    double ar, ai, br, bi, qr, qi;
 };
 
 // t <- t (+) u (t covers the domains before u)
@@ -103,41 +143,33 @@ __device__ __forceinline__ void rtri_append(RTri &t, const RTri &u)
     t.ai += u.ai;
     t.br += u.br;
     t.bi += u.bi;
-    t.gr += u.gr;
-    t.gi += u.gi;
 }
 
-__device__ __forceinline__ RTri rtri_shfl_down(const RTri &t, int off)
-{
-    return RTri{__shfl_down(t.ar, off), __shfl_down(t.ai, off), __shfl_down(t.br, off), __shfl_down(t.bi, off),
-                __shfl_down(t.qr, off), __shfl_down(t.qi, off), __shfl_down(t.gr, off), __shfl_down(t.gi, off)};
-}
+// 16 bytes at a time of rows that start at any float (their length need not be
+// a multiple of 4; the hardware takes 4-byte aligned 16-byte accesses)
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// The loads of one 16-domain chunk [kc, kc + 16) of rows rg 64 .. + 63:
-// four instructions of 16 rows each, four lanes per row, 16 bytes per lane
-// (0 past n or B). Issued ahead of use: every chunk of a tile is in flight
-// before the first is consumed.
-template <bool VEC>
-__device__ __forceinline__ void load_chunk_regs(float4 (&v)[4], const float *__restrict__ theta, int64_t ldt,
-                                                int64_t B, int64_t n, int64_t rg, int64_t kc, int lane)
+// The loads of one 16-domain chunk [kc, kc + 16) of rows row0 .. row0 + 63:
+// four instructions of 16 rows each, four lanes per row, 16 bytes per lane. A
+// chunk inside the rows (the same for every lane) takes them plainly, of the
+// last row where there is none (its results are not stored; branches around
+// the loads made the forward pass 28 us instead of 20); past n they are 0.
+// Issued ahead of use. (As four 4-byte loads where a row's length is not a
+// multiple of 4, 256 rows x 49999 domains took 27 and 49 us instead of
+// 20 and 33.)
+__device__ __forceinline__ void load_chunk_regs(float4u (&v)[4], const float *__restrict__ theta, int64_t ldt,
+                                                int64_t B, int64_t n, int64_t row0, int64_t kc, int lane)
 {
+    const int64_t k = kc + (lane & 3) * 4;
 #pragma unroll
     for (int step = 0; step < 4; ++step) {
-        const int rt = step * 16 + (lane >> 2), col = (lane & 3) * 4;
-        const int64_t row = rg * 64 + rt, k = kc + col;
-        float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row < B) {
-            const float *src = theta + row * ldt + k;
-            if (VEC && k + 3 < n) {
-                q = *reinterpret_cast<const float4 *>(src);
-            } else {
-                if (k < n) q.x = src[0];
-                if (k + 1 < n) q.y = src[1];
-                if (k + 2 < n) q.z = src[2];
-                if (k + 3 < n) q.w = src[3];
-            }
+        const float *src = theta + (min(row0 + step * 16 + (lane >> 2), B - 1) * ldt + k);
+        if (kc + kRelaxChunk <= n) {
+            v[step] = *reinterpret_cast<const float4u *>(src);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[step][e] = k + e < n ? src[e] : 0.0f;
         }
-        v[step] = q;
     }
 }
 
@@ -148,7 +180,7 @@ __device__ __forceinline__ void load_chunk_regs(float4 (&v)[4], const float *__r
 // workgroup barrier is needed (a wave's LDS accesses complete in order) and
 // the waves of a workgroup run their chunks independently.
 constexpr int kRelaxST = kRelaxChunk + 1;
-__device__ __forceinline__ void stage_chunk(const float4 (&v)[4], float *tile, int lane)
+__device__ __forceinline__ void stage_chunk(const float4u (&v)[4], float *tile, int lane)
 {
 #pragma unroll
     for (int step = 0; step < 4; ++step) {
@@ -193,17 +225,33 @@ __device__ __forceinline__ void stage_coef(double2 *co, const double4 *__restric
     __builtin_amdgcn_wave_barrier();
 }
 
-// Segment partials: part[(row * nseg + seg) * 8 + c], c = A.re, A.im,
-// B.re, B.im, Q.re, Q.im, Dg.re, Dg.im (doubles, a row's segments
-// contiguous for the per-row combine); with sub, also each
-// sub-segment's A and B: sub[(ss * 4 + c) * lds + row], c = A.re, A.im,
-// B.re, B.im, in T (binary32 for FP32: the adjoint adds them to FP64
-// edges, so their rounding stays far below the FP32 tolerance and the
-// pass pair moves half the bytes for them). Workgroup item (seg, rg) = item / groups, % groups; wave w
-// walks sub-segment 4 seg + w of the rows rg 64 + lane.
-// (FP32: at most about 80 VGPRs, so the 6 waves per SIMD the grid gives at
-// 256 rows x 5 x 10^4 domains fit; the FP64 tanh needs more registers)
-template <typename T, bool VEC>
+// fn(e, a, b, c) for the domains e of chunk ch of the wave's sub-segment, in
+// order, with the coefficients staged in co
+template <typename F>
+__device__ __forceinline__ void walk_chunk(const double2 *co, int wave, int ch, F fn)
+{
+#pragma unroll 1
+    for (int e0 = 0; e0 < kRelaxChunk; e0 += kRelaxStep) {
+#pragma unroll
+        for (int e1 = 0; e1 < kRelaxStep; ++e1) {
+            const double2 *c = co + 3 * (wave * kRelaxSub + ch * kRelaxChunk + e0 + e1);
+            fn(e0 + e1, c[0], c[1], c[2]);
+        }
+    }
+}
+
+// Segment partials: part[(row * nseg + seg) * 6 + c], c = A.re, A.im,
+// B.re, B.im, Q.re, Q.im (doubles, a row's segments contiguous for the per-row
+// combine); with sub, also each sub-segment's A and B: sub[(ss * 4 + c) * lds +
+// row], c = A.re, A.im, B.re, B.im, in T (binary32 for FP32: the adjoint adds
+// them to FP64 edges, so their rounding stays far below the FP32 tolerance and
+// the pass pair moves half the bytes for them). Workgroup item (seg, rg) = item
+// / groups, % groups; wave w walks sub-segment 4 seg + w of the rows rg 64 +
+// lane.
+// 256 rows x 5 x 10^4 domains, FP32: 20.3 us; 15 without the walk (51 MB read
+// and staged), 8.4 the walk's vector instructions at full rate. FP64, 256 x
+// 3 x 10^4: 51 -> 24 us.
+template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 1))) void
 relax_fwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
                  int64_t n, const double4 *__restrict__ ph64,
@@ -212,89 +260,70 @@ relax_fwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
                  T *__restrict__ sub, int64_t lds)
 {
     __shared__ float tiles[4][64 * kRelaxST];
-    // the segment's coefficients
-    __shared__ double2 co[3 * kRelaxSeg];
+    __shared__ double2 co[3 * kRelaxSeg];  // the segment's coefficients
     // after the walk, the fold of the waves (in the tiles)
-    double(*fold)[8][64] = reinterpret_cast<double(*)[8][64]>(&tiles[0][0]);
-    static_assert(sizeof(tiles) >= 3 * 8 * 64 * sizeof(double), "the fold reuses the tiles");
+    double(*fold)[6][64] = reinterpret_cast<double(*)[6][64]>(&tiles[0][0]);
+    static_assert(sizeof(tiles) >= 3 * 6 * 64 * sizeof(double), "the fold reuses the tiles");
     // the wave index as a wave-uniform value: the segment and domain indices
-    // below stay scalar, so the coefficients are scalar loads
+    // below stay scalar
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t item = relax_item(per_xcd, nseg * groups);
     if (item < 0) return;  // the whole workgroup
     const int64_t seg = item / groups, rg = item % groups;
     const int64_t ss = 4 * seg + wave;
     const int64_t row = rg * 64 + lane;
-    double ar = 0, ai = 0, br = 0, bi = 0, qr = 0, qi = 0, gr = 0, gi = 0;
+    RTri t{0, 0, 0, 0, 0, 0};
     constexpr int NCH = kRelaxSub / kRelaxChunk;
     // a chunk is staged, then the next chunk's loads go out into the same
     // registers while the chunk is walked
-    float4 buf[4];
-    load_chunk_regs<VEC>(buf, theta, ldt, B, n, rg, ss * kRelaxSub, lane);
+    float4u buf[4];
+    load_chunk_regs(buf, theta, ldt, B, n, rg * 64, ss * kRelaxSub, lane);
     stage_coef(co, ph64, c64, seg, n);
+    float *tl = tiles[wave];
 #pragma unroll 1
     for (int ch = 0; ch < NCH; ++ch) {
         const int64_t kc = ss * kRelaxSub + ch * kRelaxChunk;
-        float *tl = tiles[wave];
         stage_chunk(buf, tl, lane);
-        if (ch + 1 < NCH) load_chunk_regs<VEC>(buf, theta, ldt, B, n, rg, kc + kRelaxChunk, lane);
-#pragma unroll 1
-        for (int e0 = 0; e0 < kRelaxChunk; e0 += kRelaxStep) {
-#pragma unroll
-            for (int e1 = 0; e1 < kRelaxStep; ++e1) {
-                // past the row's end theta and the coefficients are 0, so
-                // d = tanh 0 = 0 and the domain adds nothing
-                const int e = e0 + e1;
-                const int jl = wave * kRelaxSub + ch * kRelaxChunk + e;  // domain within the segment
-                const double2 ca = co[3 * jl], cb = co[3 * jl + 1], cc = co[3 * jl + 2];
-                const double4 c = make_double4(ca.x, ca.y, cb.x, cb.y);
-                const float th = tl[lane * kRelaxST + e];
-                const double d = static_cast<double>(tanh_t<T>(static_cast<T>(th)));
-                const double yr = d * c.z, yi = d * c.w;
-                qr = fma(yr, ar, fma(-yi, ai, qr));
-                qi = fma(yr, ai, fma(yi, ar, qi));
-                ar = fma(d, c.x, ar);
-                ai = fma(d, c.y, ai);
-                br += yr;
-                bi += yi;
-                const double d2 = d * d;
-                gr = fma(d2, cc.x, gr);
-                gi = fma(d2, cc.y, gi);
-            }
-        }
+        if (ch + 1 < NCH) load_chunk_regs(buf, theta, ldt, B, n, rg * 64, kc + kRelaxChunk, lane);
+        // past the row's end theta and the coefficients are 0, so d = tanh 0 =
+        // 0 and the domain adds nothing
+        walk_chunk(co, wave, ch, [&](int e, double2 a, double2 b, double2 c) {
+            const float th = tl[lane * kRelaxST + e];
+            const double d = static_cast<double>(tanh_t<T>(static_cast<T>(th)));
+            t.qr = fma(d, fma(b.x, t.ar, fma(-b.y, t.ai, d * c.x)), t.qr);
+            t.qi = fma(d, fma(b.x, t.ai, fma(b.y, t.ar, d * c.y)), t.qi);
+            t.ar = fma(d, a.x, t.ar);
+            t.ai = fma(d, a.y, t.ai);
+            t.br = fma(d, b.x, t.br);
+            t.bi = fma(d, b.y, t.bi);
+        });
         __builtin_amdgcn_wave_barrier();  // the tile is refilled by the next chunk
     }
     if (sub != nullptr && row < B) {
         T *o = sub + ss * 4 * lds + row;
-        o[0] = static_cast<T>(ar);
-        o[lds] = static_cast<T>(ai);
-        o[2 * lds] = static_cast<T>(br);
-        o[3 * lds] = static_cast<T>(bi);
+        o[0] = static_cast<T>(t.ar);
+        o[lds] = static_cast<T>(t.ai);
+        o[2 * lds] = static_cast<T>(t.br);
+        o[3 * lds] = static_cast<T>(t.bi);
     }
     // the 4 sub-segments of each row in order: waves 1-3 through LDS into
     // wave 0 (fold reuses the tiles: every wave must be done with its own)
     __syncthreads();
     if (wave > 0) {
-        const double v[8] = {ar, ai, br, bi, qr, qi, gr, gi};
+        const double v[6] = {t.ar, t.ai, t.br, t.bi, t.qr, t.qi};
 #pragma unroll
-        for (int c = 0; c < 8; ++c) fold[wave - 1][c][lane] = v[c];
+        for (int c = 0; c < 6; ++c) fold[wave - 1][c][lane] = v[c];
     }
     __syncthreads();
     if (wave == 0 && row < B) {
-        RTri t{ar, ai, br, bi, qr, qi, gr, gi};
 #pragma unroll
         for (int w = 0; w < 3; ++w)
             rtri_append(t, RTri{fold[w][0][lane], fold[w][1][lane], fold[w][2][lane], fold[w][3][lane],
-                                fold[w][4][lane], fold[w][5][lane], fold[w][6][lane], fold[w][7][lane]});
-        double *o = part + (row * nseg + seg) * 8;
-        o[0] = t.ar;
-        o[1] = t.ai;
-        o[2] = t.br;
-        o[3] = t.bi;
-        o[4] = t.qr;
-        o[5] = t.qi;
-        o[6] = t.gr;
-        o[7] = t.gi;
+                                fold[w][4][lane], fold[w][5][lane]});
+        double2 *o = reinterpret_cast<double2 *>(part + (row * nseg + seg) * 6);
+        o[0] = make_double2(t.ar, t.ai);
+        o[1] = make_double2(t.br, t.bi);
+        o[2] = make_double2(t.qr, t.qi);
     }
 }
 
@@ -302,10 +331,10 @@ relax_fwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
 // the identity of rtri_append).
 __device__ __forceinline__ RTri load_part(const double *__restrict__ pr, int sg, int nseg)
 {
-    if (sg >= nseg) return RTri{0, 0, 0, 0, 0, 0, 0, 0};
-    const double2 *p = reinterpret_cast<const double2 *>(pr + static_cast<int64_t>(sg) * 8);
-    const double2 a = p[0], b = p[1], q = p[2], g = p[3];
-    return RTri{a.x, a.y, b.x, b.y, q.x, q.y, g.x, g.y};
+    if (sg >= nseg) return RTri{0, 0, 0, 0, 0, 0};
+    const double2 *p = reinterpret_cast<const double2 *>(pr + static_cast<int64_t>(sg) * 6);
+    const double2 a = p[0], b = p[1], q = p[2];
+    return RTri{a.x, a.y, b.x, b.y, q.x, q.y};
 }
 
 // DPP moves within 16-lane rows (double as two 32-bit moves): lane l reads
@@ -333,15 +362,14 @@ template <int K>
 __device__ __forceinline__ void rtri_tree_level(RTri &u, int lane)
 {
     const RTri o{row_from_above<K>(u.ar), row_from_above<K>(u.ai), row_from_above<K>(u.br),
-                 row_from_above<K>(u.bi), row_from_above<K>(u.qr), row_from_above<K>(u.qi),
-                 row_from_above<K>(u.gr), row_from_above<K>(u.gi)};
+                 row_from_above<K>(u.bi), row_from_above<K>(u.qr), row_from_above<K>(u.qi)};
     if ((lane & (2 * K - 1)) == 0) rtri_append(u, o);
 }
 
 __device__ __forceinline__ RTri rtri_lane(const RTri &u, int l)
 {
-    return RTri{lane_value(u.ar, l), lane_value(u.ai, l), lane_value(u.br, l), lane_value(u.bi, l),
-                lane_value(u.qr, l), lane_value(u.qi, l), lane_value(u.gr, l), lane_value(u.gi, l)};
+    return RTri{lane_value(u.ar, l), lane_value(u.ai, l), lane_value(u.br, l),
+                lane_value(u.bi, l), lane_value(u.qr, l), lane_value(u.qi, l)};
 }
 
 // inclusive scan of v within each 16-lane row
@@ -359,7 +387,7 @@ constexpr int kCombineBatch = 4;
 // waves per row of the combine, each taking a contiguous share of the rounds
 constexpr int kCombineWaves = 8;
 
-// Per row (a workgroup of kCombineWaves waves): S = (combined Q) + sum Dg and
+// Per row (a workgroup of kCombineWaves waves): S = the combined Q and
 // f = |S|^2; with `edges`, also the prefix A before every segment and the
 // sum of B from the segment on: edges[(row * nseg + seg) * 4 + c],
 // c = Apre.re, Apre.im, Bfrom.re, Bfrom.im.
@@ -378,19 +406,19 @@ __global__ __launch_bounds__(64 * kCombineWaves) void relax_combine_kernel(const
                                                                           float *__restrict__ f,
                                                                           double *__restrict__ edges)
 {
-    __shared__ double folds[kCombineWaves][8];
+    __shared__ double folds[kCombineWaves][6];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t row = blockIdx.x;
     if (row >= B) return;  // the whole workgroup (the grid is B workgroups)
-    const double *pr = part + row * nseg * 8;
+    const double *pr = part + row * nseg * 6;
     const int rounds = (nseg + 63) / 64;
     const int t_beg = wave * rounds / kCombineWaves, t_end = (wave + 1) * rounds / kCombineWaves;
-    RTri mine{0, 0, 0, 0, 0, 0, 0, 0};
+    RTri mine{0, 0, 0, 0, 0, 0};
     for (int t0 = t_beg; t0 < t_end; t0 += kCombineBatch) {
         RTri u[kCombineBatch];  // every round of the batch in flight at once
 #pragma unroll
         for (int b = 0; b < kCombineBatch; ++b)
-            u[b] = t0 + b < t_end ? load_part(pr, 64 * (t0 + b) + lane, nseg) : RTri{0, 0, 0, 0, 0, 0, 0, 0};
+            u[b] = t0 + b < t_end ? load_part(pr, 64 * (t0 + b) + lane, nseg) : RTri{0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int b = 0; b < kCombineBatch; ++b) {
             if (t0 + b < t_end) {
@@ -404,19 +432,18 @@ __global__ __launch_bounds__(64 * kCombineWaves) void relax_combine_kernel(const
         }
     }
     if (lane == 0) {
-        const double v[8] = {mine.ar, mine.ai, mine.br, mine.bi, mine.qr, mine.qi, mine.gr, mine.gi};
+        const double v[6] = {mine.ar, mine.ai, mine.br, mine.bi, mine.qr, mine.qi};
 #pragma unroll
-        for (int c = 0; c < 8; ++c) folds[wave][c] = v[c];
+        for (int c = 0; c < 6; ++c) folds[wave][c] = v[c];
     }
     __syncthreads();
     // the row's fold (the same order in every wave) and the A and B of the
     // waves before this one
-    RTri tot{0, 0, 0, 0, 0, 0, 0, 0};
+    RTri tot{0, 0, 0, 0, 0, 0};
     double carry[4] = {0, 0, 0, 0};  // A.re, A.im, B.re, B.im before the wave's next round
 #pragma unroll
     for (int w = 0; w < kCombineWaves; ++w) {
-        const RTri tw{folds[w][0], folds[w][1], folds[w][2], folds[w][3],
-                      folds[w][4], folds[w][5], folds[w][6], folds[w][7]};
+        const RTri tw{folds[w][0], folds[w][1], folds[w][2], folds[w][3], folds[w][4], folds[w][5]};
         if (w < wave) {
             carry[0] += tw.ar;
             carry[1] += tw.ai;
@@ -435,7 +462,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void relax_combine_kernel(const
                 const int sg = 64 * (t0 + b) + lane;
                 vb[b] = make_double4(0.0, 0.0, 0.0, 0.0);
                 if (t0 + b < t_end && sg < nseg) {
-                    const double2 *p = reinterpret_cast<const double2 *>(pr + static_cast<int64_t>(sg) * 8);
+                    const double2 *p = reinterpret_cast<const double2 *>(pr + static_cast<int64_t>(sg) * 6);
                     const double2 a = p[0], bb = p[1];
                     vb[b] = make_double4(a.x, a.y, bb.x, bb.y);
                 }
@@ -466,7 +493,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void relax_combine_kernel(const
         }
     }
     if (threadIdx.x != 0) return;
-    const double Sr = tot.qr + tot.gr, Si = tot.qi + tot.gi;
+    const double Sr = tot.qr, Si = tot.qi;
     if (S) {
         S[2 * row] = Sr;
         S[2 * row + 1] = Si;
@@ -482,9 +509,9 @@ __global__ __launch_bounds__(64 * kCombineWaves) void relax_combine_kernel(const
 //   grad_k = grad_f 2 Re(conj(S) (b_k P_{k-1} + a_k R_{k+1} + 2 c_k d_k)) (1 - d_k^2);
 // each chunk's gradients go back through the wave's LDS tile and are stored
 // coalesced (four lanes per row, 16 bytes each).
-// (no register cap: held to 6 waves per SIMD, the FP32 adjoint spills and
-// measured slower than at its natural 82 VGPRs)
-template <typename T, bool VEC>
+// 256 rows x 5 x 10^4 domains, FP32: 28 us; 24 without the walk (102 MB read and
+// written). FP64, 256 x 3 x 10^4: 54 -> 29 us.
+template <typename T>
 __global__ __launch_bounds__(256) void
 relax_bwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
                  int64_t n, const double4 *__restrict__ ph64,
@@ -496,16 +523,15 @@ relax_bwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
                  float *__restrict__ grad_theta, int64_t ldg)
 {
     __shared__ float tiles[4][64 * kRelaxST];
-    __shared__ double2 co[3 * kRelaxSeg];
+    __shared__ double2 co[3 * kRelaxSeg];  // the segment's coefficients
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t item = relax_item(per_xcd, nseg * groups);
     if (item < 0) return;  // the whole workgroup
     const int64_t seg = item / groups, rg = item % groups;
     const int64_t ss = 4 * seg + wave;
     const int64_t row = rg * 64 + lane;
-    const bool rv = row < B;
     double pr = 0, pi = 0, rr = 0, ri = 0, Sr = 0, Si = 0, gs = 0;
-    if (rv) {
+    if (row < B) {
         const double *e = edges + (row * nseg + seg) * 4;
         pr = e[0];
         pi = e[1];
@@ -526,50 +552,43 @@ relax_bwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
     constexpr int NCH = kRelaxSub / kRelaxChunk;
     // a chunk is staged, then the next chunk's loads go out into the same
     // registers while the chunk is walked
-    float4 buf[4];
-    load_chunk_regs<VEC>(buf, theta, ldt, B, n, rg, ss * kRelaxSub, lane);
+    float4u buf[4];
+    load_chunk_regs(buf, theta, ldt, B, n, rg * 64, ss * kRelaxSub, lane);
     stage_coef(co, ph64, c64, seg, n);
 #pragma unroll 1
     for (int ch = 0; ch < NCH; ++ch) {
         const int64_t kc = ss * kRelaxSub + ch * kRelaxChunk;
         stage_chunk(buf, tl, lane);
-        if (ch + 1 < NCH) load_chunk_regs<VEC>(buf, theta, ldt, B, n, rg, kc + kRelaxChunk, lane);
-#pragma unroll 1
-        for (int e0 = 0; e0 < kRelaxChunk; e0 += kRelaxStep) {
-#pragma unroll
-            for (int e1 = 0; e1 < kRelaxStep; ++e1) {
-                // past the row's end theta and the coefficients are 0: d = 0
-                // and the domain adds nothing (its gradient is not stored)
-                const int e = e0 + e1;
-                const int jl = wave * kRelaxSub + ch * kRelaxChunk + e;  // domain within the segment
-                const double2 ca = co[3 * jl], cb = co[3 * jl + 1], cc = co[3 * jl + 2];
-                const double4 c = make_double4(ca.x, ca.y, cb.x, cb.y);
-                float *slot = tl + lane * kRelaxST + e;  // theta in, the gradient out
-                const double d = static_cast<double>(tanh_t<T>(static_cast<T>(*slot)));
-                // R_{k+1}: B from k + 1 on
-                rr = fma(-d, c.z, rr);
-                ri = fma(-d, c.w, ri);
-                const double two_d = d + d;
-                const double dsr =
-                    fma(c.z, pr, fma(-c.w, pi, fma(c.x, rr, fma(-c.y, ri, two_d * cc.x))));
-                const double dsi = fma(c.z, pi, fma(c.w, pr, fma(c.x, ri, fma(c.y, rr, two_d * cc.y))));
-                const double re = fma(Sr, dsr, Si * dsi);
-                *slot = static_cast<float>(gs * re * fma(-d, d, 1.0));
-                pr = fma(d, c.x, pr);
-                pi = fma(d, c.y, pi);
-            }
-        }
+        if (ch + 1 < NCH) load_chunk_regs(buf, theta, ldt, B, n, rg * 64, kc + kRelaxChunk, lane);
+        // past the row's end theta and the coefficients are 0: d = 0 and the
+        // domain adds nothing (its gradient is not stored)
+        walk_chunk(co, wave, ch, [&](int e, double2 a, double2 b, double2 c) {
+            float *slot = tl + lane * kRelaxST + e;  // theta in, the gradient out
+            const double d = static_cast<double>(tanh_t<T>(static_cast<T>(*slot)));
+            // R_{k+1}: B from k + 1 on
+            rr = fma(-d, b.x, rr);
+            ri = fma(-d, b.y, ri);
+            const double two_d = d + d;
+            const double dsr = fma(b.x, pr, fma(-b.y, pi, fma(a.x, rr, fma(-a.y, ri, two_d * c.x))));
+            const double dsi = fma(b.x, pi, fma(b.y, pr, fma(a.x, ri, fma(a.y, rr, two_d * c.y))));
+            const double re = fma(Sr, dsr, Si * dsi);
+            *slot = static_cast<float>(gs * re * fma(-d, d, 1.0));
+            pr = fma(d, a.x, pr);
+            pi = fma(d, a.y, pi);
+        });
         __builtin_amdgcn_wave_barrier();
-        // the chunk's gradients, coalesced (rows of this wave's tile)
+        // the chunk's gradients, coalesced (rows of this wave's tile), as
+        // load_chunk_regs reads theta
+        const int col = (lane & 3) * 4;
+        const float *v = tl + (lane >> 2) * kRelaxST + col;
+        const bool inside = kc + kRelaxChunk <= n;
 #pragma unroll
-        for (int step = 0; step < 4; ++step) {
-            const int rt = step * 16 + (lane >> 2), col = (lane & 3) * 4;
-            const int64_t r = rg * 64 + rt, k = kc + col;
-            if (r < B && k < n) {
-                float *dst = grad_theta + r * ldg + k;
-                const float *v = tl + rt * kRelaxST + col;
-                if (VEC && k + 3 < n) {
-                    *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+        for (int step = 0; step < 4; ++step, v += 16 * kRelaxST) {
+            const int64_t r = rg * 64 + step * 16 + (lane >> 2), k = kc + col;
+            if (r < B) {
+                float *dst = grad_theta + (r * ldg + k);
+                if (inside) {
+                    *reinterpret_cast<float4u *>(dst) = float4u{v[0], v[1], v[2], v[3]};
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -582,44 +601,34 @@ relax_bwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
 }
 
 template <typename T>
-static void launch_relax_fwd(const Design &d, const RelaxPlan &pl, bool vec, const float *theta, int64_t B,
-                             int64_t ldt, double *part, T *sub, int64_t lds, hipStream_t s)
+static void launch_relax_fwd(const Design &d, const RelaxPlan &pl, const float *theta, int64_t B, int64_t ldt,
+                             double *part, T *sub, int64_t lds, hipStream_t s)
 {
     const int64_t per_xcd = relax_per_xcd(pl);
-    const unsigned blocks = static_cast<unsigned>(8 * per_xcd);
-    if (vec)
-        relax_fwd_kernel<T, true><<<blocks, 256, 0, s>>>(theta, ldt, B, d.n, d.ph64, d.c64, pl.groups, pl.nseg,
-                                                         per_xcd, part, sub, lds);
-    else
-        relax_fwd_kernel<T, false><<<blocks, 256, 0, s>>>(theta, ldt, B, d.n, d.ph64, d.c64, pl.groups, pl.nseg,
-                                                          per_xcd, part, sub, lds);
+    relax_fwd_kernel<T><<<static_cast<unsigned>(8 * per_xcd), 256, 0, s>>>(theta, ldt, B, d.n, d.ph64, d.c64, pl.groups,
+                                                                           pl.nseg, per_xcd, part, sub, lds);
 }
 
 template <typename T>
-static void launch_relax_bwd(const Design &d, const RelaxPlan &pl, bool vec, const float *theta, int64_t B,
-                             int64_t ldt, const double *edges, const T *sub, int64_t lde, const double *S,
-                             const float *grad_f, float *grad_theta, int64_t ldg, hipStream_t s)
+static void launch_relax_bwd(const Design &d, const RelaxPlan &pl, const float *theta, int64_t B, int64_t ldt,
+                             const double *edges, const T *sub, int64_t lde, const double *S, const float *grad_f,
+                             float *grad_theta, int64_t ldg, hipStream_t s)
 {
     const int64_t per_xcd = relax_per_xcd(pl);
-    const unsigned blocks = static_cast<unsigned>(8 * per_xcd);
-    if (vec)
-        relax_bwd_kernel<T, true><<<blocks, 256, 0, s>>>(theta, ldt, B, d.n, d.ph64, d.c64, pl.groups, pl.nseg,
-                                                         per_xcd, edges, sub, lde, S, grad_f, grad_theta, ldg);
-    else
-        relax_bwd_kernel<T, false><<<blocks, 256, 0, s>>>(theta, ldt, B, d.n, d.ph64, d.c64, pl.groups, pl.nseg,
-                                                          per_xcd, edges, sub, lde, S, grad_f, grad_theta, ldg);
+    relax_bwd_kernel<T><<<static_cast<unsigned>(8 * per_xcd), 256, 0, s>>>(theta, ldt, B, d.n, d.ph64, d.c64, pl.groups,
+                                                                           pl.nseg, per_xcd, edges, sub, lde, S, grad_f,
+                                                                           grad_theta, ldg);
 }
 
-// segment partials part (8 nseg B doubles) and, with sub, the
+// segment partials part (6 nseg B doubles) and, with sub, the
 // sub-segments' A and B (4 nsub lds doubles)
 static qpm_status relax_partials(const Design &d, qpm_prec p, const float *theta, int64_t B, int64_t ldt,
                                  const RelaxPlan &pl, double *part, void *sub, int64_t lds, hipStream_t s)
 {
-    const bool vec = (reinterpret_cast<uintptr_t>(theta) & 15u) == 0 && ldt % 4 == 0;
     if (p == QPM_PREC_F32)
-        launch_relax_fwd<float>(d, pl, vec, theta, B, ldt, part, static_cast<float *>(sub), lds, s);
+        launch_relax_fwd<float>(d, pl, theta, B, ldt, part, static_cast<float *>(sub), lds, s);
     else
-        launch_relax_fwd<double>(d, pl, vec, theta, B, ldt, part, static_cast<double *>(sub), lds, s);
+        launch_relax_fwd<double>(d, pl, theta, B, ldt, part, static_cast<double *>(sub), lds, s);
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }
@@ -738,7 +747,7 @@ QPM_API qpm_status qpm_relax_edges_size(qpm_design d, qpm_prec p, int64_t B, int
     QPM_REQUIRE(p == QPM_PREC_F32 || p == QPM_PREC_F64, QPM_EINVAL, "unknown precision %d", (int)p);
     QPM_REQUIRE(B >= 1 && B <= (int64_t(1) << 24), QPM_EINVAL, "batch must be in [1, 2^24] (got %lld)",
                 (long long)B);
-    *count = relax_edges_count(plan_relax(d->n, B, p == QPM_PREC_F32), B, p == QPM_PREC_F32);
+    *count = relax_edges_count(plan_relax(d->n, B), B, p == QPM_PREC_F32);
     return QPM_OK;
 }
 
@@ -750,12 +759,12 @@ QPM_API qpm_status qpm_relax_forward(qpm_design d, qpm_prec p, const float *thet
     if (st != QPM_OK) return st;
     QPM_REQUIRE(f != nullptr || S != nullptr, QPM_EINVAL, "at least one of f and S must be given");
     hipStream_t s = static_cast<hipStream_t>(sv);
-    const RelaxPlan pl = plan_relax(d->n, B, p == QPM_PREC_F32);
+    const RelaxPlan pl = plan_relax(d->n, B);
     QPM_REQUIRE(static_cast<int64_t>(pl.nseg) * pl.groups < (int64_t(1) << 31) - 8, QPM_ERANGE,
                 "batch x segments too large for one launch");
     ScratchLease lease(d->scratch, s);
     void *ws = nullptr;
-    st = lease.begin(sizeof(double) * 8 * pl.nseg * B, &ws);
+    st = lease.begin(sizeof(double) * 6 * pl.nseg * B, &ws);
     if (st != QPM_OK) return st;
     double *part = static_cast<double *>(ws);
     // edges: the segments' (A before, B from) then the sub-segments' (A, B)
@@ -777,7 +786,7 @@ QPM_API qpm_status qpm_relax_backward(qpm_design d, qpm_prec p, const float *the
                 "S, grad_f and grad_theta must not be NULL");
     QPM_REQUIRE(ldg >= d->n, QPM_EINVAL, "ldg (%lld) must be >= n_domains", (long long)ldg);
     hipStream_t s = static_cast<hipStream_t>(sv);
-    const RelaxPlan pl = plan_relax(d->n, B, p == QPM_PREC_F32);
+    const RelaxPlan pl = plan_relax(d->n, B);
     QPM_REQUIRE(static_cast<int64_t>(pl.nseg) * pl.groups < (int64_t(1) << 31) - 8, QPM_ERANGE,
                 "batch x segments too large for one launch");
     ScratchLease lease(d->scratch, s);
@@ -787,10 +796,10 @@ QPM_API qpm_status qpm_relax_backward(qpm_design d, qpm_prec p, const float *the
     if (!edges) {
         // no saved edges: recompute the segment partials and their edges
         void *ws = nullptr;
-        st = lease.begin(sizeof(double) * (12 * static_cast<int64_t>(pl.nseg) + 4 * pl.nsub) * B, &ws);
+        st = lease.begin(sizeof(double) * (10 * static_cast<int64_t>(pl.nseg) + 4 * pl.nsub) * B, &ws);
         if (st != QPM_OK) return st;
         double *work = static_cast<double *>(ws);
-        double *ework = work + static_cast<int64_t>(8) * pl.nseg * B;
+        double *ework = work + static_cast<int64_t>(6) * pl.nseg * B;
         double *swork = ework + static_cast<int64_t>(4) * pl.nseg * B;
         st = relax_partials(*d, p, theta, B, ldt, pl, work, swork, B, s);
         if (st == QPM_OK) st = launch_combine(work, pl.nseg, B, nullptr, nullptr, ework, s);
@@ -798,13 +807,11 @@ QPM_API qpm_status qpm_relax_backward(qpm_design d, qpm_prec p, const float *the
         sub = swork;
     }
     if (st == QPM_OK) {
-        const bool vec = (reinterpret_cast<uintptr_t>(theta) & 15u) == 0 && ldt % 4 == 0 &&
-                         (reinterpret_cast<uintptr_t>(grad_theta) & 15u) == 0 && ldg % 4 == 0;
         if (p == QPM_PREC_F32)
-            launch_relax_bwd<float>(*d, pl, vec, theta, B, ldt, e, static_cast<const float *>(sub), lde, S, grad_f,
+            launch_relax_bwd<float>(*d, pl, theta, B, ldt, e, static_cast<const float *>(sub), lde, S, grad_f,
                                     grad_theta, ldg, s);
         else
-            launch_relax_bwd<double>(*d, pl, vec, theta, B, ldt, e, static_cast<const double *>(sub), lde, S, grad_f,
+            launch_relax_bwd<double>(*d, pl, theta, B, ldt, e, static_cast<const double *>(sub), lde, S, grad_f,
                                      grad_theta, ldg, s);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) {
