@@ -411,6 +411,29 @@ __global__ __launch_bounds__(256) void batch_gwo_kernel(BatchPop bp, const InstD
     store_word(nib, q, id.n, bits + id.wofs * ld, ld, i);
 }
 
+// The same for large batches (kGwoRowsGenes): R consecutive individuals per
+// workgroup (gwo_rows), grid x = 8 per_xcd groups of them. 32 designs of up to
+// 5 x 10^4 domains, NP = 256 (193 x 10^6 genes): 410 -> 308 us.
+template <int VARIANT, int R>
+__global__ __launch_bounds__(256) void batch_gwo_rows_kernel(BatchPop bp, const InstDesc *__restrict__ inst,
+                                                        const Tile *__restrict__ tiles,
+                                                        const int32_t *__restrict__ leaders,
+                                                        const float *__restrict__ a_tab, uint32_t k0, uint32_t k1,
+                                                        const uint32_t *__restrict__ gen, uint32_t inst0,
+                                                        uint32_t *__restrict__ bits, int64_t ld, int per_xcd)
+{
+    const int np = static_cast<int>(bp.np);
+    const int i0 = R * (static_cast<int>(blockIdx.x & 7u) * per_xcd + static_cast<int>(blockIdx.x >> 3));
+    if (i0 >= np) return;
+    const Tile tl = tiles[blockIdx.y];
+    const InstDesc id = inst[tl.inst];
+    const int L0 = leaders[3 * tl.inst], L1 = leaders[3 * tl.inst + 1], L2 = leaders[3 * tl.inst + 2];
+    if (L0 < 0 || L0 >= np || L1 < 0 || L1 >= np || L2 < 0 || L2 >= np) return;
+    const uint32_t g = gen[0];
+    gwo_rows<VARIANT, R>(view_of(bp, id, tl.inst), i0, static_cast<int64_t>(tl.chunk) * 256 + threadIdx.x, L0, L1, L2,
+                         a_tab[g], g, inst0 + static_cast<uint32_t>(tl.inst), k0, k1, bits + id.wofs * ld, ld, false);
+}
+
 // rows of instance b's current population -> dense out[np][ldo]
 __global__ __launch_bounds__(256) void batch_gather_kernel(BatchPop bp, const InstDesc *__restrict__ inst, int b,
                                                            float *__restrict__ out, int64_t ldo)
@@ -1014,16 +1037,26 @@ static qpm_status launch_batch_de(qpm_batch_run_s *r, int ipw, int passes)
 static qpm_status launch_batch_gwo(qpm_batch_run_s *r)
 {
     const qpm_run_config &c = r->cfg;
-    const int64_t per_xcd = (c.np + 7) / 8;
+    const uint32_t k0 = static_cast<uint32_t>(c.seed), k1 = static_cast<uint32_t>(c.seed >> 32);
+    const bool rows = r->gene_bytes >= sizeof(float) * kGwoRowsGenes;
+    const int64_t group = rows ? 32 : 8, per_xcd = (c.np + group - 1) / group;
     const dim3 grid(static_cast<unsigned>(8 * per_xcd), static_cast<unsigned>(r->n_gtiles));
-    if (c.gwo_variant == 1)
-        batch_gwo_kernel<1><<<grid, 256, 0, r->st>>>(r->pop(), r->inst, r->gtiles, r->leaders, r->a_tab,
-                                                    static_cast<uint32_t>(c.seed), static_cast<uint32_t>(c.seed >> 32),
-                                                    r->gen, c.inst, r->bits, r->ld, per_xcd);
-    else
-        batch_gwo_kernel<0><<<grid, 256, 0, r->st>>>(r->pop(), r->inst, r->gtiles, r->leaders, r->a_tab,
-                                                    static_cast<uint32_t>(c.seed), static_cast<uint32_t>(c.seed >> 32),
-                                                    r->gen, c.inst, r->bits, r->ld, per_xcd);
+    if (rows) {
+        if (c.gwo_variant == 1)
+            batch_gwo_rows_kernel<1, 4><<<grid, 256, 0, r->st>>>(r->pop(), r->inst, r->gtiles, r->leaders, r->a_tab, k0,
+                                                                 k1, r->gen, c.inst, r->bits, r->ld,
+                                                                 static_cast<int>(per_xcd));
+        else
+            batch_gwo_rows_kernel<0, 4><<<grid, 256, 0, r->st>>>(r->pop(), r->inst, r->gtiles, r->leaders, r->a_tab, k0,
+                                                                 k1, r->gen, c.inst, r->bits, r->ld,
+                                                                 static_cast<int>(per_xcd));
+    } else if (c.gwo_variant == 1) {
+        batch_gwo_kernel<1><<<grid, 256, 0, r->st>>>(r->pop(), r->inst, r->gtiles, r->leaders, r->a_tab, k0, k1, r->gen,
+                                                    c.inst, r->bits, r->ld, per_xcd);
+    } else {
+        batch_gwo_kernel<0><<<grid, 256, 0, r->st>>>(r->pop(), r->inst, r->gtiles, r->leaders, r->a_tab, k0, k1, r->gen,
+                                                    c.inst, r->bits, r->ld, per_xcd);
+    }
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }

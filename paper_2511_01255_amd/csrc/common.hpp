@@ -297,6 +297,9 @@ qpm_status launch_draws(int64_t np, int64_t D, uint64_t seed, const uint32_t *ge
 // cand: take the leaders from a finish step's candidates (defer_leaders; double
 // values with cand_f64) and store them in `leaders` (when merges_leaders)
 constexpr int64_t kMergeGroups = 3000;
+// grey-wolf steps take 4 individuals per workgroup from this many genes on (see
+// launch_gwo)
+constexpr int64_t kGwoRowsGenes = 10000000;
 bool merges_leaders(int64_t np, int64_t D);
 qpm_status launch_gwo(const PopView &pv, int32_t *leaders, const float *a_tab, float a,
                       uint64_t seed, const uint32_t *gen_dev, uint32_t gen, uint32_t inst,

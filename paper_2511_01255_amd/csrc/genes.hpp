@@ -344,16 +344,11 @@ __device__ __forceinline__ float4 gwo_quad_coef(float4 xv, float4 X0, float4 X1,
     return make_float4(ys[0], ys[1], ys[2], ys[3]);
 }
 
-// A and C of gene quad q of individual i from its 12 words
-__device__ __forceinline__ void gwo_coef(uint32_t q, uint32_t i, uint32_t g, uint32_t inst, uint32_t k0, uint32_t k1,
-                                         float a, float two_a, float (&A)[12], float (&Cc)[12])
+// A and C of a quad from its 12 words
+__device__ __forceinline__ void gwo_word_coef(U4 wa, U4 wb, U4 wc, float a, float two_a, float (&A)[12],
+                                              float (&Cc)[12])
 {
-    const uint32_t c3 = (inst << 8) | kTagGwo;
-    const uint32_t cq = 3u * q;
     const float two_a_s = two_a * 0x1p-16f;
-    const U4 wa = philox10(cq, i, g, c3, k0, k1);
-    const U4 wb = philox10(cq + 1u, i, g, c3, k0, k1);
-    const U4 wc = philox10(cq + 2u, i, g, c3, k0, k1);
     const uint32_t wrd[12] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w, wc.x, wc.y, wc.z, wc.w};
 #pragma unroll
     for (int t = 0; t < 12; ++t) {
@@ -365,6 +360,16 @@ __device__ __forceinline__ void gwo_coef(uint32_t q, uint32_t i, uint32_t g, uin
     }
 }
 
+// A and C of gene quad q of individual i
+__device__ __forceinline__ void gwo_coef(uint32_t q, uint32_t i, uint32_t g, uint32_t inst, uint32_t k0, uint32_t k1,
+                                         float a, float two_a, float (&A)[12], float (&Cc)[12])
+{
+    const uint32_t c3 = (inst << 8) | kTagGwo;
+    const uint32_t cq = 3u * q;
+    gwo_word_coef(philox10(cq, i, g, c3, k0, k1), philox10(cq + 1u, i, g, c3, k0, k1),
+                  philox10(cq + 2u, i, g, c3, k0, k1), a, two_a, A, Cc);
+}
+
 template <int VARIANT>
 __device__ __forceinline__ float4 gwo_quad(float4 xv, float4 X0, float4 X1, float4 X2, uint32_t q, uint32_t i,
                                            uint32_t g, uint32_t inst, uint32_t k0, uint32_t k1, float a, float two_a)
@@ -372,6 +377,79 @@ __device__ __forceinline__ float4 gwo_quad(float4 xv, float4 X0, float4 X1, floa
     float A[12], Cc[12];
     gwo_coef(q, i, g, inst, k0, k1, a, two_a, A, Cc);
     return gwo_quad_coef<VARIANT>(xv, X0, X1, X2, A, Cc);
+}
+
+// four words at any word address
+typedef uint32_t uint4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// The grey-wolf candidates of R consecutive individuals i0 .. i0 + R - 1 (i0 a
+// multiple of R) of gene quad q per thread, as gwo_quad: a thread keeps its
+// quad's leader genes and the individual-free part of its Philox calls for all R,
+// loads the next row while it computes one, and stores R bit words at once.
+// Leaders L0 .. L2 (in [0, np)) and their words are left alone; with `whole`
+// rows are written up to ldx and columns up to ld as gwo_kernel says.
+template <int VARIANT, int R>
+__device__ __forceinline__ void gwo_rows(const PopView &pv, int i0, int64_t q, int L0, int L1, int L2, float a,
+                                         uint32_t g, uint32_t inst, uint32_t k0, uint32_t k1,
+                                         uint32_t *__restrict__ bits, int64_t ld, bool whole)
+{
+    const int np = static_cast<int>(pv.np);
+    const int64_t D = pv.D, j0 = 4 * q, cols = whole ? pv.ldx : D;
+    const int64_t jc = j0 < cols ? j0 : (cols - 1) / 4 * 4;  // (in bounds)
+    // rows by offsets between the buffers: as a choice between the pointers of
+    // `pv`, the compiler keeps `pv` in memory
+    const int64_t dx = pv.x1 - pv.x0, dout = pv.out1 - pv.out0;
+    auto flag = [&](int r) -> bool { return pv.flags != nullptr && pv.flags[r] != 0u; };
+    auto quad_of = [&](int r, bool second) -> float4 {
+        return *reinterpret_cast<const float4 *>(pv.x0 + (r * pv.ldx + (second ? dx : 0) + jc));
+    };
+    bool second[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) second[r] = flag(min(i0 + r, np - 1));
+    float4 next = quad_of(min(i0, np - 1), second[0]);
+    const float4 X0 = quad_of(L0, flag(L0)), X1 = quad_of(L1, flag(L1)), X2 = quad_of(L2, flag(L2));
+    const float two_a = 2.0f * a;
+    const uint32_t c3 = (inst << 8) | kTagGwo, cq = 3u * static_cast<uint32_t>(q);
+    const PhiloxHead ha = philox10_head(cq, g, c3, k0, k1), hb = philox10_head(cq + 1u, g, c3, k0, k1),
+                     hc = philox10_head(cq + 2u, g, c3, k0, k1);
+    uint32_t w[R];
+    bool plain = true;  // every individual moves (the same in every lane)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = i0 + r;
+        const float4 xv = next;
+        if (r + 1 < R) next = quad_of(min(i + 1, np - 1), second[r + 1 < R ? r + 1 : r]);
+        float *const out = pv.out0 + (i * pv.ldx + (second[r] ? 0 : dout));
+        uint32_t nib = 0;
+        if (i < np && i != L0 && i != L1 && i != L2) {
+            const uint64_t pi = philox10_individual(static_cast<uint32_t>(i), g, k0);
+            float A[12], Cc[12];
+            gwo_word_coef(philox10_rest(ha, pi, k0, k1), philox10_rest(hb, pi, k0, k1), philox10_rest(hc, pi, k0, k1),
+                          a, two_a, A, Cc);
+            const float4 yv = gwo_quad_coef<VARIANT>(xv, X0, X1, X2, A, Cc);
+            if (j0 < cols) store_quad_nt(out, j0, D, cols, yv, xv);
+            nib = j0 < D ? quad_nibble(yv, j0, D) : 0u;
+        } else {
+            plain = false;
+            if (whole && i < np && j0 < cols) store_quad_nt(out, j0, cols, xv);
+        }
+        w[r] = or8_into_last(nib << (4 * (threadIdx.x & 7)));
+    }
+    if ((threadIdx.x & 7) == 7 && 4 * (q & ~int64_t(7)) < D) {
+        uint32_t *const b = bits + ((q >> 3) * ld + i0);
+        if (plain || whole) {
+            if constexpr (R == 4)
+                *reinterpret_cast<uint4u *>(b) = uint4u{w[0], w[1], w[2], w[3]};
+            else
+                for (int r = 0; r < R; ++r) b[r] = w[r];
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int i = i0 + r;
+                if (i < np && i != L0 && i != L1 && i != L2) b[r] = w[r];
+            }
+        }
+    }
 }
 
 // Improved discrete four-leader step (paper Sec. 3.1.2, as read here: the
