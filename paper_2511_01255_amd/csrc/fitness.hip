@@ -250,8 +250,14 @@ FitPlan plan_fitness_table(const Design &d, qpm_prec p, int gw, int wpw)
 // wave) from the work, in waves' words: 64-genome groups x words. Small work
 // takes small workgroups (a wave walks its words one after the other, and
 // few large ones leave CUs idle); large work takes large ones, which stage
-// each table for more genomes. Kernel + combine, us, shape / shape:
-//   FP32  N = 1000, NP = 256 (128): 1/2 6.3, 2/4 7.2
+// each table for more genomes. In FP32 a wave's words go with the fold that
+// follows: short walks until the kernel fills the chip (work 5000), but 4 words
+// where 2 would leave 31 to 47 segments, the longest ranges of the fold
+// (combine_ranges). Kernel + combine, us, shape / shape:
+//   FP32  N = 1000, NP = 256 (128): 1/2 6.3, 2/4 7.2;  2000, 500 (504): 1/2 6.7, 1/4 7.8
+//         1000, 1000 (512): 1/2 6.6, 1/4 7.8;  3000, 1000 (1504): 1/2 7.4, 1/4 8.3
+//         2 x 10^4, 300 (3125): 1/2 10.0, 1/4 11.6;  12000, 200 (1500): 1/2 10.2, 1/4 9.5
+//         25000, 600 (7820): 1/2 12.2, 1/4 12.1;  5 x 10^4, 256 (6252): 1/2 13.6, 1/4 11.9
 //         10^4, 1024 (5008): 1/4 9.4, 4/4 11.8;  3000, 5000 (7426): 1/4 9.6, 4/4 10.8
 //         6600, 5000 (16353): 4/5 13.0, 4/4 16.4, 1/4 16.3
 //         10^4, 4096 (20032): 4/5 14.9, 4/4 17.1;  5 x 10^4, 1001 (25008): 4/5 19.3, 2/4 20.9
@@ -263,7 +269,7 @@ static void table_shape(bool f32, int64_t np, int64_t words, int *gw, int *wpw)
     if (f32) {
         const bool large = work > 12000;
         *gw = large ? (groups >= 16 ? 4 : (groups >= 8 ? 2 : 1)) : 1;
-        *wpw = large ? 5 : (work > 256 ? 4 : 2);
+        *wpw = large ? 5 : (work > 5000 || (words > 240 && words < 384) ? 4 : 2);
     } else {
         *gw = work > 6000 && groups >= 2 ? 2 : 1;
         *wpw = 2;
