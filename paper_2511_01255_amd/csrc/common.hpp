@@ -126,6 +126,8 @@ struct FitPlan {
 };
 
 FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel);
+// the plan of a run's evaluations, whose fold is the finish step's
+FitPlan plan_fitness_run(const Design &d, qpm_prec p, int64_t np, int kernel);
 size_t fitness_workspace_bytes(const FitPlan &plan, int64_t ld);
 qpm_status launch_fitness(const Design &d, qpm_prec p, const uint32_t *bits, int64_t np, int64_t ld,
                           void *fitness, const FitPlan &plan, double *workspace, hipStream_t s);

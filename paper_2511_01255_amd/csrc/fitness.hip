@@ -307,6 +307,21 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
     return pl;
 }
 
+// The finish step folds 64 genomes per workgroup (its selection needs them), so
+// 16 ranges of many segments keep one CU's loads busy: an FP32 table plan takes
+// more words per wave where that leaves fewer than 48 segments. Kernel + finish,
+// us, at 12472 x 86: 2 words (49 segments) 4.0 + 6.9, 4 words 5.2 + 3.7.
+FitPlan plan_fitness_run(const Design &d, qpm_prec p, int64_t np, int kernel)
+{
+    const FitPlan pl = plan_fitness(d, p, np, kernel);
+    if (pl.kind != QPM_FIT_TABLE) return pl;
+    for (int wpw = pl.wpw; wpw <= table_max_wpw(p == QPM_PREC_F32); ++wpw) {
+        const FitPlan q = plan_fitness_table(d, p, pl.waves, wpw);
+        if (combine_ranges(q.gy) != kMaxRanges) return q;
+    }
+    return pl;
+}
+
 FitPlan plan_fitness_shape(const Design &d, int waves, int wpw)
 {
     FitPlan pl;

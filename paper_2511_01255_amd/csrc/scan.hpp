@@ -51,6 +51,7 @@ __device__ __forceinline__ void tri_append(Tri &t, const Tri &u)
 // after the other: N = 5 x 10^4 (196 segments) took 18-19 us in 4 ranges for
 // 256 or 1001 genomes, longer than the evaluation itself, and takes 6.6-7 us
 // in 16 ranges with 8 segments (48 loads) in flight; 98 segments 10.7 and 5 us,
+// 49 segments in the finish step of a run 9.3 with 8 in flight and 6.9 us with 4,
 // 40 segments 4.0-5.9 and 4.8 us, 20 segments 3.8 and 4.7 us (the longer
 // fold of the ranges and more code), so 4 ranges stay below 48 segments.
 constexpr int kMaxRanges = 16;
@@ -99,6 +100,8 @@ __device__ __forceinline__ Tri combine_segments(const double *__restrict__ part,
             }
         } else if (gy <= 2 * NR) {
             fold_segments<2>(t, part, ld, i, s0, s1);
+        } else if (gy <= 4 * NR) {
+            fold_segments<4>(t, part, ld, i, s0, s1);
         } else {
             fold_segments<8>(t, part, ld, i, s0, s1);
         }

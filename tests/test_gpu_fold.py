@@ -64,3 +64,16 @@ def test_batch_fold_equals_single(q, ns, npop, prec):
         D = q.precompute_phases(z, inputs.DK1, inputs.DK2)
         g = q.eval_fitness(D, bits[k], npop, 1, kernel=q.FIT_SEGMENTED).cpu().numpy()
         assert np.max(np.abs(f[k] - g) / np.maximum(g, 1e-2 * np.median(g))) <= 2 * TOL[prec]
+
+
+# runs around 48 segments at two words per wave, and past 48 at the most words
+@pytest.mark.parametrize("n,npop,prec", [(12256, 70, 0), (12257, 70, 0), (12257, 70, 1), (24544, 66, 1), (24600, 66, 1),
+                                         (30720, 20, 0), (30721, 20, 0)])
+def test_run_fitness_of_long_designs(q, orc, n, npop, prec):
+    z = inputs.uniform_boundaries(n, 2.0)
+    R = q.Run(q.precompute_phases(z, inputs.DK1, inputs.DK2), npop, 2, seed=6, prec=prec, fused=-1)
+    R.advance(2)
+    x, f, _, _ = R.read()
+    R.destroy()
+    _, fo = orc.Design(z, inputs.DK1, inputs.DK2).fitness(orc.sign_map(x.cpu().numpy()))
+    assert np.max(np.abs(f.double().cpu().numpy() - fo) / fo) <= (1e-12 if prec == 1 else 1e-5)
