@@ -48,31 +48,42 @@ __global__ __launch_bounds__(64 * NR) void finish_kernel(const double *__restric
     }
 }
 
-// Sum, maximum and minimum over the 1024 threads of the workgroup in a
-// fixed order (butterfly within each wave, then the 16 wave results in
-// order by every thread), so the result does not depend on timing.
+// v + the value of the lane a DPP control names (0 where there is none, or where
+// the row mask leaves the row out)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double add_lane(double v)
+{
+    return v + __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false),
+                                __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false));
+}
+
+// Sum, maximum and minimum over the 1024 threads of the workgroup in a fixed
+// order (by DPP within each wave, then over the 16 wave results in every wave),
+// so the result does not depend on timing.
 __device__ __forceinline__ void block_sum_max_min(double &s, double &mx, double &mn, double *sh)
 {
-    for (int o = 1; o < 64; o <<= 1) {
-        s += __shfl_xor(s, o);
-        mx = fmax(mx, __shfl_xor(mx, o));
-        mn = fmin(mn, __shfl_xor(mn, o));
-    }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
+    auto mxop = [](double a, double b) { return fmax(a, b); };
+    auto mnop = [](double a, double b) { return fmin(a, b); };
+    auto sum16 = [](double v) {  // of each 16-lane row, in its last lane
+        v = add_lane<0x111, 0xF>(v);
+        v = add_lane<0x112, 0xF>(v);
+        v = add_lane<0x114, 0xF>(v);
+        return add_lane<0x118, 0xF>(v);
+    };
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    s = add_lane<0x143, 0xC>(add_lane<0x142, 0xA>(sum16(s)));  // the wave's, in lane 63
+    mx = wave_reduce(mx, mxop);
+    mn = wave_reduce(mn, mnop);
+    if (lane == 63) {
         sh[3 * w] = s;
         sh[3 * w + 1] = mx;
         sh[3 * w + 2] = mn;
     }
     __syncthreads();
-    s = sh[0];
-    mx = sh[1];
-    mn = sh[2];
-    for (int k = 1; k < 16; ++k) {
-        s += sh[3 * k];
-        mx = fmax(mx, sh[3 * k + 1]);
-        mn = fmin(mn, sh[3 * k + 2]);
-    }
+    const int k = 3 * (lane & 15);
+    s = lane63(sum16(sh[k]));
+    mx = wave_reduce(sh[k + 1], mxop);
+    mn = wave_reduce(sh[k + 2], mnop);
     __syncthreads();
 }
 
