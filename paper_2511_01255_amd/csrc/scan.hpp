@@ -189,26 +189,34 @@ __device__ __forceinline__ void scan_word_f32(Tri &t, uint32_t word, const doubl
 template <int R>
 __device__ __forceinline__ void word_tab_q(Tri &t, uint32_t word, const int2 *__restrict__ tb, double sc)
 {
-    const uint32_t p0 = word & 15u;
-    const int2 A0 = tb[p0];
+    // the blocks' pattern offsets (8 bytes each) as the bytes of two words: two
+    // instructions for four blocks, and each byte is taken by the add of the
+    // table's address (5 SHG designs 3000 x 5000, where this is a third of the
+    // walk: 14.4 -> 13.5 us; the full triple's walk does not change)
+    uint32_t even = (word << 3) & 0x78787878u, odd = (word >> 1) & 0x78787878u;
+    asm("" : "+v"(even), "+v"(odd));  // (or the compiler extracts each from the word again)
+    auto entry = [&](int h, int row) -> int2 {
+        const uint32_t off = (((h & 1) != 0 ? odd : even) >> (8 * (h >> 1))) & 0xFFu;
+        return *reinterpret_cast<const int2 *>(reinterpret_cast<const char *>(tb) + off + (h * R + row) * 128);
+    };
+    const int2 A0 = entry(0, 0);
     int ar = A0.x, ai = A0.y;
     if constexpr (R == 1) {
 #pragma unroll
         for (int h = 1; h < 8; ++h) {
-            const int2 A = tb[h * 16 + ((word >> (4 * h)) & 15u)];
+            const int2 A = entry(h, 0);
             ar += A.x;
             ai += A.y;
         }
         t.ar += static_cast<double>(ar) * sc;
         t.ai += static_cast<double>(ai) * sc;
     } else {
-        const int2 B0 = tb[16 + p0], Q0 = tb[32 + p0];
+        const int2 B0 = entry(0, 1), Q0 = entry(0, 2);
         int br = B0.x, bi = B0.y;
         float qr = __int_as_float(Q0.x), qi = __int_as_float(Q0.y);
 #pragma unroll
         for (int h = 1; h < 8; ++h) {
-            const uint32_t pt = (word >> (4 * h)) & 15u;
-            const int2 A = tb[h * R * 16 + pt], B = tb[(h * R + 1) * 16 + pt], Q = tb[(h * R + 2) * 16 + pt];
+            const int2 A = entry(h, 0), B = entry(h, 1), Q = entry(h, 2);
             const float fr = static_cast<float>(ar), fi = static_cast<float>(ai);
             const float bx = static_cast<float>(B.x), by = static_cast<float>(B.y);
             qr = fmaf(-fi, by, fmaf(fr, bx, qr + __int_as_float(Q.x)));
