@@ -110,7 +110,7 @@ __global__ __launch_bounds__(WAVES * 64) void batch_fit_kernel(const uint32_t *_
 
 // The table kernel over (instance, segment) tiles: the sign-pattern tables
 // and bit rows of instance b start at its word row wofs_b.
-template <bool F32, int GW>
+template <bool F32, int GW, bool STAGED>
 __global__ __launch_bounds__(GW * 256) void batch_fit_tab_kernel(const uint32_t *__restrict__ bits, int64_t ld,
                                                                  const double2 *__restrict__ tab64,
                                                                  const int2 *__restrict__ tabq,
@@ -127,9 +127,15 @@ __global__ __launch_bounds__(GW * 256) void batch_fit_tab_kernel(const uint32_t 
     const InstDesc id = inst[fs.inst];
     const int64_t i = (static_cast<int64_t>(blockIdx.x) * GW + (threadIdx.x >> 8)) * 64 + (threadIdx.x & 63);
     Tri t;
-    if (!tab_segment<F32, GW>(t, bits + id.wofs * ld, ld, static_cast<int>(id.words), fs.w0,
-                              tab64 + id.wofs * 8 * 48, tabq + id.wofs * 8 * 48, wsc + id.wofs, wpw, np, lds))
-        return;
+    const int W = static_cast<int>(id.words);
+    const double2 *t64 = tab64 + id.wofs * 8 * 48;
+    const int2 *tq = tabq + id.wofs * 8 * 48;
+    if constexpr (STAGED) {
+        if (!tab_segment_staged<F32, GW>(t, bits + id.wofs * ld, ld, W, fs.w0, t64, tq, wsc + id.wofs, wpw, np, lds))
+            return;
+    } else {
+        if (!tab_segment<F32, GW>(t, bits + id.wofs * ld, ld, W, fs.w0, t64, tq, wsc + id.wofs, wpw, np, lds)) return;
+    }
     double *o = part + static_cast<int64_t>(fs.slot) * 6 * ld + i;
     o[0] = t.ar;
     o[ld] = t.ai;
@@ -491,18 +497,21 @@ static BatchFitPlan make_tab_plan(const std::vector<InstDesc> &h, int gw, int wp
 
 // Launch shape of the batched table kernel from the work, in waves' words (64-
 // genome groups x words of all instances): as for single designs, small work
-// takes small workgroups. Kernel + combine, us, shape / shape:
+// takes small workgroups, large work long staged segments. Kernel + combine, us,
+// shape / shape:
 //   FP32  16 designs of 72 words, NP = 100 (1920): 1/2 8.6, 1/4 9.9
 //         10 designs, NP = 400 (3122): 1/2 8.9, 4/4 12.0
-//         32 designs, NP = 256 (94204): 4/5 39.8, 4/4 40.0;  64 (188920): 4/5 66.4, 4/4 69.1
-//   FP64  10 designs, NP = 400: 2/2 9.4, 4/2 10.1;  64, NP = 256: 4/2 108, 2/2 121
+//         64 designs, NP = 256 (188920): 4/8 62.8, 4/5 72.7;  32 (94204): 4/8 36.6, 4/5 41.9
+//         39, NP = 125 (51122): 2/8 30.8, 2/5 32.0;  16, NP = 505 (46864): 4/8 26.9, 4/5 29.1
+//   FP64  10 designs, NP = 400: 2/2 9.4, 4/2 10.1;  64, NP = 256: 4/12 71.4, 4/8 76.9, 4/2 94.7
+//         32: 4/12 37.2, 4/2 50.2;  39, NP = 125: 2/6 35.7, 2/2 39.9;  16, NP = 505: 4/12 25.0, 4/2 30.3
 static void default_tab_shape(int64_t np, int64_t words, bool f32, int *gw, int *wpw)
 {
     const int64_t groups = (np + 63) / 64;
     const bool large = groups * words > 12000;
     const int most = large ? 4 : (f32 ? 1 : 2);
     *gw = groups >= 4 ? most : (groups >= 2 ? std::min(most, 2) : 1);
-    *wpw = f32 ? (large ? 5 : 2) : 2;
+    *wpw = !large ? 2 : (f32 ? 8 : (*gw == 4 ? 12 : 6));
 }
 
 static void default_fit_shape(const std::vector<InstDesc> &h, int64_t np, int *waves, int *wpw)
@@ -696,15 +705,23 @@ static qpm_status launch_batch_fit(const qpm_batch_s &bt, qpm_prec p, const uint
         const dim3 grid(static_cast<unsigned>((np + 64 * pl.gw - 1) / (64 * pl.gw)),
                         static_cast<unsigned>(nsegs));
         const size_t lds = table_lds_bytes(4 * pl.wpw, p == QPM_PREC_F32, pl.gw, pl.wpw);
+        const bool staged = pl.wpw > table_max_wpw(p == QPM_PREC_F32);
+#define QPM_BT_KERNEL(F, G, ST)                                                                                    \
+    batch_fit_tab_kernel<F, G, ST><<<grid, G * 256, lds, s>>>(bits, ld, bt.tab64, bt.tabq, bt.wsc, pl.wpw, np, bt.dev, \
+                                                              segs_dev, part, advance)
 #define QPM_BT_CASE(G)                                                                                             \
     case G:                                                                                                        \
-        if (p == QPM_PREC_F32)                                                                                     \
-            batch_fit_tab_kernel<true, G><<<grid, G * 256, lds, s>>>(bits, ld, bt.tab64, bt.tabq, bt.wsc, pl.wpw, np,   \
-                                                                     bt.dev,                                      \
-                                                                    segs_dev, part, advance);                      \
-        else                                                                                                       \
-            batch_fit_tab_kernel<false, G><<<grid, G * 256, lds, s>>>(bits, ld, bt.tab64, bt.tabq, bt.wsc, pl.wpw, np, \
-                                                                     bt.dev, segs_dev, part, advance);             \
+        if (p == QPM_PREC_F32) {                                                                                   \
+            if (staged)                                                                                            \
+                QPM_BT_KERNEL(true, G, true);                                                                      \
+            else                                                                                                   \
+                QPM_BT_KERNEL(true, G, false);                                                                     \
+        } else {                                                                                                   \
+            if (staged)                                                                                            \
+                QPM_BT_KERNEL(false, G, true);                                                                     \
+            else                                                                                                   \
+                QPM_BT_KERNEL(false, G, false);                                                                    \
+        }                                                                                                          \
         break;
         switch (pl.gw) {
             QPM_BT_CASE(1)
@@ -713,6 +730,7 @@ static qpm_status launch_batch_fit(const qpm_batch_s &bt, qpm_prec p, const uint
         default: QPM_REQUIRE(false, QPM_EINVAL, "unsupported genome groups per workgroup %d", pl.gw);
         }
 #undef QPM_BT_CASE
+#undef QPM_BT_KERNEL
         QPM_TRY_HIP(hipGetLastError());
         return QPM_OK;
     }
@@ -1140,7 +1158,7 @@ static qpm_status tune_fitness(qpm_batch_run_s *r)
     const std::string key = tune_key("batchtab", r->bt->total_words, c.np, c.prec, r->bt->n_inst);
     {
         int v0, v1;
-        const int maxw = table_max_wpw(p == QPM_PREC_F32);
+        const int maxw = kTabPlanWords;
         if (tune_lookup(key, &v0, &v1, [&](int g, int w) { return (g == 1 || g == 2 || g == 4) && w >= 1 && w <= maxw; })) {
             r->fplan = make_tab_plan(r->bt->host, v0, v1);
             return QPM_OK;
@@ -1149,6 +1167,8 @@ static qpm_status tune_fitness(qpm_batch_run_s *r)
     std::vector<std::pair<int, int>> cands;
     for (int g : {1, 2, 4})
         for (int w = 1; w <= table_max_wpw(p == QPM_PREC_F32); ++w) cands.push_back({g, w});
+    for (int g : {2, 4})
+        for (int w : {6, 8, 12}) cands.push_back({g, w});
     hipEvent_t e0, e1;
     QPM_TRY_HIP(hipEventCreate(&e0));
     QPM_TRY_HIP(hipEventCreate(&e1));

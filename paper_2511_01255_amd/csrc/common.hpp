@@ -288,6 +288,9 @@ FitPlan plan_fitness_shape(const Design &d, int waves, int wpw);
 // (1 <= wpw <= table_max_wpw: 4 wpw words of tables fit in 64 KB of LDS)
 FitPlan plan_fitness_table(const Design &d, qpm_prec p, int gw, int wpw);
 __host__ __device__ constexpr int table_max_wpw(bool f32) { return f32 ? 5 : 2; }
+// longer segments are walked in stages (tab_segment_staged); the most words per
+// wave that a plan takes
+constexpr int kTabPlanWords = 16;
 // LDS of one table-kernel workgroup (tables, reused for the combine)
 size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw);
 // DE draws of generation *gen_dev for every individual

@@ -146,7 +146,8 @@ __global__ __launch_bounds__(128) void fit_per_genome_kernel(const uint32_t *__r
 // order. FP32: the word's A and B summed exactly in fixed point, its Q in
 // binary32, each word's triple folded into FP64 (word_tab_q); FP64:
 // binary64 throughout.
-template <bool F32, int GW>
+// STAGED: segments of more words than table_max_wpw (tab_segment_staged).
+template <bool F32, int GW, bool STAGED>
 __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__restrict__ bits, int64_t ld, int W,
                                                            const double2 *__restrict__ tab64,
                                                            const int2 *__restrict__ tabq,
@@ -162,7 +163,11 @@ __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__res
     const int wbase = static_cast<int>(blockIdx.y) * 4 * wpw;
     const int64_t i = (static_cast<int64_t>(blockIdx.x) * GW + (threadIdx.x >> 8)) * 64 + (threadIdx.x & 63);
     Tri t;
-    if (!tab_segment<F32, GW>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
+    if constexpr (STAGED) {
+        if (!tab_segment_staged<F32, GW>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
+    } else {
+        if (!tab_segment<F32, GW>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
+    }
     if (direct) {
         store_fitness(fit, out_f64, i, t, C);
     } else {
@@ -179,7 +184,8 @@ __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__res
 size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw)
 {
     const int64_t words = std::min<int64_t>(W, 4 * static_cast<int64_t>(wpw));
-    const size_t tab = static_cast<size_t>(words) * 8 * 48 * (f32 ? 8 : 16);
+    const size_t tab = wpw > table_max_wpw(f32) ? 2 * (f32 ? TabStage<true>::kBytes : TabStage<false>::kBytes)
+                                                : static_cast<size_t>(words) * 8 * 48 * (f32 ? 8 : 16);
     const size_t comb = static_cast<size_t>(gw) * 4 * 64 * 6 * 8;
     return std::max(tab, comb);
 }
@@ -194,11 +200,15 @@ static qpm_status launch_tab(const Design &d, const FitPlan &pl, const uint32_t 
     const int direct = direct_ok && pl.gy == 1;
     const int W = static_cast<int>(d.words);
     const size_t lds = table_lds_bytes(d.words, F32, gw, pl.wpw);
+#define QPM_TAB_KERNEL(G, ST)                                                                                 \
+    fit_tab_kernel<F32, G, ST><<<grid, dim3(G * 256), lds, s>>>(bits, ld, W, d.tab64, d.tabq, d.wsc, pl.wpw, np,  \
+                                                                part, d.Cdev, fit, direct, out_f64, advance)
 #define QPM_TAB_CASE(G)                                                                                       \
     case G:                                                                                                   \
-        fit_tab_kernel<F32, G><<<grid, dim3(G * 256), lds, s>>>(bits, ld, W, d.tab64, d.tabq, d.wsc, pl.wpw, np,  \
-                                                                part,                                         \
-                                                                d.Cdev, fit, direct, out_f64, advance);      \
+        if (pl.wpw > table_max_wpw(F32))                                                                      \
+            QPM_TAB_KERNEL(G, true);                                                                          \
+        else                                                                                                  \
+            QPM_TAB_KERNEL(G, false);                                                                         \
         break;
     switch (gw) {
         QPM_TAB_CASE(1)
@@ -207,6 +217,7 @@ static qpm_status launch_tab(const Design &d, const FitPlan &pl, const uint32_t 
     default: QPM_REQUIRE(false, QPM_EINVAL, "unsupported genome groups per workgroup %d", gw);
     }
 #undef QPM_TAB_CASE
+#undef QPM_TAB_KERNEL
     return QPM_OK;
 }
 
@@ -260,20 +271,27 @@ FitPlan plan_fitness_table(const Design &d, qpm_prec p, int gw, int wpw)
 //         25000, 600 (7820): 1/2 12.2, 1/4 12.1;  5 x 10^4, 256 (6252): 1/2 13.6, 1/4 11.9
 //         10^4, 1024 (5008): 1/4 9.4, 4/4 11.8;  3000, 5000 (7426): 1/4 9.6, 4/4 10.8
 //         6600, 5000 (16353): 4/5 13.0, 4/4 16.4, 1/4 16.3
-//         10^4, 4096 (20032): 4/5 14.9, 4/4 17.1;  5 x 10^4, 1001 (25008): 4/5 19.3, 2/4 20.9
-//   FP64  10^4, 1024: 1/2 10.4, 4/2 12.3;  5 x 10^4, 256 (6252): 2/2 13.6, 1/2 16.6
-//         3000, 5000: 2/2 10.3, 1/2 11.7;  10^4, 4096: 2/2 19.4, 4/2 20.5
+//         10^4, 4096 (20032): 4/5 14.2, 4/8 16.8;  5 x 10^4, 1001 (25008): 4/8 17.7, 4/5 19.3, 4/6 20.7
+//   FP64  10^4, 1024: 1/2 9.9, 2/3 11.0;  5 x 10^4, 256 (6252): 2/4 12.2, 2/2 13.6
+//         3000, 5000: 2/4 10.0, 2/2 10.3;  10^4, 4096: 4/6 15.5, 4/4 17.9, 2/2 18.8
+//         5 x 10^4, 1001: 4/8 17.7, 4/4 18.6, 4/6 21.3, 2/2 24.9
 static void table_shape(bool f32, int64_t np, int64_t words, int *gw, int *wpw)
 {
     const int64_t groups = (np + 63) / 64, work = groups * words;
+    const bool large = work > 12000;
     if (f32) {
-        const bool large = work > 12000;
         *gw = large ? (groups >= 16 ? 4 : (groups >= 8 ? 2 : 1)) : 1;
         *wpw = large ? 5 : (work > 5000 || (words > 240 && words < 384) ? 4 : 2);
     } else {
-        *gw = work > 6000 && groups >= 2 ? 2 : 1;
-        *wpw = 2;
+        *gw = large && groups >= 4 ? 4 : (work > 6000 && groups >= 2 ? 2 : 1);
+        *wpw = large ? 3 : (work > 6000 && groups >= 2 ? 4 : 2);
     }
+    if (!large) return;
+    // the fewest words (two at a time in FP32) that leave one workgroup per CU,
+    // at most 8
+    auto blocks = [&](int w) { return (groups + *gw - 1) / *gw * ((words + 4 * w - 1) / (4 * w)); };
+    while (*wpw < 8 && blocks(*wpw) > 256) ++*wpw;
+    if (f32 && *wpw == 7) *wpw = 8;
 }
 
 FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
@@ -308,14 +326,15 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
 }
 
 // The finish step folds 64 genomes per workgroup (its selection needs them), so
-// 16 ranges of many segments keep one CU's loads busy: an FP32 table plan takes
+// 16 ranges of many segments keep one CU's loads busy: a table plan takes
 // more words per wave where that leaves fewer than 48 segments. Kernel + finish,
 // us, at 12472 x 86: 2 words (49 segments) 4.0 + 6.9, 4 words 5.2 + 3.7.
+constexpr int kRunWords = 5;
 FitPlan plan_fitness_run(const Design &d, qpm_prec p, int64_t np, int kernel)
 {
     const FitPlan pl = plan_fitness(d, p, np, kernel);
     if (pl.kind != QPM_FIT_TABLE) return pl;
-    for (int wpw = pl.wpw; wpw <= table_max_wpw(p == QPM_PREC_F32); ++wpw) {
+    for (int wpw = pl.wpw; wpw <= std::max(pl.wpw, kRunWords); ++wpw) {
         const FitPlan q = plan_fitness_table(d, p, pl.waves, wpw);
         if (combine_ranges(q.gy) != kMaxRanges) return q;
     }

@@ -400,13 +400,13 @@ static qpm_status tune_run(qpm_run_s *r)
         const std::string key = tune_key("tab", r->d->words, c.np, c.prec, 1);
         int gw = 0, wpw = 0;
         const auto tab_ok = [&](int g, int w) {
-            return (g == 1 || g == 2 || g == 4) && w >= 1 && w <= table_max_wpw(p == QPM_PREC_F32) &&
+            return (g == 1 || g == 2 || g == 4) && w >= 1 && w <= kTabPlanWords &&
                    plan_fitness_table(*r->d, p, g, w).gy <= 65535;
         };
         if (!tune_lookup(key, &gw, &wpw, tab_ok)) {
             std::vector<FitPlan> cands;
             for (int g : {1, 2, 4})
-                for (int w = 1; w <= table_max_wpw(p == QPM_PREC_F32); ++w) {
+                for (int w : {1, 2, 3, 4, 5, 6, 8}) {
                     FitPlan pl = plan_fitness_table(*r->d, p, g, w);
                     if (pl.gy <= 65535) cands.push_back(pl);
                 }

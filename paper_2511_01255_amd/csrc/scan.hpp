@@ -232,6 +232,36 @@ __device__ __forceinline__ void word_tab_q(Tri &t, uint32_t word, const int2 *__
     }
 }
 
+// The 4 segment triples of each genome group of a table workgroup, in order,
+// through LDS (the tables are no longer read): the workgroup's triple in t, and
+// true, in the first segment wave of each group for live genomes.
+template <int GW>
+__device__ __forceinline__ bool fold_segment_waves(Tri &t, int wpw, int nw, int gsub, int ssub, int wave, int lane,
+                                                   bool live, unsigned char *lds)
+{
+    constexpr int SW = 4;
+    __syncthreads();
+    double *sh = reinterpret_cast<double *>(lds);  // [6][GW * SW][64]
+    constexpr int NWV = GW * SW;
+    sh[(0 * NWV + wave) * 64 + lane] = t.ar;
+    sh[(1 * NWV + wave) * 64 + lane] = t.ai;
+    sh[(2 * NWV + wave) * 64 + lane] = t.br;
+    sh[(3 * NWV + wave) * 64 + lane] = t.bi;
+    sh[(4 * NWV + wave) * 64 + lane] = t.qr;
+    sh[(5 * NWV + wave) * 64 + lane] = t.qi;
+    __syncthreads();
+    if (ssub != 0 || !live) return false;
+#pragma unroll 1
+    for (int s2 = 1; s2 < SW; ++s2) {
+        if (s2 * wpw >= nw) break;
+        const int v = gsub * SW + s2;
+        tri_append(t, Tri{sh[(0 * NWV + v) * 64 + lane], sh[(1 * NWV + v) * 64 + lane], sh[(2 * NWV + v) * 64 + lane],
+                          sh[(3 * NWV + v) * 64 + lane], sh[(4 * NWV + v) * 64 + lane],
+                          sh[(5 * NWV + v) * 64 + lane]});
+    }
+    return true;
+}
+
 // One workgroup of the table kernels (GW genome groups of 64 x 4 segment
 // waves, lane = genome) over the words [wbase, wbase + 4 wpw) of a design
 // of W words: `bits` and the tables point at the design's word 0; the
@@ -308,28 +338,107 @@ __device__ __forceinline__ bool tab_segment(Tri &t, const uint32_t *__restrict__
             }
         }
     }
-    // the 4 segment triples of each genome group, in order, through LDS
-    // (the tables are no longer read)
-    __syncthreads();
-    double *sh = reinterpret_cast<double *>(lds);  // [6][GW * SW][64]
-    constexpr int NWV = GW * SW;
-    sh[(0 * NWV + wave) * 64 + lane] = t.ar;
-    sh[(1 * NWV + wave) * 64 + lane] = t.ai;
-    sh[(2 * NWV + wave) * 64 + lane] = t.br;
-    sh[(3 * NWV + wave) * 64 + lane] = t.bi;
-    sh[(4 * NWV + wave) * 64 + lane] = t.qr;
-    sh[(5 * NWV + wave) * 64 + lane] = t.qi;
-    __syncthreads();
-    if (ssub != 0 || !live) return false;
+    return fold_segment_waves<GW>(t, wpw, nw, gsub, ssub, wave, lane, live, lds);
+}
+
+// Words per wave of one stage of the table kernels, and the bytes of a stage's
+// tables (4 waves' words: 8 blocks x 48 entries each)
+template <bool F32>
+struct TabStage {
+    static constexpr int kWords = F32 ? 2 : 1;
+    static constexpr int kWordBytes = 8 * 48 * (F32 ? 8 : 16);
+    static constexpr int kBytes = 4 * kWords * kWordBytes;
+};
+
+// tab_segment for longer segments than LDS holds the tables of (wpw >
+// table_max_wpw): each wave walks its words in stages of kWords, and the tables
+// of the next stage's words (and the wave's bit words) arrive in the other half
+// of `lds` while one is walked, so only the first stage waits for memory and a
+// workgroup leaves fewer segments to fold. Kernel + fold, us, against one stage:
+// 49999 x 1001 FP64 18.1 + 6.8 -> 13.6 + 4.1, FP32 14.5 + 4.8 -> 13.4 + 4.3; 64
+// designs of up to 5 x 10^4 domains, NP = 256, FP32 63.6 + 9.1 -> 56.2 + 6.6, FP64
+// 76 + 19 -> 66 + 6. Short segments gain nothing and pay for the stages (2000 x
+// 500 FP32: 4.1 -> 4.5).
+template <bool F32, int GW>
+__device__ __forceinline__ bool tab_segment_staged(Tri &t, const uint32_t *__restrict__ bits, int64_t ld, int W, int wbase,
+                                            const double2 *__restrict__ tab64, const int2 *__restrict__ tabq,
+                                            const double *__restrict__ wsc, int wpw, int64_t np, unsigned char *lds)
+{
+    constexpr int SW = 4;
+    constexpr int NT = GW * 256;
+    using Stage = TabStage<F32>;
+    constexpr int WS = Stage::kWords;
+    constexpr int PIECE = WS * Stage::kWordBytes / 16;  // 16-byte units of one wave's words
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int gsub = wave / SW, ssub = wave % SW;
+    const int64_t i = (static_cast<int64_t>(blockIdx.x) * GW + gsub) * 64 + lane;
+    const int nw = min(W - wbase, SW * wpw);  // >= 1 by the grid
+    const uint4 *const tabs =
+        F32 ? reinterpret_cast<const uint4 *>(tabq) : reinterpret_cast<const uint4 *>(tab64);
+    const bool live = i < np;
+    const int w0 = ssub * wpw, w1 = min(nw, w0 + wpw);
+    const int64_t ic = i < ld ? i : ld - 1;
+    uint32_t next[WS];
+    // stage k: words s wpw + k WS .. of every segment s, straight to LDS (16
+    // bytes per lane per load, no registers, no wait between loads)
+    auto issue = [&](int k) {
+        unsigned char *const to = lds + (k & 1) * Stage::kBytes;
+#pragma unroll
+        for (int u = 0; u < (SW * PIECE + NT - 1) / NT; ++u) {
+            const int idx = u * NT + static_cast<int>(threadIdx.x);
+            const int s = idx / PIECE, in = idx % PIECE;
+            const int w = s * wpw + k * WS + in / (PIECE / WS);  // the unit's word
+            if (idx < SW * PIECE && w < min(nw, (s + 1) * wpw))
+                __builtin_amdgcn_global_load_lds(
+                    tabs + (static_cast<int64_t>(wbase + s * wpw + k * WS) * (PIECE / WS) + in),
+                    reinterpret_cast<__attribute__((address_space(3))) void *>(
+                        reinterpret_cast<uintptr_t>(to + static_cast<size_t>(u * NT + wave * 64) * 16)),
+                    16, 0, 0);
+        }
+        // this wave's bit words (clamped addresses, so every load is in
+        // bounds and none is branched around)
+#pragma unroll
+        for (int j = 0; j < WS; ++j) next[j] = bits[static_cast<int64_t>(min(wbase + w0 + k * WS + j, W - 1)) * ld + ic];
+    };
+    issue(0);
+    t = Tri{0, 0, 0, 0, 0, 0};
+    const int stages = (min(wpw, nw) + WS - 1) / WS;  // the same in every wave
 #pragma unroll 1
-    for (int s2 = 1; s2 < SW; ++s2) {
-        if (s2 * wpw >= nw) break;
-        const int v = gsub * SW + s2;
-        tri_append(t, Tri{sh[(0 * NWV + v) * 64 + lane], sh[(1 * NWV + v) * 64 + lane], sh[(2 * NWV + v) * 64 + lane],
-                          sh[(3 * NWV + v) * 64 + lane], sh[(4 * NWV + v) * 64 + lane],
-                          sh[(5 * NWV + v) * 64 + lane]});
+    for (int k = 0; k < stages; ++k) {
+        // this stage's loads have arrived in every wave, and every wave is
+        // done with the half the next ones go to
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        uint32_t wv[WS];
+#pragma unroll
+        for (int j = 0; j < WS; ++j) wv[j] = live ? next[j] : 0u;
+        if (k + 1 < stages) issue(k + 1);
+        const unsigned char *const from = lds + (k & 1) * Stage::kBytes + ssub * (PIECE * 16);
+#pragma unroll
+        for (int j = 0; j < WS; ++j) {
+            const int wr = w0 + k * WS + j;
+            if (wr >= w1) break;
+            const uint32_t word = wv[j];
+            if constexpr (F32) {
+                word_tab_q<3>(t, word, reinterpret_cast<const int2 *>(from) + j * 8 * 48, wsc[wbase + wr]);
+            } else {
+                const double2 *tb = reinterpret_cast<const double2 *>(from) + j * 8 * 48;
+#pragma unroll
+                for (int h = 0; h < 8; ++h) {
+                    const uint32_t pt = (word >> (4 * h)) & 15u;
+                    const double2 A = tb[h * 48 + pt], B = tb[h * 48 + 16 + pt], Q = tb[h * 48 + 32 + pt];
+                    t.qr = fma(-t.ai, B.y, fma(t.ar, B.x, t.qr + Q.x));
+                    t.qi = fma(t.ai, B.x, fma(t.ar, B.y, t.qi + Q.y));
+                    t.ar += A.x;
+                    t.ai += A.y;
+                    t.br += B.x;
+                    t.bi += B.y;
+                }
+            }
+        }
     }
-    return true;
+    return fold_segment_waves<GW>(t, wpw, nw, gsub, ssub, wave, lane, live, lds);
 }
 
 }  // namespace qpm

@@ -24,7 +24,8 @@ def q():
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("n,npop", [(8192, 64), (8193, 64), (24000, 1024), (24064, 1024), (48001, 511),
                                     (48001, 513),
-                                    (7680, 130), (7681, 130), (12256, 70), (12257, 70), (2970, 3400), (2970, 3500)])
+                                    (7680, 130), (7681, 130), (12256, 70), (12257, 70), (2970, 3400), (2970, 3500),
+                                    (50000, 1030), (49985, 1100), (31900, 390), (12257, 2200)])
 def test_default_shape_matches_oracle(q, orc, n, npop, prec):
     import torch
     z = inputs.jittered_boundaries(n, 2.0, 0.2, seed=n)
@@ -41,7 +42,8 @@ def test_default_shape_matches_oracle(q, orc, n, npop, prec):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
-@pytest.mark.parametrize("ns,npop", [([1000] * 7, 100), ([32000, 32000, 32000], 256), ([32000, 32000, 32033], 256)])
+@pytest.mark.parametrize("ns,npop", [([1000] * 7, 100), ([32000, 32000, 32000], 256), ([32000, 32000, 32033], 256),
+                                     ([40000, 9001, 33, 31000], 257), ([50000, 48001], 300), ([90000, 70001], 100)])
 def test_batch_default_shape_equals_single(q, ns, npop, prec):
     import torch
     zs = [inputs.jittered_boundaries(n, 2.0, 0.2, seed=k) for k, n in enumerate(ns)]
