@@ -294,6 +294,14 @@ static void table_shape(bool f32, int64_t np, int64_t words, int *gw, int *wpw)
     if (f32 && *wpw == 7) *wpw = 8;
 }
 
+// Designs of at most this many words: one workgroup walks them all and writes
+// the fitness itself, so that nothing is launched after it. us per call back to
+// back / with a wait after each, one launch against table_shape's two, both
+// precisions, NP = 64 to 5000:
+//   N =  640 (20 words): FP32 7.2 / 20.0 against 10.0 / 21.0, FP64 7.2 / 21.2 against 10.0 / 21.0
+//   N =  800 (25):       FP32 7.2 / 21.7 against 9.9 / 21.0,  FP64 8.1 / 22.7 against 9.9 / 21.0
+//   N = 1280 (40):       FP32 8.8 / 23.5 against 10.0 / 21.2, FP64 10.7 / 25.2 against 9.9 / 21.2
+constexpr int64_t kDirectWords = 20;
 FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
 {
     FitPlan pl;
@@ -305,6 +313,7 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
     if (kernel == QPM_FIT_AUTO || kernel == QPM_FIT_TABLE) {
         int gw, wpw;
         table_shape(p == QPM_PREC_F32, np, d.words, &gw, &wpw);
+        if (d.words <= kDirectWords) wpw = static_cast<int>((d.words + 3) / 4);
         return plan_fitness_table(d, p, gw, wpw);
     }
     pl.kind = QPM_FIT_SEGMENTED;
@@ -332,8 +341,11 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
 constexpr int kRunWords = 5;
 FitPlan plan_fitness_run(const Design &d, qpm_prec p, int64_t np, int kernel)
 {
-    const FitPlan pl = plan_fitness(d, p, np, kernel);
+    FitPlan pl = plan_fitness(d, p, np, kernel);
     if (pl.kind != QPM_FIT_TABLE) return pl;
+    // a run folds in its finish step whatever the number of segments
+    table_shape(p == QPM_PREC_F32, np, d.words, &pl.waves, &pl.wpw);
+    pl = plan_fitness_table(d, p, pl.waves, pl.wpw);
     for (int wpw = pl.wpw; wpw <= std::max(pl.wpw, kRunWords); ++wpw) {
         const FitPlan q = plan_fitness_table(d, p, pl.waves, wpw);
         if (combine_ranges(q.gy) != kMaxRanges) return q;

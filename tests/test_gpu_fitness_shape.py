@@ -25,7 +25,8 @@ def q():
 @pytest.mark.parametrize("n,npop", [(8192, 64), (8193, 64), (24000, 1024), (24064, 1024), (48001, 511),
                                     (48001, 513),
                                     (7680, 130), (7681, 130), (12256, 70), (12257, 70), (2970, 3400), (2970, 3500),
-                                    (50000, 1030), (49985, 1100), (31900, 390), (12257, 2200)])
+                                    (50000, 1030), (49985, 1100), (31900, 390), (12257, 2200),
+                                    (40, 70), (417, 65), (640, 300), (641, 300)])
 def test_default_shape_matches_oracle(q, orc, n, npop, prec):
     import torch
     z = inputs.jittered_boundaries(n, 2.0, 0.2, seed=n)
