@@ -33,12 +33,14 @@ struct ObjShape {
 
 constexpr int kSegWaves = 4;
 
+// LDS of the partials kernel: one design's tables, which the fold reuses; or
+// those of two designs and two folds
 template <bool F32, bool THG>
-size_t obj_lds_bytes(int wpw)
+size_t obj_lds_bytes(int wpw, bool twice)
 {
     const size_t tables = static_cast<size_t>(kSegWaves) * wpw * 8 * ObjShape<THG>::R * 16 * (F32 ? 8 : 16);
     const size_t fold = static_cast<size_t>(ObjShape<THG>::NC) * kSegWaves * 64 * sizeof(double);
-    return tables > fold ? tables : fold;
+    return twice ? 2 * (tables + fold) : (tables > fold ? tables : fold);
 }
 
 }  // namespace
@@ -46,7 +48,12 @@ size_t obj_lds_bytes(int wpw)
 // Grid: x = genome groups of 64, y = workgroup segments of 4 wpw words.
 // part[(k gy + y) NC + c][ld] + i: the segment's (A, B, Q) (THG) or A (SHG)
 // of design k for genome i, the 4 segment waves folded in order.
-template <bool F32, bool THG>
+// TWICE: the tables of design k + 1 arrive in the other half of LDS while
+// design k is walked, and its fold waits for the barrier that they need anyway
+// (one per design instead of four), by a wave that changes from design to design.
+// A workgroup's time is mostly these waits: 3000 x 5000, 5 SHG wavelengths FP32,
+// 11.0 -> 9.7 us (4 words per wave).
+template <bool F32, bool THG, bool TWICE>
 __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, const uint32_t *__restrict__ bits,
                                                            int64_t ld, int W, int wpw, int gy, int64_t np,
                                                            double *__restrict__ part, uint32_t *__restrict__ advance)
@@ -66,16 +73,14 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
     const bool live = i < np;
     const int w0 = wave * wpw, w1 = min(nw, w0 + wpw);
     const int64_t ic = i < ld ? i : ld - 1;
-    // the bit words of this wave's segment, loaded once for all K designs
-    uint32_t wv[MAXW];
-#pragma unroll
-    for (int k = 0; k < MAXW; ++k) wv[k] = bits[static_cast<int64_t>(min(wbase + w0 + k, W - 1)) * ld + ic];
     const int n16 = nw * 8 * R * PPR;
-    for (int kd = 0; kd < K; ++kd) {
-        // design kd's table rows of words [wbase, wbase + nw) into LDS:
-        // piece idx = ((word 8 + block) R + row) PPR + q
+    const int half = TWICE ? kSegWaves * wpw * 8 * R * 16 * ES : 0;  // bytes of one design's tables
+    // design kd's table rows of words [wbase, wbase + nw) into LDS:
+    // piece idx = ((word 8 + block) R + row) PPR + q
+    auto issue = [&](int kd) {
         const unsigned char *src = F32 ? reinterpret_cast<const unsigned char *>(tabs.tq[kd])
                                        : reinterpret_cast<const unsigned char *>(tabs.t64[kd]);
+        unsigned char *const to = lds + (kd & 1) * half;
         for (int r0 = 0; r0 * 256 < n16; ++r0) {
             const int idx = r0 * 256 + static_cast<int>(threadIdx.x);
             if (idx < n16) {
@@ -85,12 +90,45 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
                 __builtin_amdgcn_global_load_lds(
                     reinterpret_cast<const uint4 *>(src + off),
                     reinterpret_cast<__attribute__((address_space(3))) void *>(
-                        reinterpret_cast<uintptr_t>(lds + static_cast<size_t>(r0 * 256 + wave * 64) * 16)),
+                        reinterpret_cast<uintptr_t>(to + static_cast<size_t>(r0 * 256 + wave * 64) * 16)),
                     16, 0, 0);
             }
         }
+    };
+    // design kd's 4 segment waves in order, from LDS, by one wave
+    auto fold = [&](int kd, const double *sh) {  // sh: [NC][4][64]
+        if (!live) return;
+        auto at = [&](int c, int s2) { return c < NC ? sh[(c * kSegWaves + s2) * 64 + lane] : 0.0; };
+        Tri t{at(0, 0), at(1, 0), at(2, 0), at(3, 0), at(4, 0), at(5, 0)};
+        for (int s2 = 1; s2 < kSegWaves; ++s2) {
+            if (s2 * wpw >= nw) break;
+            if constexpr (THG) {
+                tri_append(t, Tri{at(0, s2), at(1, s2), at(2, s2), at(3, s2), at(4, s2), at(5, s2)});
+            } else {
+                t.ar += at(0, s2);
+                t.ai += at(1, s2);
+            }
+        }
+        double *p = part + ((static_cast<int64_t>(kd) * gy + blockIdx.y) * NC) * ld + i;
+        const double out[6] = {t.ar, t.ai, t.br, t.bi, t.qr, t.qi};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) p[c * ld] = out[c];
+    };
+    issue(0);
+    // the bit words of this wave's segment, loaded once for all K designs
+    uint32_t wv[MAXW];
+#pragma unroll
+    for (int k = 0; k < MAXW; ++k) wv[k] = bits[static_cast<int64_t>(min(wbase + w0 + k, W - 1)) * ld + ic];
+    for (int kd = 0; kd < K; ++kd) {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
+        double *const folds = reinterpret_cast<double *>(lds + 2 * half);
+        constexpr int kFold = NC * kSegWaves * 64;
+        if constexpr (TWICE) {
+            if (kd + 1 < K) issue(kd + 1);
+            if (kd > 0 && wave == (kd - 1) % kSegWaves) fold(kd - 1, folds + ((kd - 1) & 1) * kFold);
+        }
+        const unsigned char *const from = lds + (kd & 1) * half;
         Tri t{0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int k = 0; k < MAXW; ++k) {
@@ -98,10 +136,10 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
             if (wr >= w1) break;
             const uint32_t word = live ? wv[k] : 0u;
             if constexpr (F32) {
-                word_tab_q<R>(t, word, reinterpret_cast<const int2 *>(lds) + wr * 8 * R * 16,
+                word_tab_q<R>(t, word, reinterpret_cast<const int2 *>(from) + wr * 8 * R * 16,
                               tabs.wsc[kd][wbase + wr]);
             } else {
-                const double2 *tb = reinterpret_cast<const double2 *>(lds) + wr * 8 * R * 16;
+                const double2 *tb = reinterpret_cast<const double2 *>(from) + wr * 8 * R * 16;
 #pragma unroll
                 for (int h = 0; h < 8; ++h) {
                     const uint32_t pt = (word >> (4 * h)) & 15u;
@@ -118,31 +156,22 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
                 }
             }
         }
-        // fold the 4 segment waves in order through LDS (tables done)
-        __syncthreads();
-        double *sh = reinterpret_cast<double *>(lds);  // [NC][4][64]
+        if constexpr (!TWICE) __syncthreads();  // the fold takes the tables' place
+        double *sh = TWICE ? folds + (kd & 1) * kFold : reinterpret_cast<double *>(lds);
         const double comp[6] = {t.ar, t.ai, t.br, t.bi, t.qr, t.qi};
 #pragma unroll
         for (int c = 0; c < NC; ++c) sh[(c * kSegWaves + wave) * 64 + lane] = comp[c];
-        __syncthreads();
-        if (wave == 0 && live) {
-            for (int s2 = 1; s2 < kSegWaves; ++s2) {
-                if (s2 * wpw >= nw) break;
-                if constexpr (THG) {
-                    tri_append(t, Tri{sh[(0 * kSegWaves + s2) * 64 + lane], sh[(1 * kSegWaves + s2) * 64 + lane],
-                                      sh[(2 * kSegWaves + s2) * 64 + lane], sh[(3 * kSegWaves + s2) * 64 + lane],
-                                      sh[(4 * kSegWaves + s2) * 64 + lane], sh[(5 * kSegWaves + s2) * 64 + lane]});
-                } else {
-                    t.ar += sh[(0 * kSegWaves + s2) * 64 + lane];
-                    t.ai += sh[(1 * kSegWaves + s2) * 64 + lane];
-                }
+        if constexpr (!TWICE) {
+            __syncthreads();
+            if (wave == 0) fold(kd, sh);
+            if (kd + 1 < K) {
+                __syncthreads();
+                issue(kd + 1);
             }
-            double *p = part + ((static_cast<int64_t>(kd) * gy + blockIdx.y) * NC) * ld + i;
-            const double out[6] = {t.ar, t.ai, t.br, t.bi, t.qr, t.qi};
-#pragma unroll
-            for (int c = 0; c < NC; ++c) p[c * ld] = out[c];
+        } else if (kd + 1 == K) {
+            __syncthreads();
+            if (wave == kd % kSegWaves) fold(kd, sh);
         }
-        __syncthreads();  // LDS is refilled for the next design
     }
 }
 
@@ -314,15 +343,22 @@ ObjPlan plan_objective(const Objective &o, qpm_prec p, int64_t np)
     // the most words per wave (fewest partials to write and fold) that still
     // leaves 400 workgroups, or 256 for 2 words, at most the register limit of
     // the word cache. Partials + values, us, by words per wave: 3000 x 5000, 5
-    // SHG wavelengths FP32: 1 13.3 + 6.4, 2 10.4 + 4.4, 4 10.8 + 3.9, 5 12.3 +
-    // 3.9; 13200 x 1500: 1 14.5 + 23.4, 2 11.2 + 12.3, 5 12.3 + 6.1 (THG, 3
-    // designs: 1 19.9 + 12.6, 2 16.6 + 7.4, 5 18.9 + 4.7); 6000 x 1000 THG, 2
+    // SHG wavelengths FP32: 1 13.1 + 5.9, 2 10.4 + 4.4, 4 9.7 + 3.8, 5 10.6 +
+    // 4.4; 13200 x 1500: 1 15.4 + 8.5, 2 12.7 + 8.2, 5 11.2 + 4.4 (THG, 3
+    // designs: 1 18.3 + 9.6, 2 17.4 + 6.4, 5 19.4 + 4.0); 6000 x 1000 THG, 2
     // designs: 1 7.6 + 8.3, 2 8.1 + 4.6, 3 8.9 + 4.0; 1000 x 300: 1 4.9 + 3.2, 2
-    // 5.4 + 2.9.
+    // 5.4 + 2.9. Where 1 word would leave the longest folds (48 segments), several
+    // designs take at least 2, and 3 where they are copied two at a time: 9000 x
+    // 300, 5 SHG wavelengths FP32 1 6.3 + 8.9, 2 6.6 + 6.3, 3 7.2 + 5.2, 4 7.8 +
+    // 5.0, FP64 1 6.8 + 8.7, 2 7.4 + 6.2; 12000 x 140, 3 THG designs FP32 1 7.4 +
+    // 9.4, 2 8.9 + 5.7, 3 10.6 + 4.4; but one THG design, 9894 x 89: 1 4.2 + 5.1, 2
+    // 4.9 + 5.2.
     const bool f32 = p == QPM_PREC_F32;
     const int64_t groups = (np + 63) / 64;
+    const bool folds = o.K > 1 && combine_ranges(static_cast<int>((o.words + 3) / 4)) == kMaxRanges;
+    const int least = !folds ? 1 : (f32 && o.kind != QPM_OBJ_THG ? 3 : 2);
     int wpw = table_max_wpw(f32);
-    while (wpw > 1 && groups * ((o.words + 4 * wpw - 1) / (4 * wpw)) < (wpw > 2 ? 400 : 256)) --wpw;
+    while (wpw > least && groups * ((o.words + 4 * wpw - 1) / (4 * wpw)) < (wpw > 2 ? 400 : 256)) --wpw;
     while (wpw < table_max_wpw(f32) && (o.words + 4 * wpw - 1) / (4 * wpw) > 65535) ++wpw;
     return plan_objective_shape(o, wpw);
 }
@@ -340,19 +376,28 @@ qpm_status launch_objective_partials(const Objective &o, qpm_prec p, const uint3
     const dim3 grid(static_cast<unsigned>((np + 63) / 64), static_cast<unsigned>(pl.gy));
     const int W = static_cast<int>(o.words);
     const bool f32 = p == QPM_PREC_F32, thg = o.kind == QPM_OBJ_THG;
+    // two designs at a time where three workgroups per CU hold the whole grid
+    // (their LDS leaves no more); beyond that and in FP64 and THG, whose tables
+    // are 2 to 6 times as large, more workgroups hide more than the copies. us,
+    // one / two at a time: 3000 x 5000, 5 wavelengths (474 workgroups of 4 words)
+    // 11.0 / 9.7, 12000 x 80, 2 (32 of 3) 5.2 / 4.6, 3000 x 2000, 8 (384 of 2) 11.6
+    // / 10.0; 20000 x 3000, 3 (1504 of 5) 13.8 / 16.2, 3000 x 50000, 2 19.2 / 25.5;
+    // FP64 13200 x 1500, 5 12.2 / 16.8.
+    const bool twice = f32 && !thg && o.K > 1 && static_cast<int64_t>(grid.x) * grid.y <= 768;
+#define QPM_OP(F, H, T2)                                                                                          \
+    obj_partials_kernel<F, H, T2><<<grid, 256, obj_lds_bytes<F, H>(pl.wpw, T2), s>>>(o.tabs, o.K, bits, ld, W, pl.wpw, \
+                                                                                     pl.gy, np, part, advance)
     if (f32 && thg)
-        obj_partials_kernel<true, true><<<grid, 256, obj_lds_bytes<true, true>(pl.wpw), s>>>(o.tabs, o.K, bits, ld, W,
-                                                                                          pl.wpw, pl.gy, np, part,
-                                                                                          advance);
+        QPM_OP(true, true, false);
+    else if (twice)
+        QPM_OP(true, false, true);
     else if (f32)
-        obj_partials_kernel<true, false><<<grid, 256, obj_lds_bytes<true, false>(pl.wpw), s>>>(
-            o.tabs, o.K, bits, ld, W, pl.wpw, pl.gy, np, part, advance);
+        QPM_OP(true, false, false);
     else if (thg)
-        obj_partials_kernel<false, true><<<grid, 256, obj_lds_bytes<false, true>(pl.wpw), s>>>(
-            o.tabs, o.K, bits, ld, W, pl.wpw, pl.gy, np, part, advance);
+        QPM_OP(false, true, false);
     else
-        obj_partials_kernel<false, false><<<grid, 256, obj_lds_bytes<false, false>(pl.wpw), s>>>(
-            o.tabs, o.K, bits, ld, W, pl.wpw, pl.gy, np, part, advance);
+        QPM_OP(false, false, false);
+#undef QPM_OP
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }
