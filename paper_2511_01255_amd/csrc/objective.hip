@@ -12,6 +12,7 @@
 // the whole (A, B, Q) triple.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "common.hpp"
@@ -43,6 +44,32 @@ size_t obj_lds_bytes(int wpw, bool twice)
     return twice ? 2 * (tables + fold) : (tables > fold ? tables : fold);
 }
 
+// where a grid of one segment writes its values itself (DIRECT)
+struct ObjOut {
+    double scale, G0, beta;
+    void *fit;
+    int f64;
+    double *G;
+    int64_t ldG;
+    int gk_at;  // LDS offset of the G_k
+};
+struct ObjNoOut {};
+template <bool DIRECT>
+using ObjOutArg = std::conditional_t<DIRECT, ObjOut, ObjNoOut>;
+
+// -(sum_k |G0 - G_k| + beta (max G - min G)) from gk[k stride]
+__device__ __forceinline__ double obj_h(const double *gk, int stride, int K, double G0, double beta)
+{
+    double sum = 0.0, gmax = 0.0, gmin = 0.0;
+    for (int k = 0; k < K; ++k) {
+        const double Gk = gk[k * stride];
+        sum += fabs(G0 - Gk);
+        gmax = k == 0 ? Gk : fmax(gmax, Gk);
+        gmin = k == 0 ? Gk : fmin(gmin, Gk);
+    }
+    return -(sum + beta * (gmax - gmin));
+}
+
 }  // namespace
 
 // Grid: x = genome groups of 64, y = workgroup segments of 4 wpw words.
@@ -53,10 +80,13 @@ size_t obj_lds_bytes(int wpw, bool twice)
 // (one per design instead of four), by a wave that changes from design to design.
 // A workgroup's time is mostly these waits: 3000 x 5000, 5 SHG wavelengths FP32,
 // 11.0 -> 9.7 us (4 words per wave).
-template <bool F32, bool THG, bool TWICE>
+// DIRECT (grids of one segment): the fold takes G_k, and the objective follows
+// here instead of in a second launch; the G_k stand behind the other LDS.
+template <bool F32, bool THG, bool TWICE, bool DIRECT>
 __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, const uint32_t *__restrict__ bits,
                                                            int64_t ld, int W, int wpw, int gy, int64_t np,
-                                                           double *__restrict__ part, uint32_t *__restrict__ advance)
+                                                           double *__restrict__ part, uint32_t *__restrict__ advance,
+                                                           ObjOutArg<DIRECT> out)
 {
     if (advance != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) advance[0] += 1u;
     constexpr int R = ObjShape<THG>::R;
@@ -109,10 +139,17 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
                 t.ai += at(1, s2);
             }
         }
-        double *p = part + ((static_cast<int64_t>(kd) * gy + blockIdx.y) * NC) * ld + i;
-        const double out[6] = {t.ar, t.ai, t.br, t.bi, t.qr, t.qi};
+        if constexpr (DIRECT) {
+            const double re = THG ? t.qr + tabs.C[kd][0] : t.ar, im = THG ? t.qi + tabs.C[kd][1] : t.ai;
+            const double Gk = sqrt(fma(re, re, im * im)) * out.scale;
+            reinterpret_cast<double *>(lds + out.gk_at)[kd * 64 + lane] = Gk;
+            if (out.G) out.G[kd * out.ldG + i] = Gk;
+        } else {
+            double *p = part + ((static_cast<int64_t>(kd) * gy + blockIdx.y) * NC) * ld + i;
+            const double comp[6] = {t.ar, t.ai, t.br, t.bi, t.qr, t.qi};
 #pragma unroll
-        for (int c = 0; c < NC; ++c) p[c * ld] = out[c];
+            for (int c = 0; c < NC; ++c) p[c * ld] = comp[c];
+        }
     };
     issue(0);
     // the bit words of this wave's segment, loaded once for all K designs
@@ -172,6 +209,15 @@ __global__ __launch_bounds__(256) void obj_partials_kernel(ObjTabs tabs, int K, 
             __syncthreads();
             if (wave == kd % kSegWaves) fold(kd, sh);
         }
+    }
+    if constexpr (DIRECT) {
+        __syncthreads();
+        if (wave != 0 || !live) return;
+        const double h = obj_h(reinterpret_cast<const double *>(lds + out.gk_at) + lane, 64, K, out.G0, out.beta);
+        if (out.f64)
+            static_cast<double *>(out.fit)[i] = h;
+        else
+            static_cast<float *>(out.fit)[i] = static_cast<float>(h);
     }
 }
 
@@ -263,16 +309,7 @@ __device__ double obj_value(const ObjTabs &tabs, int K, int kb, double scale, do
         }
         __syncthreads();
     }
-    double sum = 0.0, gmax = 0.0, gmin = 0.0;
-    if (slot == 0) {
-        for (int k = 0; k < K; ++k) {
-            const double Gk = gk[k * NG + gl];
-            sum += fabs(G0 - Gk);
-            gmax = k == 0 ? Gk : fmax(gmax, Gk);
-            gmin = k == 0 ? Gk : fmin(gmin, Gk);
-        }
-    }
-    return -(sum + beta * (gmax - gmin));
+    return slot == 0 ? obj_h(gk + gl, NG, K, G0, beta) : 0.0;
 }
 
 // designs folded together by obj_value, and its LDS
@@ -369,8 +406,10 @@ size_t objective_partials_bytes(const Objective &o, const ObjPlan &pl, int64_t l
     return sizeof(double) * static_cast<size_t>(o.K) * pl.gy * nc * static_cast<size_t>(ld);
 }
 
-qpm_status launch_objective_partials(const Objective &o, qpm_prec p, const uint32_t *bits, int64_t np, int64_t ld,
-                                     const ObjPlan &pl, double *part, hipStream_t s, uint32_t *advance)
+template <bool DIRECT>
+static qpm_status launch_partials(const Objective &o, qpm_prec p, const uint32_t *bits, int64_t np, int64_t ld,
+                                  const ObjPlan &pl, double *part, hipStream_t s, uint32_t *advance,
+                                  ObjOutArg<DIRECT> out)
 {
     QPM_REQUIRE(pl.gy <= 65535, QPM_ERANGE, "too many workgroup segments (%d)", pl.gy);
     const dim3 grid(static_cast<unsigned>((np + 63) / 64), static_cast<unsigned>(pl.gy));
@@ -385,8 +424,12 @@ qpm_status launch_objective_partials(const Objective &o, qpm_prec p, const uint3
     // FP64 13200 x 1500, 5 12.2 / 16.8.
     const bool twice = f32 && !thg && o.K > 1 && static_cast<int64_t>(grid.x) * grid.y <= 768;
 #define QPM_OP(F, H, T2)                                                                                          \
-    obj_partials_kernel<F, H, T2><<<grid, 256, obj_lds_bytes<F, H>(pl.wpw, T2), s>>>(o.tabs, o.K, bits, ld, W, pl.wpw, \
-                                                                                     pl.gy, np, part, advance)
+    do {                                                                                                          \
+        const size_t lds = obj_lds_bytes<F, H>(pl.wpw, T2);                                                       \
+        if constexpr (DIRECT) out.gk_at = static_cast<int>(lds);                                                  \
+        obj_partials_kernel<F, H, T2, DIRECT><<<grid, 256, lds + (DIRECT ? o.K * 512 : 0), s>>>(                  \
+            o.tabs, o.K, bits, ld, W, pl.wpw, pl.gy, np, part, advance, out);                                     \
+    } while (0)
     if (f32 && thg)
         QPM_OP(true, true, false);
     else if (twice)
@@ -400,6 +443,12 @@ qpm_status launch_objective_partials(const Objective &o, qpm_prec p, const uint3
 #undef QPM_OP
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
+}
+
+qpm_status launch_objective_partials(const Objective &o, qpm_prec p, const uint32_t *bits, int64_t np, int64_t ld,
+                                     const ObjPlan &pl, double *part, hipStream_t s, uint32_t *advance)
+{
+    return launch_partials<false>(o, p, bits, np, ld, pl, part, s, advance, ObjNoOut{});
 }
 
 qpm_status launch_objective_values(const Objective &o, const ObjPlan &pl, const double *part, int64_t ld, int64_t np,
@@ -552,7 +601,19 @@ QPM_API qpm_status qpm_eval_objective(qpm_objective o, qpm_prec p, const uint32_
     qpm_status st = check_objective_args(o, p, bits, np, ld, fitness, G, ldG);
     if (st != QPM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(sv);
-    const ObjPlan pl = plan_objective(*o, p, np);
+    ObjPlan pl = plan_objective(*o, p, np);
+    // Few words: one launch, which walks up to table_max_wpw words per wave and
+    // writes the values itself, unless the longer walks of K THG designs cost more
+    // than that launch. us per call back to back / with a wait after each, two
+    // launches against one: 500 x 1000 SHG FP32, 1 design 11.4 / 22.0 against 9.2 /
+    // 19.6, 8 designs 11.9 / 27.7 against 11.1 / 26.8; 640 x 256, 8 designs 11.9 /
+    // 27.7 against 12.0 / 27.0; 100 x 300, 8 THG designs (1 word per wave) 17.9 /
+    // 33.6 against 13.5 / 29.3, 256 x 100, 3 THG designs (2 words) 11.4 / 25.0
+    // against 9.1 / 23.4. Table of partials by words, above: 3 THG designs of 5
+    // words instead of 1 walk 7.7 us longer than their values launch took.
+    const int wpw = static_cast<int>(std::min<int64_t>((o->words + 3) / 4, table_max_wpw(p == QPM_PREC_F32) + 1));
+    if (wpw <= table_max_wpw(p == QPM_PREC_F32) && (o->kind != QPM_OBJ_THG || o->K * (wpw - 1) <= 5))
+        pl = plan_objective_shape(*o, wpw);
     return eval_with_plan(o, p, bits, np, ld, fitness, G, ldG, pl, s);
 }
 
@@ -573,6 +634,9 @@ QPM_API qpm_status qpm_eval_objective_shape(qpm_objective o, qpm_prec p, const u
 static qpm_status eval_with_plan(qpm_objective o, qpm_prec p, const uint32_t *bits, int64_t np, int64_t ld,
                                  void *fitness, double *G, int64_t ldG, const ObjPlan &pl, hipStream_t s)
 {
+    if (pl.gy == 1)
+        return launch_partials<true>(*o, p, bits, np, ld, pl, nullptr, s, nullptr,
+                                     ObjOut{o->scale, o->G0, o->beta, fitness, p == QPM_PREC_F64, G, ldG, 0});
     ScratchLease lease(o->scratch, s);
     void *ws = nullptr;
     qpm_status st = lease.begin(objective_partials_bytes(*o, pl, ld), &ws);

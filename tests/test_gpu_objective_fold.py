@@ -45,7 +45,8 @@ def test_run_equals_oracle(q, orc, K, npop, n, G, kind):
 @pytest.mark.parametrize("kind", [0, 1])
 @pytest.mark.parametrize("n,npop,K", [(2048, 1985, 2), (2049, 2049, 3), (6400, 1990, 2), (12801, 1000, 1), (9894, 89, 1),
                                       (12000, 80, 2), (6145, 100, 3), (6144, 100, 3),
-                                      (2561, 9792, 2), (2561, 9792, 5), (2561, 9793, 3), (33, 70, 8)])
+                                      (2561, 9792, 2), (2561, 9792, 5), (2561, 9793, 3), (33, 70, 8), (640, 70, 1), (640, 129, 3),
+                                      (641, 70, 1), (128, 65, 8), (256, 100, 5), (257, 33, 6)])
 def test_default_shape_matches_oracle(q, orc, n, npop, K, kind, prec):
     import torch
     O, Oo = _pair(q, orc, inputs.jittered_boundaries(n, 2.0, 0.3, seed=n), K, kind)
