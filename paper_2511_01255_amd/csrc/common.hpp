@@ -125,7 +125,9 @@ struct FitPlan {
     int gy = 1;                    // workgroup segments along the domain axis
 };
 
-FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel);
+constexpr size_t kNoAllocScratchBytes = size_t(16) << 20;  // the fixed scratch of qpm_eval_fitness_noalloc
+// ld: of the call's bits, or 0 where the partials are the caller's to size
+FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel, int64_t ld = 0);
 // the plan of a run's evaluations, whose fold is the finish step's
 FitPlan plan_fitness_run(const Design &d, qpm_prec p, int64_t np, int kernel);
 size_t fitness_workspace_bytes(const FitPlan &plan, int64_t ld);

@@ -302,7 +302,7 @@ static void table_shape(bool f32, int64_t np, int64_t words, int *gw, int *wpw)
 //   N =  800 (25):       FP32 7.2 / 21.7 against 9.9 / 21.0,  FP64 8.1 / 22.7 against 9.9 / 21.0
 //   N = 1280 (40):       FP32 8.8 / 23.5 against 10.0 / 21.2, FP64 10.7 / 25.2 against 9.9 / 21.2
 constexpr int64_t kDirectWords = 20;
-FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
+FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel, int64_t ld)
 {
     FitPlan pl;
     if (kernel == QPM_FIT_PER_GENOME) {
@@ -314,7 +314,12 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel)
         int gw, wpw;
         table_shape(p == QPM_PREC_F32, np, d.words, &gw, &wpw);
         if (d.words <= kDirectWords) wpw = static_cast<int>((d.words + 3) / 4);
-        return plan_fitness_table(d, p, gw, wpw);
+        pl = plan_fitness_table(d, p, gw, wpw);
+        // few genomes in wide rows: no more partials than 4 words per wave leave,
+        // where the fixed scratch holds only those
+        if (p == QPM_PREC_F32 && wpw < 4 && fitness_workspace_bytes(pl, ld) > kNoAllocScratchBytes)
+            pl = plan_fitness_table(d, p, gw, 4);
+        return pl;
     }
     pl.kind = QPM_FIT_SEGMENTED;
     const int64_t groups = (np + 63) / 64;
@@ -468,7 +473,7 @@ QPM_API qpm_status qpm_eval_fitness(qpm_design d, qpm_prec p, const uint32_t *bi
                 "the per-genome kernel computes in FP64 only");
     qpm_status st = check_fitness_args(d, p, bits, np, ld, fitness);
     if (st != QPM_OK) return st;
-    return run_plan(d, p, bits, np, ld, fitness, plan_fitness(*d, p, np, kernel), static_cast<hipStream_t>(sv));
+    return run_plan(d, p, bits, np, ld, fitness, plan_fitness(*d, p, np, kernel, ld), static_cast<hipStream_t>(sv));
 }
 
 QPM_API qpm_status qpm_eval_fitness_shape(qpm_design d, qpm_prec p, const uint32_t *bits, int64_t np, int64_t ld,

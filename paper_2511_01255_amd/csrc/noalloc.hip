@@ -9,7 +9,6 @@
 
 namespace qpm {
 
-constexpr size_t kNoAllocScratchBytes = size_t(16) << 20;  // 16 MiB per device
 
 // The segment partials of every call on a device: each device that runs the
 // library holds its own copy until the process ends. Host code reaches it
@@ -70,9 +69,12 @@ QPM_API qpm_status qpm_eval_fitness_noalloc(qpm_design d, qpm_prec p, const uint
     QPM_REQUIRE((reinterpret_cast<uintptr_t>(bits) & 3u) == 0, QPM_EINVAL, "bits must be 4-byte aligned");
     QPM_REQUIRE(np <= (int64_t(1) << 31) && d->words * ld <= (int64_t(1) << 40), QPM_ERANGE,
                 "population too large");
-    const FitPlan pl = plan_fitness(*d, p, np, kernel);
+    const FitPlan pl = plan_fitness(*d, p, np, kernel, ld);
     QPM_REQUIRE(pl.gy <= 65535, QPM_ERANGE, "too many workgroup segments (%d)", pl.gy);
-    const size_t bytes = fitness_workspace_bytes(pl, ld);
+    // the limit does not move with the launch shape: 4 words per wave in FP32, 2 in
+    // FP64, of which no plan needs more
+    const FitPlan most = pl.kind == QPM_FIT_TABLE ? plan_fitness_table(*d, p, 1, p == QPM_PREC_F32 ? 4 : 2) : pl;
+    const size_t bytes = std::max(fitness_workspace_bytes(pl, ld), fitness_workspace_bytes(most, ld));
     QPM_REQUIRE(bytes <= kNoAllocScratchBytes, QPM_ERANGE,
                 "this population needs %zu bytes of segment partials, more than the %zu of the fixed scratch "
                 "(use qpm_eval_fitness)",

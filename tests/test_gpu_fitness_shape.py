@@ -56,3 +56,25 @@ def test_batch_default_shape_equals_single(q, ns, npop, prec):
         D = q.precompute_phases(z, inputs.DK1, inputs.DK2)
         g = q.eval_fitness(D, bits[k], npop, 1, kernel=q.FIT_SEGMENTED).cpu().numpy()
         assert np.max(np.abs(f[k] - g) / np.maximum(g, 1e-2 * np.median(g))) <= 2 * TOL[prec]
+
+
+@pytest.mark.parametrize("words,ld,st", [(100, 40000, 0), (112, 49920, 0), (112, 49984, -2), (20, 174720, 0),
+                                         (20, 174784, -2), (16, 200000, 0)])
+def test_fixed_scratch_takes_the_populations_it_took(q, words, ld, st):
+    # few genomes in wide rows, FP32: 48 ld ceil(words / 16) bytes of partials
+    # (none for one segment) against 16 MiB
+    import ctypes as C
+    import torch
+    n, npop = 32 * words, 40
+    D = q.precompute_phases(inputs.uniform_boundaries(n, 2.0), inputs.DK1, inputs.DK2)
+    bits = torch.zeros((words, ld), dtype=torch.int32, device="cuda")
+    one = inputs.pack_bits(inputs.random_signs(npop, n, seed=words)).view(np.int32)
+    bits[:, :one.shape[1]] = torch.from_numpy(one).cuda()
+    out = torch.zeros(npop, dtype=torch.float32, device="cuda")
+    got = q.lib().qpm_eval_fitness_noalloc(D.handle, 0, C.c_void_p(bits.data_ptr()), npop, ld,
+                                           C.c_void_p(out.data_ptr()), q.FIT_AUTO,
+                                           C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert got == st
+    if st == 0:
+        torch.cuda.synchronize()
+        assert torch.equal(out, q.eval_fitness(D, bits, npop, 0))
