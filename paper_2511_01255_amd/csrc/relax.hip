@@ -665,7 +665,11 @@ __global__ __launch_bounds__(256) void polish_project_kernel(const float *__rest
 }
 
 // For each of the three leaders: keep the projected row when its exact +-1
-// fitness beats the leader's. One workgroup per leader.
+// fitness beats the leader's. One workgroup per leader. fcand: the projected
+// rows' fitness, then that of the leaders' present signs from the same launch.
+// Both that and the fitness the run holds must be exceeded: the held one may
+// come from sums folded in another order (the fused generations' walk), whose
+// last bits would pass an unchanged sign pattern off as better.
 template <typename T>
 __global__ __launch_bounds__(256) void polish_accept_kernel(const float *__restrict__ y, int64_t n, int64_t ldy,
                                                             const T *__restrict__ fcand, const int32_t *__restrict__ L,
@@ -676,7 +680,7 @@ __global__ __launch_bounds__(256) void polish_accept_kernel(const float *__restr
     const int k = blockIdx.x;
     const int64_t row = L[k];
     const T fc = fcand[k];
-    if (!(fc > f_cur[row])) return;
+    if (!(fc > fcand[3 + k] && fc > f_cur[row])) return;
     float *dst = (flags[row] ? x1 : x0) + row * ldx;
     for (int64_t j = threadIdx.x; j < n; j += 256) dst[j] = y[k * ldy + j];
     __syncthreads();

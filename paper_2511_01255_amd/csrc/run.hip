@@ -71,8 +71,8 @@ struct qpm_run_s {
     float *pol = nullptr;       // theta, grad, y: 3 rows of ldx each
     double *pol_S = nullptr;   // 3 x 2
     float *pol_f = nullptr;    // 3 relaxed values, then 3 ones (grad_f)
-    void *pol_fc = nullptr;    // 3 exact fitness values
-    uint32_t *pol_bits = nullptr;  // W x 64
+    void *pol_fc = nullptr;    // exact fitness of the 3 projected rows, then of the 3 leaders as they are
+    uint32_t *pol_bits = nullptr;  // W x 64: the same 6 rows
     uint32_t *pol_acc = nullptr;
     double *pol_ws = nullptr;
     double *pol_edges = nullptr;  // relaxation edges of the 3 rows (both precisions' sizes)
@@ -857,15 +857,14 @@ QPM_API qpm_status qpm_run_polish(qpm_run_handle r, int32_t steps, float eta, in
     const qpm_run_config &c = r->cfg;
     const qpm_prec p = static_cast<qpm_prec>(c.prec);
     const int64_t ldx = r->ldx, D = r->D;
-    const FitPlan pl3 = plan_fitness(*r->d, p, 3, QPM_FIT_AUTO);
     if (!r->pol) {
         hipError_t e = hipMalloc(&r->pol, sizeof(float) * 9 * ldx);
         if (e == hipSuccess) e = hipMalloc(&r->pol_S, sizeof(double) * 6);
         if (e == hipSuccess) e = hipMalloc(&r->pol_f, sizeof(float) * 6);
-        if (e == hipSuccess) e = hipMalloc(&r->pol_fc, sizeof(double) * 3);
+        if (e == hipSuccess) e = hipMalloc(&r->pol_fc, sizeof(double) * 6);
         if (e == hipSuccess) e = hipMalloc(&r->pol_bits, sizeof(uint32_t) * r->W * 64);
         if (e == hipSuccess) e = hipMalloc(&r->pol_acc, sizeof(uint32_t));
-        const size_t wsb = fitness_workspace_bytes(pl3, 64);
+        const size_t wsb = fitness_workspace_bytes(r->plan, 64);
         if (e == hipSuccess && wsb) e = hipMalloc(&r->pol_ws, wsb);
         int64_t ne = 0;
         if (e == hipSuccess && qpm_relax_edges_size(static_cast<qpm_design>(const_cast<qpm_design_s *>(
@@ -886,6 +885,7 @@ QPM_API qpm_status qpm_run_polish(qpm_run_handle r, int32_t steps, float eta, in
     auto *dh = const_cast<qpm_design_s *>(static_cast<const qpm_design_s *>(r->d));
     const PopView pv = r->view();
     qpm_status st = launch_gather(pv, r->leaders, 3, theta, ldx, r->st);
+    if (st == QPM_OK) st = launch_pack_pop(theta, 3, D, ldx, r->pol_bits + 3, 64, r->st);
     for (int32_t k = 0; k < steps && st == QPM_OK; ++k) {
         st = qpm_relax_forward(dh, p, theta, 3, ldx, r->pol_f, r->pol_S, r->pol_edges, r->st);
         if (st == QPM_OK)
@@ -894,7 +894,8 @@ QPM_API qpm_status qpm_run_polish(qpm_run_handle r, int32_t steps, float eta, in
     }
     if (st == QPM_OK) st = launch_polish_project(theta, y, 3, D, ldx, r->st);
     if (st == QPM_OK) st = launch_pack_pop(y, 3, D, ldx, r->pol_bits, 64, r->st);
-    if (st == QPM_OK) st = launch_fitness(*r->d, p, r->pol_bits, 3, 64, r->pol_fc, pl3, r->pol_ws, r->st);
+    // the run's own plan, so that an accepted fitness is the sum its evaluations make
+    if (st == QPM_OK) st = launch_fitness(*r->d, p, r->pol_bits, 6, 64, r->pol_fc, r->plan, r->pol_ws, r->st);
     if (st == QPM_OK) {
         QPM_TRY_HIP(hipMemsetAsync(r->pol_acc, 0, sizeof(uint32_t), r->st));
         st = launch_polish_accept(y, D, ldx, r->pol_fc, r->f64(), r->leaders, pv, r->f_cur, r->pol_acc, r->st);
