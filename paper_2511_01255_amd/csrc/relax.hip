@@ -90,17 +90,21 @@ __device__ __forceinline__ float tanh_t<float>(float x)
 // FP64: tanh |x| = E / (E + 2) with E = e^y - 1, y = 2 |x|: y = k ln 2 + r, |r| <=
 // ln 2 / 2, e^r - 1 by its Taylor series (the next term, r^15 / 15!, is below
 // 2^-61 of the sum), E = 2^k (e^r - 1) + (2^k - 1), the quotient by two Newton
-// steps on the hardware reciprocal and a residual correction. 1 from |x| = 20 on
-// (1 - tanh 20 < 2^-56); NaN stays NaN. (The library's tanh takes twice
-// the vector instructions.)
+// steps on the hardware reciprocal and a residual correction. r, e^r - 1, E and
+// E + 2 are each a sum of two parts, so that their roundings do not add up: over
+// binary32 arguments in [0, 1] at most 0.72 ulp off and 0.251 on average, where
+// the library's tanh is 0.86 and 0.256 off (without the low parts of r and e^r -
+// 1: 1.74 and 0.280). 1 from |x| = 20 on (1 - tanh 20 < 2^-56); NaN stays NaN.
+// (The library's tanh takes twice the vector instructions.)
 template <>
 __device__ __forceinline__ double tanh_t<double>(double x)
 {
     const double ax = fabs(x);
     const double y = 2.0 * fmin(ax, 20.0);
     const double k = rint(y * 1.4426950408889634);
-    double r = fma(k, -0x1.62e42fefa39efp-1, y);  // ln 2 in two parts
-    r = fma(k, -0x1.abc9e3b39803fp-56, r);
+    const double r0 = fma(k, -0x1.62e42fep-1, y);  // exact: the first part of ln 2 has 28 bits
+    const double r = fma(k, -0x1.f473de6af278fp-30, r0);
+    const double r_lo = fma(k, -0x1.f473de6af278fp-30, r0 - r);
     double p = 1.0 / 87178291200.0;
     p = fma(p, r, 1.0 / 6227020800.0);
     p = fma(p, r, 1.0 / 479001600.0);
@@ -114,13 +118,15 @@ __device__ __forceinline__ double tanh_t<double>(double x)
     p = fma(p, r, 1.0 / 24.0);
     p = fma(p, r, 1.0 / 6.0);
     p = fma(p, r, 0.5);
-    p = fma(p * r, r, r);  // e^r - 1
+    // e^r - 1, and what its rounding and r_lo (times e^r = 1 + r + ..) add
+    const double pr = p * r, s = fma(pr, r, r);
+    const double s_lo = fma(pr, r, r - s) + fma(r, r_lo, r_lo);
     const double two_k = ldexp(1.0, static_cast<int>(k));
-    // E and E + 2 as sums of two parts (two_k - 1 is exact, and larger than the
-    // other term unless it is 0)
+    // (two_k - 1 is exact below 2^53, beyond which tanh does not see it, and larger
+    // than the other term unless it is 0)
     const double m = two_k - 1.0;
-    const double E = fma(two_k, p, m), E_lo = fma(two_k, p, m - E);
-    const double D = E + 2.0, D_lo = (2.0 - D) + E + E_lo;
+    const double E = fma(two_k, s, m), E_lo = fma(two_k, s_lo, fma(two_k, s, m - E));
+    const double D = E + 2.0, D_lo = (fmax(E, 2.0) - D) + fmin(E, 2.0) + E_lo;
     double q = __builtin_amdgcn_rcp(D);
     q = fma(fma(-D, q, 1.0), q, q);
     q = fma(fma(-D, q, 1.0), q, q);
