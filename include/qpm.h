@@ -126,6 +126,12 @@ qpm_status qpm_design_read_phases(qpm_design d, double *a, double *b, double *c)
  * fitness: device, np floats (QPM_PREC_F32) or doubles (QPM_PREC_F64).
  * kernel: a qpm_fit_kernel; QPM_FIT_PER_GENOME needs QPM_PREC_F64.
  * Device scratch: the segment partials (see Conventions, Scratch).
+ * The sums are taken in the order of the launch plan, which follows from the
+ * design's size, the precision and np (and ld where a few genomes lie in very
+ * wide rows): equal sizes give equal bits, another np, a batch or an explicit
+ * shape the same value within rounding. A run that is neither tuned nor fused
+ * evaluates on the plan of a call with its np, so its fitness is that call's,
+ * bit for bit.
  * Errors: QPM_EINVAL (np < 1, ld < np or not a multiple of 64, NULL
  * pointer, unknown precision or kernel), QPM_ENOMEM, QPM_EHIP.
  */

@@ -123,13 +123,17 @@ struct FitPlan {
     int waves = 16;                // waves per workgroup (segmented) or genome groups (table)
     int wpw = 2;                   // bit words per wave
     int gy = 1;                    // workgroup segments along the domain axis
+    bool direct = false;           // launch_fitness walks all segments in one workgroup (no partials)
 };
 
 constexpr size_t kNoAllocScratchBytes = size_t(16) << 20;  // the fixed scratch of qpm_eval_fitness_noalloc
-// ld: of the call's bits, or 0 where the partials are the caller's to size
+// The default plan, of a call and of an untuned run's evaluations alike, so that both
+// give a genome the same bits at the same np. ld: of the call's bits, or 0 where
+// the partials are the caller's to size.
 FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel, int64_t ld = 0);
-// the plan of a run's evaluations, whose fold is the finish step's
-FitPlan plan_fitness_run(const Design &d, qpm_prec p, int64_t np, int kernel);
+// once per design: FP64 tables of 11 to kDirectWords words pass the 64 KB of LDS that a
+// launch may ask for without saying so first
+qpm_status prepare_fitness(const Design &d);
 size_t fitness_workspace_bytes(const FitPlan &plan, int64_t ld);
 qpm_status launch_fitness(const Design &d, qpm_prec p, const uint32_t *bits, int64_t np, int64_t ld,
                           void *fitness, const FitPlan &plan, double *workspace, hipStream_t s);
@@ -294,7 +298,7 @@ __host__ __device__ constexpr int table_max_wpw(bool f32) { return f32 ? 5 : 2; 
 // wave that a plan takes
 constexpr int kTabPlanWords = 16;
 // LDS of one table-kernel workgroup (tables, reused for the combine)
-size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw);
+size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw, bool staged = false);
 // DE draws of generation *gen_dev for every individual
 qpm_status launch_draws(int64_t np, int64_t D, uint64_t seed, const uint32_t *gen_dev, uint32_t inst, int4 *draws,
                         hipStream_t s);

@@ -146,8 +146,10 @@ __global__ __launch_bounds__(128) void fit_per_genome_kernel(const uint32_t *__r
 // order. FP32: the word's A and B summed exactly in fixed point, its Q in
 // binary32, each word's triple folded into FP64 (word_tab_q); FP64:
 // binary64 throughout.
-// STAGED: segments of more words than table_max_wpw (tab_segment_staged).
-template <bool F32, int GW, bool STAGED>
+// STAGED: 1, segments of more words than table_max_wpw; 2, every segment of a
+// short design one after the other (tab_segment_staged); 3, side by side, GW of
+// them (tab_segment).
+template <bool F32, int GW, int STAGED>
 __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__restrict__ bits, int64_t ld, int W,
                                                            const double2 *__restrict__ tab64,
                                                            const int2 *__restrict__ tabq,
@@ -161,10 +163,13 @@ __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__res
     // read the counter (the finish step after it reads the new value)
     if (advance != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) advance[0] += 1u;
     const int wbase = static_cast<int>(blockIdx.y) * 4 * wpw;
-    const int64_t i = (static_cast<int64_t>(blockIdx.x) * GW + (threadIdx.x >> 8)) * 64 + (threadIdx.x & 63);
+    const int64_t i = (STAGED == 3 ? static_cast<int64_t>(blockIdx.x)
+                                   : static_cast<int64_t>(blockIdx.x) * GW + (threadIdx.x >> 8)) * 64 + (threadIdx.x & 63);
     Tri t;
-    if constexpr (STAGED) {
-        if (!tab_segment_staged<F32, GW>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
+    if constexpr (STAGED == 3) {
+        if (!tab_segment<F32, GW, true>(t, bits, ld, W, 0, tab64, tabq, wsc, wpw, np, lds)) return;
+    } else if constexpr (STAGED != 0) {
+        if (!tab_segment_staged<F32, GW, STAGED == 2>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
     } else {
         if (!tab_segment<F32, GW>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
     }
@@ -181,10 +186,26 @@ __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__res
     }
 }
 
-size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw)
+// Designs of at most this many words: one workgroup walks all their segments and
+// writes the fitness itself, so that nothing is launched after it; segment by segment
+// in the order of the fold, so that the bits are those of a run's evaluation and its
+// finish step. Side by side (4 waves each, every table in LDS) while a workgroup
+// takes one group of genomes, else one after the other. us per call back to
+// back / with a wait after each, two launches against one that walked a single
+// segment (both precisions, NP = 64 to 5000), and side by side (NP = 300):
+//   N =  640 (20 words): FP32 10.0 / 21.0, 7.2 / 20.0; FP64 10.0 / 21.0, 7.2 / 21.2
+//   N =  800 (25):       FP32 9.9 / 21.0, 7.2 / 21.7;  FP64 9.9 / 21.0, 8.1 / 22.7
+//   N = 1280 (40):       FP32 10.0 / 21.2, 8.8 / 23.5; FP64 9.9 / 21.2, 10.7 / 25.2
+//   N =  640, single segment / one after the other / side by side, with a wait:
+//                        FP32 21.1 / 23.4 / 20.4, FP64 22.4 / 24.2 / 20.7
+constexpr int64_t kDirectWords = 20;
+// the most segments that one workgroup walks to the end (FitPlan::direct)
+constexpr int kDirectSegments = 3;
+
+size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw, bool staged)
 {
     const int64_t words = std::min<int64_t>(W, 4 * static_cast<int64_t>(wpw));
-    const size_t tab = wpw > table_max_wpw(f32) ? 2 * (f32 ? TabStage<true>::kBytes : TabStage<false>::kBytes)
+    const size_t tab = staged || wpw > table_max_wpw(f32) ? 2 * (f32 ? TabStage<true>::kBytes : TabStage<false>::kBytes)
                                                 : static_cast<size_t>(words) * 8 * 48 * (f32 ? 8 : 16);
     const size_t comb = static_cast<size_t>(gw) * 4 * 64 * 6 * 8;
     return std::max(tab, comb);
@@ -196,20 +217,33 @@ static qpm_status launch_tab(const Design &d, const FitPlan &pl, const uint32_t 
                              uint32_t *advance = nullptr)
 {
     const int gw = pl.waves;
-    const dim3 grid(static_cast<unsigned>((np + 64 * gw - 1) / (64 * gw)), static_cast<unsigned>(pl.gy));
-    const int direct = direct_ok && pl.gy == 1;
+    const bool many = direct_ok && pl.direct && pl.gy > 1;
+    const dim3 grid(static_cast<unsigned>((np + 64 * gw - 1) / (64 * gw)), static_cast<unsigned>(many ? 1 : pl.gy));
+    const int direct = direct_ok && (many || pl.gy == 1);
     const int W = static_cast<int>(d.words);
-    const size_t lds = table_lds_bytes(d.words, F32, gw, pl.wpw);
+    const bool side = many && gw == 1;  // the segments side by side
+    const size_t lds = side ? std::max<size_t>(static_cast<size_t>(W) * 8 * 48 * (F32 ? 8 : 16), pl.gy * 4 * 64 * 6 * 8)
+                            : table_lds_bytes(d.words, F32, gw, pl.wpw, many);
 #define QPM_TAB_KERNEL(G, ST)                                                                                 \
     fit_tab_kernel<F32, G, ST><<<grid, dim3(G * 256), lds, s>>>(bits, ld, W, d.tab64, d.tabq, d.wsc, pl.wpw, np,  \
                                                                 part, d.Cdev, fit, direct, out_f64, advance)
 #define QPM_TAB_CASE(G)                                                                                       \
     case G:                                                                                                   \
-        if (pl.wpw > table_max_wpw(F32))                                                                      \
-            QPM_TAB_KERNEL(G, true);                                                                          \
+        if (many)                                                                                             \
+            QPM_TAB_KERNEL(G, 2);                                                                             \
+        else if (pl.wpw > table_max_wpw(F32))                                                                 \
+            QPM_TAB_KERNEL(G, 1);                                                                             \
         else                                                                                                  \
-            QPM_TAB_KERNEL(G, false);                                                                         \
+            QPM_TAB_KERNEL(G, 0);                                                                             \
         break;
+    if (side) {
+        static_assert(kDirectSegments == 3, "two or three segments side by side");
+        if (pl.gy == 2)
+            QPM_TAB_KERNEL(2, 3);
+        else
+            QPM_TAB_KERNEL(3, 3);
+        return QPM_OK;
+    }
     switch (gw) {
         QPM_TAB_CASE(1)
         QPM_TAB_CASE(2)
@@ -257,6 +291,17 @@ FitPlan plan_fitness_table(const Design &d, qpm_prec p, int gw, int wpw)
     return pl;
 }
 
+qpm_status prepare_fitness(const Design &d)
+{
+    const int lds = static_cast<int>(d.words * 8 * 48 * 16);
+    if (d.words > kDirectWords || lds <= 65536) return QPM_OK;
+    QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fit_tab_kernel<false, 2, 3>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kFusedMaxLds));
+    QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fit_tab_kernel<false, 3, 3>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kFusedMaxLds));
+    return QPM_OK;
+}
+
 // Launch shape of the table kernel (genome groups per workgroup, words per
 // wave) from the work, in waves' words: 64-genome groups x words. Small work
 // takes small workgroups (a wave walks its words one after the other, and
@@ -294,14 +339,15 @@ static void table_shape(bool f32, int64_t np, int64_t words, int *gw, int *wpw)
     if (f32 && *wpw == 7) *wpw = 8;
 }
 
-// Designs of at most this many words: one workgroup walks them all and writes
-// the fitness itself, so that nothing is launched after it. us per call back to
-// back / with a wait after each, one launch against table_shape's two, both
-// precisions, NP = 64 to 5000:
-//   N =  640 (20 words): FP32 7.2 / 20.0 against 10.0 / 21.0, FP64 7.2 / 21.2 against 10.0 / 21.0
-//   N =  800 (25):       FP32 7.2 / 21.7 against 9.9 / 21.0,  FP64 8.1 / 22.7 against 9.9 / 21.0
-//   N = 1280 (40):       FP32 8.8 / 23.5 against 10.0 / 21.2, FP64 10.7 / 25.2 against 9.9 / 21.2
-constexpr int64_t kDirectWords = 20;
+// More words per wave (up to kFoldWords) where that leaves fewer than 48 segments. A
+// run's finish step folds 64 genomes per workgroup (its selection needs them), so
+// 16 ranges of many segments keep one CU's loads busy. us per generation, two
+// words per wave / as here: 12472 x 86 FP32 33.8 / 30.1, 18000 x 66 38.7 / 31.9,
+// 22000 x 200 54.5 / 46.8, 25000 x 100 45.5 / 39.3, 30000 x 130 52.5 / 47.2; FP64 34.0
+// / 31.6, 39.1 / 33.5, 56.2 / 49.0, 46.0 / 42.7, 55.1 / 49.6. (A call alone loses: 25000 x
+// 100 FP64 25.2 / 28.5, 16000 x 150 FP32 24.4 / 26.3, back to back 0 to 14 %; it
+// takes the same plan so that a call gives the run's bits.)
+constexpr int kFoldWords = 5;
 FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel, int64_t ld)
 {
     FitPlan pl;
@@ -313,11 +359,19 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel, int64_
     if (kernel == QPM_FIT_AUTO || kernel == QPM_FIT_TABLE) {
         int gw, wpw;
         table_shape(p == QPM_PREC_F32, np, d.words, &gw, &wpw);
-        if (d.words <= kDirectWords) wpw = static_cast<int>((d.words + 3) / 4);
+        wpw = std::min(wpw, static_cast<int>((d.words + 3) / 4));
         pl = plan_fitness_table(d, p, gw, wpw);
+        for (int w = wpw; w <= std::max(wpw, kFoldWords); ++w) {
+            const FitPlan q = plan_fitness_table(d, p, gw, w);
+            if (combine_ranges(q.gy) != kMaxRanges) {
+                pl = q;
+                break;
+            }
+        }
+        pl.direct = d.words <= kDirectWords && pl.gy <= kDirectSegments;
         // few genomes in wide rows: no more partials than 4 words per wave leave,
         // where the fixed scratch holds only those
-        if (p == QPM_PREC_F32 && wpw < 4 && fitness_workspace_bytes(pl, ld) > kNoAllocScratchBytes)
+        if (p == QPM_PREC_F32 && pl.wpw < 4 && fitness_workspace_bytes(pl, ld) > kNoAllocScratchBytes)
             pl = plan_fitness_table(d, p, gw, 4);
         return pl;
     }
@@ -339,25 +393,6 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel, int64_
     return pl;
 }
 
-// The finish step folds 64 genomes per workgroup (its selection needs them), so
-// 16 ranges of many segments keep one CU's loads busy: a table plan takes
-// more words per wave where that leaves fewer than 48 segments. Kernel + finish,
-// us, at 12472 x 86: 2 words (49 segments) 4.0 + 6.9, 4 words 5.2 + 3.7.
-constexpr int kRunWords = 5;
-FitPlan plan_fitness_run(const Design &d, qpm_prec p, int64_t np, int kernel)
-{
-    FitPlan pl = plan_fitness(d, p, np, kernel);
-    if (pl.kind != QPM_FIT_TABLE) return pl;
-    // a run folds in its finish step whatever the number of segments
-    table_shape(p == QPM_PREC_F32, np, d.words, &pl.waves, &pl.wpw);
-    pl = plan_fitness_table(d, p, pl.waves, pl.wpw);
-    for (int wpw = pl.wpw; wpw <= std::max(pl.wpw, kRunWords); ++wpw) {
-        const FitPlan q = plan_fitness_table(d, p, pl.waves, wpw);
-        if (combine_ranges(q.gy) != kMaxRanges) return q;
-    }
-    return pl;
-}
-
 FitPlan plan_fitness_shape(const Design &d, int waves, int wpw)
 {
     FitPlan pl;
@@ -371,7 +406,7 @@ FitPlan plan_fitness_shape(const Design &d, int waves, int wpw)
 
 size_t fitness_workspace_bytes(const FitPlan &pl, int64_t ld)
 {
-    if (pl.kind == QPM_FIT_PER_GENOME || pl.gy <= 1) return 0;
+    if (pl.kind == QPM_FIT_PER_GENOME || pl.gy <= 1 || pl.direct) return 0;
     return sizeof(double) * 6 * static_cast<size_t>(pl.gy) * static_cast<size_t>(ld);
 }
 
@@ -398,7 +433,7 @@ qpm_status launch_fitness(const Design &d, qpm_prec p, const uint32_t *bits, int
             st = p == QPM_PREC_F32 ? launch_seg<true>(d, pl, bits, np, ld, part, fit, out_f64, true, s)
                                    : launch_seg<false>(d, pl, bits, np, ld, part, fit, out_f64, true, s);
         if (st != QPM_OK) return st;
-        if (pl.gy > 1) {
+        if (pl.gy > 1 && !pl.direct) {
             if (combine_ranges(pl.gy) == kMaxRanges)
                 fit_combine_kernel<kMaxRanges><<<static_cast<unsigned>((np + 15) / 16), 256, 0, s>>>(
                     part, pl.gy, ld, np, d.Cdev, fit, out_f64);

@@ -331,6 +331,11 @@ QPM_API qpm_status qpm_precompute_phases(const double *z, int64_t n, double dk1,
         set_error("phase precompute failed: %s", hipGetErrorString(e));
         return QPM_EHIP;
     }
+    st = prepare_fitness(*d);
+    if (st != QPM_OK) {
+        free_design(d);
+        return st;
+    }
     // the per-call scratch cache (without it every call allocates its own)
     d->scratch = scratch_cache_create();
     *out = d;

@@ -256,7 +256,7 @@ __device__ __forceinline__ void walk_chunk(const double2 *co, int wave, int ch, 
 // lane.
 // 256 rows x 5 x 10^4 domains, FP32: 20.3 us; 15 without the walk (51 MB read
 // and staged), 8.4 the walk's vector instructions at full rate. FP64, 256 x
-// 3 x 10^4: 51 -> 24 us.
+// 3 x 10^4: 51 -> 27 us.
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 1))) void
 relax_fwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void relax_combine_kernel(const
 // each chunk's gradients go back through the wave's LDS tile and are stored
 // coalesced (four lanes per row, 16 bytes each).
 // 256 rows x 5 x 10^4 domains, FP32: 28 us; 24 without the walk (102 MB read and
-// written). FP64, 256 x 3 x 10^4: 54 -> 29 us.
+// written). FP64, 256 x 3 x 10^4: 54 -> 31 us.
 template <typename T>
 __global__ __launch_bounds__(256) void
 relax_bwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,

@@ -532,7 +532,7 @@ static qpm_status create_run(const Design *d, const Objective *obj, const qpm_ru
     r->lazy = c.trials == QPM_TRIALS_ACCEPTED ||
               (c.trials == QPM_TRIALS_AUTO && c.algo == QPM_ALGO_HWSDA && lazy_ok &&
                2 * static_cast<int64_t>(sizeof(float)) * c.np * r->ldx > (int64_t(64) << 20));
-    r->plan = plan_fitness_run(*d, static_cast<qpm_prec>(c.prec), c.np, c.fit_kernel);
+    r->plan = plan_fitness(*d, static_cast<qpm_prec>(c.prec), c.np, c.fit_kernel);
     if (obj) r->oplan = plan_objective(*obj, static_cast<qpm_prec>(c.prec), c.np);
     const size_t es = r->f64() ? sizeof(double) : sizeof(float);
     const size_t gene_bytes = sizeof(float) * static_cast<size_t>(c.np) * static_cast<size_t>(r->ldx);

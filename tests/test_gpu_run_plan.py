@@ -1,6 +1,7 @@
-"""An untuned run and a call score a population on one plan: the fitness a run
-holds equals that of qpm_eval_fitness (qpm_eval_objective) for the same signs and
-the same population size, bit for bit."""
+"""An untuned multi-kernel run and a call score a population on one plan: the
+fitness a run holds equals that of qpm_eval_fitness for the same signs and the
+same population size, bit for bit. Objectives: the same here (a call on a short
+design may add its words in another order, which FP64 shows at 5 to 8 words)."""
 import numpy as np
 import pytest
 
