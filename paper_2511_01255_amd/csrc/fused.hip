@@ -18,7 +18,7 @@
 // the whole chip makes them first (fused_words_kernel): the donors, the genes
 // DE takes from the mutant, and the grey-wolf coefficients A and C. The
 // generations read them back (98 bytes per gene quad, at up to 115 GB/s for one
-// compute unit) ahead of their use. At 256 x 32, FP64: 9.8 -> 5.8 us per
+// compute unit) ahead of their use (a launch of few generations makes them itself). At 256 x 32, FP64: 9.8 -> 5.8 us per
 // generation, of which the two optimiser steps' vector instructions are half
 // and the two evaluations 2 us.
 //
@@ -120,6 +120,22 @@ __host__ __device__ inline FusedLayout fused_layout(int64_t np, int64_t D, int W
     return L;
 }
 
+// the donors of individual i in generation g, packed
+__device__ __forceinline__ uint32_t fused_donors(const FusedArgs &a, int i, uint32_t g)
+{
+    const int4 d = de_draw(i, a.np, a.D, g, a.inst, a.k0, a.k1);
+    return static_cast<uint32_t>(8 * d.x) | static_cast<uint32_t>(8 * d.y) << 10 | static_cast<uint32_t>(8 * d.z) << 20;
+}
+
+// which genes of quad q individual i takes from the mutant (bits 0 .. 3)
+__device__ __forceinline__ uint32_t fused_take(const FusedArgs &a, uint32_t i, uint32_t q, uint32_t g)
+{
+    const U4 u = philox10(q, i, g, (a.inst << 8) | kTagDeCr, a.k0, a.k1);
+    const int rel = de_draw(i, a.np, a.D, g, a.inst, a.k0, a.k1).w - 4 * static_cast<int>(q);
+    return (u.x <= a.cr_max || rel == 0 ? 1u : 0u) | (u.y <= a.cr_max || rel == 1 ? 2u : 0u) |
+           (u.z <= a.cr_max || rel == 2 ? 4u : 0u) | (u.w <= a.cr_max || rel == 3 ? 8u : 0u);
+}
+
 // The random numbers of generations gen[0] + blockIdx.y. Grid: 4 workgroups
 // (together the threads of the generation kernel) x generations.
 __global__ __launch_bounds__(256) void fused_words_kernel(FusedArgs a)
@@ -130,24 +146,14 @@ __global__ __launch_bounds__(256) void fused_words_kernel(FusedArgs a)
     const int t = static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x);
     const int np = static_cast<int>(a.np), D = static_cast<int>(a.D), Q = (D + 3) / 4, Qpad = 8 * a.W;
     const bool has_de = a.algo != QPM_ALGO_GWO, has_gwo = a.algo != QPM_ALGO_DE;
-    if (has_de && t < np) {
-        const int4 d = de_draw(t, a.np, a.D, g, a.inst, a.k0, a.k1);
-        reinterpret_cast<uint32_t *>(base)[t] = static_cast<uint32_t>(8 * d.x) | static_cast<uint32_t>(8 * d.y) << 10 |
-                                                static_cast<uint32_t>(8 * d.z) << 20;
-    }
+    if (has_de && t < np) reinterpret_cast<uint32_t *>(base)[t] = fused_donors(a, t, g);
     float4 *coef = reinterpret_cast<float4 *>(base + w.coef);
     const float ag = a.a_tab[g], two_a = 2.0f * ag;
     uint32_t take = 0;
     for (int k = t, r = 0; k < np * Qpad; k += kFusedThreads, ++r) {
         const uint32_t i = static_cast<uint32_t>(k / Qpad), q = static_cast<uint32_t>(k % Qpad);
         if (static_cast<int>(q) >= Q) continue;
-        if (has_de) {
-            const U4 u = philox10(q, i, g, (a.inst << 8) | kTagDeCr, a.k0, a.k1);
-            const int rel = de_draw(i, a.np, a.D, g, a.inst, a.k0, a.k1).w - 4 * static_cast<int>(q);
-            const uint32_t n = (u.x <= a.cr_max || rel == 0 ? 1u : 0u) | (u.y <= a.cr_max || rel == 1 ? 2u : 0u) |
-                               (u.z <= a.cr_max || rel == 2 ? 4u : 0u) | (u.w <= a.cr_max || rel == 3 ? 8u : 0u);
-            take |= n << (4 * r);
-        }
+        if (has_de) take |= fused_take(a, i, q, g) << (4 * r);
         if (has_gwo) {
             float A[12], Cc[12];
             gwo_coef(q, i, g, a.inst, a.k0, a.k1, ag, two_a, A, Cc);
@@ -304,7 +310,8 @@ __device__ __forceinline__ void fused_leaders(const double *fs, const int2 *cur,
     __syncthreads();
 }
 
-template <int VARIANT, bool TAB_LDS>
+// OWN: the kernel makes its random numbers itself, where they are used
+template <int VARIANT, bool TAB_LDS, bool OWN>
 __global__ __launch_bounds__(kFusedThreads) void fused_gen_kernel(FusedArgs a)
 {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -381,26 +388,36 @@ __global__ __launch_bounds__(kFusedThreads) void fused_gen_kernel(FusedArgs a)
     const int donor = min(tid, np - 1);
     uint32_t d_next = 0, take = 0, take_next = 0;
     float4 v[6] = {};
-    if (has_de) {
-        if (tid < np) dr[tid] = reinterpret_cast<const uint32_t *>(words)[tid];
-        take = reinterpret_cast<const uint32_t *>(words + fw.take)[tid];
+    if constexpr (OWN) {
+        if (has_de && tid < np) dr[tid] = fused_donors(a, tid, g);
+    } else {
+        if (has_de) {
+            if (tid < np) dr[tid] = reinterpret_cast<const uint32_t *>(words)[tid];
+            take = reinterpret_cast<const uint32_t *>(words + fw.take)[tid];
+        }
+        if (has_gwo) coef(words, 0, v);
     }
-    if (has_gwo) coef(words, 0, v);
     __syncthreads();
 
     for (int it = 0; it < a.gens; ++it, ++g) {
         const bool more = it + 1 < a.gens;
         const unsigned char *words_next = more ? words + fw.stride : words;
         const float F_next = a.F_tab[more ? g + 1 : g];
+        const float ag = OWN ? a.a_tab[g] : 0.0f;
         if (has_de) {
             // (by every thread: a load in a branch makes its uses wait for
             // every later load too)
-            d_next = reinterpret_cast<const uint32_t *>(words_next)[donor];
-            take_next = reinterpret_cast<const uint32_t *>(words_next + fw.take)[tid];
+            if constexpr (OWN) {
+                if (more && tid < np) d_next = fused_donors(a, tid, g + 1);
+            } else {
+                d_next = reinterpret_cast<const uint32_t *>(words_next)[donor];
+                take_next = reinterpret_cast<const uint32_t *>(words_next + fw.take)[tid];
+            }
             // DE trials, evaluation, greedy selection
             for (int rd = 0, i = i_first, q = q_first; rd < rounds; ++rd) {
                 uint32_t nib = 0;
                 if (i < np && q < Q) {
+                    if constexpr (OWN) take = fused_take(a, i, q, g) << (4 * rd);
                     const uint32_t d = dr[i];
                     const int2 ci = cur[i];
                     auto row = [&](uint32_t at) -> int { return *reinterpret_cast<const int *>(lds + at); };
@@ -443,16 +460,23 @@ __global__ __launch_bounds__(kFusedThreads) void fused_gen_kernel(FusedArgs a)
                 uint32_t nib = 0;
                 if (i < np && q < Q && i != L0 && i != L1 && i != L2) {
                     const int2 ci = cur[i];
-                    const float A[12] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y,
-                                         v[1].z, v[1].w, v[2].x, v[2].y, v[2].z, v[2].w};
-                    const float Cc[12] = {v[3].x, v[3].y, v[3].z, v[3].w, v[4].x, v[4].y,
-                                          v[4].z, v[4].w, v[5].x, v[5].y, v[5].z, v[5].w};
+                    float A[12], Cc[12];
+                    if constexpr (OWN) {
+                        gwo_coef(q, i, g, a.inst, a.k0, a.k1, ag, 2.0f * ag, A, Cc);
+                    } else {
+#pragma unroll
+                        for (int m = 0; m < 3; ++m) {
+                            const float4 va = v[m], vc = v[3 + m];
+                            A[4 * m] = va.x, A[4 * m + 1] = va.y, A[4 * m + 2] = va.z, A[4 * m + 3] = va.w;
+                            Cc[4 * m] = vc.x, Cc[4 * m + 1] = vc.y, Cc[4 * m + 2] = vc.z, Cc[4 * m + 3] = vc.w;
+                        }
+                    }
                     const float4 yv = gwo_quad_coef<VARIANT>(quad(ci.x + 16 * q), quad(o0 + 16 * q),
                                                              quad(o1 + 16 * q), quad(o2 + 16 * q), A, Cc);
                     quad(ci.y + 16 * q) = yv;
                     nib = below_zero_nibble(yv) & (q == Q - 1 ? tail : 15u);
                 }
-                coef(rd + 1 < rounds ? words : words_next, rd + 1 < rounds ? rd + 1 : 0, v);
+                if constexpr (!OWN) coef(rd + 1 < rounds ? words : words_next, rd + 1 < rounds ? rd + 1 : 0, v);
                 store_bits(nib, rd, i);
                 next_pair(i, q);
             }
@@ -466,8 +490,10 @@ __global__ __launch_bounds__(kFusedThreads) void fused_gen_kernel(FusedArgs a)
             // the leaders of the next generation (and those reported)
             if (!has_de) fused_leaders(fs, cur, np, sl);
         }
-        words = words_next;
-        take = take_next;
+        if constexpr (!OWN) {
+            words = words_next;
+            take = take_next;
+        }
         Fg = F_next;
     }
 
@@ -545,15 +571,28 @@ qpm_status launch_fused_generations(const FusedRun &fr, int gens, hipStream_t s)
                 "the workspace holds the random numbers of %d generations (got %d)", fr.words_gens, gens);
     const FusedWords fw = fused_words(fr.np, a.W);
     QPM_REQUIRE(fw.slots <= kFusedMaxRounds * kFusedThreads, QPM_EINVAL, "too many gene quads for one workgroup");
-    fused_words_kernel<<<dim3(kFusedThreads / 256, static_cast<unsigned>(gens)), 256, 0, s>>>(a);
-    QPM_TRY_HIP(hipGetLastError());
+    // A launch for the random numbers costs about 2.5 us, making them in one
+    // workgroup 0.7 us a generation and round. us per generation, with the launch /
+    // without, HWSDA FP64: 100 x 16 (1 round) one generation 11.6 / 9.2, three 6.0 /
+    // 5.7; 256 x 32 (2) one 16.0 / 14.8, two 11.1 / 11.6; 1000 x 16 (4) one 29.1 /
+    // 28.1; 300 x 64 (5) one 32.4 / 33.0. DE alone, 100 x 16: 9.9 / 7.4, 4.2 / 3.7.
+    const int rounds = fw.slots / kFusedThreads;
+    const bool own = gens * rounds <= (gens == 1 ? 4 : 3);
+    if (!own) {
+        fused_words_kernel<<<dim3(kFusedThreads / 256, static_cast<unsigned>(gens)), 256, 0, s>>>(a);
+        QPM_TRY_HIP(hipGetLastError());
+    }
     const bool tab_lds = fused_layout(fr.np, fr.D, a.W, true).total <= kFusedMaxLds;
     const size_t lds = fused_layout(fr.np, fr.D, a.W, tab_lds).total;
+#define QPM_FUSED_OWN(V, T, O)                                                                                   \
+    {                                                                                                            \
+        QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fused_gen_kernel<V, T, O>),              \
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));     \
+        fused_gen_kernel<V, T, O><<<1, kFusedThreads, lds, s>>>(a);                                              \
+    }
 #define QPM_FUSED(V, T)                                                                                          \
     {                                                                                                            \
-        QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fused_gen_kernel<V, T>),                 \
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));     \
-        fused_gen_kernel<V, T><<<1, kFusedThreads, lds, s>>>(a);                                                 \
+        if (own) QPM_FUSED_OWN(V, T, true) else QPM_FUSED_OWN(V, T, false)                                       \
     }
     if (fr.variant == 1) {
         if (tab_lds) QPM_FUSED(1, true) else QPM_FUSED(1, false)
@@ -561,6 +600,7 @@ qpm_status launch_fused_generations(const FusedRun &fr, int gens, hipStream_t s)
         if (tab_lds) QPM_FUSED(0, true) else QPM_FUSED(0, false)
     }
 #undef QPM_FUSED
+#undef QPM_FUSED_OWN
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }
