@@ -55,7 +55,7 @@ struct qpm_run_s {
     int de_ipw = 0;     // 0 = chosen from np
     int de_passes = 0;  // groups of individuals per DE workgroup (0 = chosen from the sizes)
     bool fused = false; // whole generations in one workgroup (fused.hip)
-    void *words = nullptr;  // fused: the random numbers of words_gens generations (after buf[1])
+    void *words = nullptr;  // fused: the random numbers of words_gens generations
     int words_gens = 0;
     hipGraph_t graph = nullptr;  // one generation
     hipGraphExec_t exec = nullptr;
@@ -106,6 +106,7 @@ static void release(qpm_run_s *r)
     (void)hipFree(r->F_base);
     (void)hipFree(r->fws);
     (void)hipFree(r->draws);
+    (void)hipFree(r->words);
     (void)hipFree(r->acc_list);
     (void)hipFree(r->acc_cnt);
     (void)hipFree(r->fbits_prev);
@@ -538,21 +539,8 @@ static qpm_status create_run(const Design *d, const Objective *obj, const qpm_ru
     hipError_t e = hipStreamCreateWithFlags(&r->st, hipStreamNonBlocking);
     // both gene buffers in one allocation (buf[1] = buf[0] + np ldx), so
     // the DE kernel can address row r of either buffer as one array
-    // (and so the fused generations' random numbers need no allocation of their
-    // own, fewer generations of them where the memory is short)
-    if (r->fused) r->words_gens = static_cast<int>(std::min<int64_t>(kFusedGens, c.generations));
-    while (e == hipSuccess) {
-        const size_t words = r->fused ? fused_words_bytes(c.np, r->D, r->words_gens) : 0;
-        e = hipMalloc(&r->buf[0], 2 * gene_bytes + words);
-        if (e != hipErrorOutOfMemory || r->words_gens <= 1) break;
-        (void)hipGetLastError();
-        r->words_gens = (r->words_gens + 1) / 2;
-        e = hipSuccess;
-    }
-    if (e == hipSuccess) {
-        r->buf[1] = r->buf[0] + c.np * r->ldx;
-        r->words = r->fused ? r->buf[1] + c.np * r->ldx : nullptr;
-    }
+    if (e == hipSuccess) e = hipMalloc(&r->buf[0], 2 * gene_bytes);
+    if (e == hipSuccess) r->buf[1] = r->buf[0] + c.np * r->ldx;
     if (e == hipSuccess) e = hipMalloc(&r->flags, sizeof(uint32_t) * c.np);
     if (e == hipSuccess) e = hipMalloc(&r->fbits, sizeof(uint32_t) * 2 * ((c.np + 63) / 64));
     if (e == hipSuccess) e = hipMalloc(&r->cand, finish_cand_bytes(c.np));
@@ -570,6 +558,16 @@ static qpm_status create_run(const Design *d, const Objective *obj, const qpm_ru
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_list, sizeof(int32_t) * c.np);
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->acc_cnt, sizeof(uint32_t));
     if (e == hipSuccess && r->lazy) e = hipMalloc(&r->fbits_prev, sizeof(uint32_t) * 2 * ((c.np + 63) / 64));
+    if (e == hipSuccess && r->fused) {
+        // (fewer generations per launch where the memory is short)
+        r->words_gens = static_cast<int>(std::min<int64_t>(kFusedGens, c.generations));
+        while (true) {
+            e = hipMalloc(&r->words, fused_words_bytes(c.np, r->D, r->words_gens));
+            if (e != hipErrorOutOfMemory || r->words_gens == 1) break;
+            (void)hipGetLastError();
+            r->words_gens = (r->words_gens + 1) / 2;
+        }
+    }
     if (e != hipSuccess) {
         set_error("run allocation failed: %s", hipGetErrorString(e));
         release(r);
