@@ -375,7 +375,9 @@ qpm_status launch_fused_generations(const FusedRun &fr, int gens, hipStream_t s)
 
 qpm_status launch_polish_step(float *theta, const float *grad, int64_t rows, int64_t n, int64_t ld, float eta,
                               hipStream_t s);
-qpm_status launch_polish_project(const float *theta, float *y, int64_t rows, int64_t n, int64_t ld, hipStream_t s);
+// rows of theta projected to y and packed, then the rows L of pv packed as they are
+qpm_status launch_polish_project(const float *theta, float *y, int64_t rows, int64_t ld, const PopView &pv,
+                                 const int32_t *L, uint32_t *bits, int64_t ldb, hipStream_t s);
 qpm_status launch_polish_accept(const float *y, int64_t n, int64_t ldy, const void *fcand, bool f64, const int32_t *L,
                                 const PopView &pv, void *f_cur, uint32_t *accepted, hipStream_t s);
 

@@ -29,6 +29,7 @@
 // FP64 in both precisions (FP64 costs what FP32 does on this chip without
 // packed FP32 instructions).
 #include "common.hpp"
+#include "genes.hpp"
 
 namespace qpm {
 
@@ -661,13 +662,25 @@ __global__ __launch_bounds__(256) void polish_step_kernel(float *__restrict__ th
 }
 
 // y = clamp(theta, -1, 1): the +-1 projection keeps the sign of theta and
-// is a valid gene row
+// is a valid gene row; its bit words, and in the columns after them those of
+// the leaders as they are (one launch: a polish of no steps is four short kernels
+// and a wait). Grid: x = chunks of 1024 genes, y = leader.
 __global__ __launch_bounds__(256) void polish_project_kernel(const float *__restrict__ theta, float *__restrict__ y,
-                                                             int64_t n, int64_t ld)
+                                                             int64_t ld, PopView pv, const int32_t *__restrict__ L,
+                                                             uint32_t *__restrict__ bits, int64_t ldb)
 {
-    const int64_t r = blockIdx.y;
-    for (int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; k < n; k += 256 * gridDim.x)
-        y[r * ld + k] = fminf(fmaxf(theta[r * ld + k], -1.0f), 1.0f);
+    const int64_t r = blockIdx.y, rows = gridDim.y;
+    const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, j0 = 4 * q;
+    uint32_t projected = 0, present = 0;
+    if (j0 < pv.D) {
+        const float4 t = *reinterpret_cast<const float4 *>(theta + (r * ld + j0));
+        const float4 v = make_float4(clamp1(t.x), clamp1(t.y), clamp1(t.z), clamp1(t.w));
+        *reinterpret_cast<float4 *>(y + (r * ld + j0)) = v;
+        projected = quad_nibble(v, j0, pv.D);
+        present = quad_nibble(*reinterpret_cast<const float4 *>(row_of(pv, L[r]) + j0), j0, pv.D);
+    }
+    store_word(projected, q, pv.D, bits, ldb, r);
+    store_word(present, q, pv.D, bits, ldb, rows + r);
 }
 
 // For each of the three leaders: keep the projected row when its exact +-1
@@ -704,11 +717,11 @@ qpm_status launch_polish_step(float *theta, const float *grad, int64_t rows, int
     return QPM_OK;
 }
 
-qpm_status launch_polish_project(const float *theta, float *y, int64_t rows, int64_t n, int64_t ld, hipStream_t s)
+qpm_status launch_polish_project(const float *theta, float *y, int64_t rows, int64_t ld, const PopView &pv,
+                                 const int32_t *L, uint32_t *bits, int64_t ldb, hipStream_t s)
 {
-    const int64_t bx = (n + 255) / 256;
-    polish_project_kernel<<<dim3(static_cast<unsigned>(bx < 64 ? bx : 64), static_cast<unsigned>(rows)), 256, 0, s>>>(
-        theta, y, n, ld);
+    polish_project_kernel<<<dim3(static_cast<unsigned>((pv.D + 1023) / 1024), static_cast<unsigned>(rows)), 256, 0,
+                            s>>>(theta, y, ld, pv, L, bits, ldb);
     QPM_TRY_HIP(hipGetLastError());
     return QPM_OK;
 }

@@ -885,15 +885,13 @@ QPM_API qpm_status qpm_run_polish(qpm_run_handle r, int32_t steps, float eta, in
     auto *dh = const_cast<qpm_design_s *>(static_cast<const qpm_design_s *>(r->d));
     const PopView pv = r->view();
     qpm_status st = launch_gather(pv, r->leaders, 3, theta, ldx, r->st);
-    if (st == QPM_OK) st = launch_pack_pop(theta, 3, D, ldx, r->pol_bits + 3, 64, r->st);
     for (int32_t k = 0; k < steps && st == QPM_OK; ++k) {
         st = qpm_relax_forward(dh, p, theta, 3, ldx, r->pol_f, r->pol_S, r->pol_edges, r->st);
         if (st == QPM_OK)
             st = qpm_relax_backward(dh, p, theta, 3, ldx, r->pol_S, r->pol_edges, r->pol_f + 3, grad, ldx, r->st);
         if (st == QPM_OK) st = launch_polish_step(theta, grad, 3, D, ldx, eta, r->st);
     }
-    if (st == QPM_OK) st = launch_polish_project(theta, y, 3, D, ldx, r->st);
-    if (st == QPM_OK) st = launch_pack_pop(y, 3, D, ldx, r->pol_bits, 64, r->st);
+    if (st == QPM_OK) st = launch_polish_project(theta, y, 3, ldx, pv, r->leaders, r->pol_bits, 64, r->st);
     // the run's own plan, so that an accepted fitness is the sum its evaluations make
     if (st == QPM_OK) st = launch_fitness(*r->d, p, r->pol_bits, 6, 64, r->pol_fc, r->plan, r->pol_ws, r->st);
     if (st == QPM_OK) {
