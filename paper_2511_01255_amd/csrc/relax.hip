@@ -594,9 +594,9 @@ relax_bwd_kernel(const float *__restrict__ theta, int64_t ldt, int64_t B,
             const int64_t r = rg * 64 + step * 16 + (lane >> 2), k = kc + col;
             if (r < B) {
                 float *dst = grad_theta + (r * ldg + k);
-                if (inside) {
+                if (inside || k + 3 < n) {
                     *reinterpret_cast<float4u *>(dst) = float4u{v[0], v[1], v[2], v[3]};
-                } else {
+                } else if (k < n) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (k + e < n) dst[e] = v[e];
