@@ -297,8 +297,8 @@ def _whole_rows(x, D):
     they need no clearing or copying first: a plain population of the usual
     row length. Other layouts keep the cleared and copied results."""
     import torch
-    return (type(x) is torch.Tensor and x.dtype == torch.float32 and x.is_contiguous() and not x.requires_grad
-            and x.shape[1] == ldx_for(D))
+    return (x.shape[1] == ldx_for(D) and type(x) is torch.Tensor and x.dtype == torch.float32 and x.is_contiguous()
+            and not x.requires_grad)
 
 
 def de_step(x, D, F, CR, seed, generation, inst=0, stream=None, shape=None):
