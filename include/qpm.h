@@ -147,9 +147,11 @@ qpm_status qpm_eval_fitness(qpm_design d, qpm_prec p, const uint32_t *bits, int6
  * ends; the call allocates and frees nothing. Every call on a device shares
  * that device's array, so calls that overlap on one device (other streams,
  * other threads) race; the caller orders them. Errors: as qpm_eval_fitness,
- * and QPM_ERANGE when the population needs more than 16 MiB of partials
- * (6 doubles per genome column ld and workgroup segment; the 4096 x 10^4
- * fitness workload needs 3.1 MB).
+ * and QPM_ERANGE when the partials of the table kernel at 4 bit words per wave
+ * (QPM_PREC_F32) or 2 (QPM_PREC_F64), or those of the kernel asked for, pass 16
+ * MiB: 6 doubles per genome column ld and workgroup segment of 4 waves, none for
+ * a single segment. The limit is the same for every launch plan, also where the
+ * plan chosen needs less (the 4096 x 10^4 fitness workload: 3.9 MB in FP32).
  */
 qpm_status qpm_eval_fitness_noalloc(qpm_design d, qpm_prec p, const uint32_t *bits, int64_t np,
                                     int64_t ld, void *fitness, int32_t kernel, qpm_stream s);

@@ -9,7 +9,6 @@
 
 namespace qpm {
 
-
 // The segment partials of every call on a device: each device that runs the
 // library holds its own copy until the process ends. Host code reaches it
 // only through the per-device address from hipGetSymbolAddress (the name
@@ -71,16 +70,17 @@ QPM_API qpm_status qpm_eval_fitness_noalloc(qpm_design d, qpm_prec p, const uint
                 "population too large");
     const FitPlan pl = plan_fitness(*d, p, np, kernel, ld);
     QPM_REQUIRE(pl.gy <= 65535, QPM_ERANGE, "too many workgroup segments (%d)", pl.gy);
-    // the limit does not move with the launch shape: 4 words per wave in FP32, 2 in
-    // FP64, of which no plan needs more
+    // the limit does not move with the launch shape, also where a short design needs no
+    // partials: those of 4 words per wave in FP32, 2 in FP64, of which no plan needs more
+    const size_t need = fitness_workspace_bytes(pl, ld);
     const FitPlan most = pl.kind == QPM_FIT_TABLE ? plan_fitness_table(*d, p, 1, p == QPM_PREC_F32 ? 4 : 2) : pl;
-    const size_t bytes = std::max(fitness_workspace_bytes(pl, ld), fitness_workspace_bytes(most, ld));
+    const size_t bytes = std::max(need, fitness_workspace_bytes(most, ld));
     QPM_REQUIRE(bytes <= kNoAllocScratchBytes, QPM_ERANGE,
-                "this population needs %zu bytes of segment partials, more than the %zu of the fixed scratch "
+                "rows of this length take up to %zu bytes of segment partials, more than the %zu of the fixed scratch "
                 "(use qpm_eval_fitness)",
                 bytes, kNoAllocScratchBytes);
     void *ws = nullptr;
-    if (bytes > 0) {
+    if (need > 0) {
         const qpm_status st = scratch_address(&ws);
         if (st != QPM_OK) return st;
     }
