@@ -605,12 +605,13 @@ QPM_API qpm_status qpm_eval_objective(qpm_objective o, qpm_prec p, const uint32_
     // Few words: one launch, which walks up to table_max_wpw words per wave and
     // writes the values itself, unless the longer walks of K THG designs cost more
     // than that launch. us per call back to back / with a wait after each, two
-    // launches against one: 500 x 1000 SHG FP32, 1 design 11.4 / 22.0 against 9.2 /
-    // 19.6, 8 designs 11.9 / 27.7 against 11.1 / 26.8; 640 x 256, 8 designs 11.9 /
-    // 27.7 against 12.0 / 27.0; 100 x 300, 8 THG designs (1 word per wave) 17.9 /
-    // 33.6 against 13.5 / 29.3, 256 x 100, 3 THG designs (2 words) 11.4 / 25.0
-    // against 9.1 / 23.4. Table of partials by words, above: 3 THG designs of 5
-    // words instead of 1 walk 7.7 us longer than their values launch took.
+    // launches against one, NP = 100 (2000 is alike), by K x words per wave. SHG FP32:
+    // 1 x 2 12.2 / 22.4 against 8.9 / 19.2, 8 x 3 12.2 / 26.4 against 9.6 / 25.2, 8 x 5
+    // 12.3 / 26.3 against 11.8 / 27.6. THG: 3 x 2 12.0 / 25.1 against 8.9 / 24.3, 4 x 2
+    // 12.1 / 26.5 against 10.7 / 26.4 (FP64 12.2 / 27.0 against 11.6 / 27.2), 2 x 3 12.3
+    // / 23.8 against 8.9 / 23.7, 5 x 2 even (8 words, NP = 1000 FP64 13.3 against 14.4,
+    // 5 words, NP = 5000 14.5 against 12.3); but 3 x 3 12.1 / 25.3 against 10.8 / 26.4,
+    // 4 x 3 12.1 / 26.6 against 13.5 / 29.1, 6 x 2 13.8 / 29.8 against 15.1 / 30.7.
     const int wpw = static_cast<int>(std::min<int64_t>((o->words + 3) / 4, table_max_wpw(p == QPM_PREC_F32) + 1));
     if (wpw <= table_max_wpw(p == QPM_PREC_F32) && (o->kind != QPM_OBJ_THG || o->K * (wpw - 1) <= 5))
         pl = plan_objective_shape(*o, wpw);
