@@ -223,14 +223,15 @@ __global__ __launch_bounds__(1024) void batch_finish_kernel(int mode, const doub
                     mode == 3 ? db : nullptr, gen, n, k0, k1, instb, accb, 0u);
 }
 
-// the leaders of instance blockIdx.x from its groups' candidates
+// the leaders of instance blockIdx.x from its groups' candidates (3 of each 64
+// genomes: at most 192)
 template <typename T>
 __global__ __launch_bounds__(64) void batch_leaders_kernel(const T *__restrict__ cand_v,
                                                            const int32_t *__restrict__ cand_i, int64_t groups,
                                                            int32_t *__restrict__ leaders)
 {
     const int64_t b = blockIdx.x;
-    merge_leaders<T, 64>(cand_v + b * 3 * groups, cand_i + b * 3 * groups, 3 * groups, leaders + 3 * b);
+    merge_few_leaders<T>(cand_v + b * 3 * groups, cand_i + b * 3 * groups, 3 * groups, leaders + 3 * b);
 }
 
 // ---------------------------------------------------------------- evolution
@@ -338,11 +339,11 @@ __global__ __launch_bounds__(256) void batch_materialize_kernel(BatchPop bp, con
     if (blockIdx.x == 0 && tl.chunk == 0) {
         const int64_t n3 = 3 * ((bp.np + 63) / 64);
         if (cand_f64)
-            merge_leaders<double, 256>(static_cast<const double *>(cand_v) + tl.inst * n3, cand_i + tl.inst * n3, n3,
-                                       leaders + 3 * tl.inst);
-        else
-            merge_leaders<float, 256>(static_cast<const float *>(cand_v) + tl.inst * n3, cand_i + tl.inst * n3, n3,
+            merge_few_leaders<double>(static_cast<const double *>(cand_v) + tl.inst * n3, cand_i + tl.inst * n3, n3,
                                       leaders + 3 * tl.inst);
+        else
+            merge_few_leaders<float>(static_cast<const float *>(cand_v) + tl.inst * n3, cand_i + tl.inst * n3, n3,
+                                     leaders + 3 * tl.inst);
     }
     const int64_t np = bp.np;
     const uint32_t n_acc = min(cnt[tl.inst], static_cast<uint32_t>(np));

@@ -217,19 +217,27 @@ __device__ void block_top3(const T *__restrict__ f, int64_t n, int32_t *__restri
     }
 }
 
-// The leaders from n candidates (cv[j], ci[j]), by a workgroup of NT lanes: up
-// to 256 of them by its first wave alone.
+// The leaders from n <= 256 candidates (cv[j], ci[j]), by the first wave of a
+// workgroup.
+template <typename T>
+__device__ __forceinline__ void merge_few_leaders(const T *__restrict__ cv, const int32_t *__restrict__ ci, int64_t n,
+                                                  int32_t *__restrict__ out)
+{
+    if (threadIdx.x >= 64) return;
+    const int lane = static_cast<int>(threadIdx.x), m = static_cast<int>(n);
+    const int b = m <= 64 ? wave_best3_of<T, 1>(cv, ci, m, lane) : wave_best3_of<T, 4>(cv, ci, m, lane);
+    if (lane < 3) out[lane] = b;
+}
+
+// The same of any number of candidates, by a workgroup of NT lanes
 template <typename T, int NT>
 __device__ __forceinline__ void merge_leaders(const T *__restrict__ cv, const int32_t *__restrict__ ci, int64_t n,
                                               int32_t *__restrict__ out)
 {
-    if (n > 256) {
+    if (n > 256)
         block_top3<T, NT>(cv, n, out, ci);
-    } else if (threadIdx.x < 64) {
-        const int lane = static_cast<int>(threadIdx.x), m = static_cast<int>(n);
-        const int b = m <= 64 ? wave_best3_of<T, 1>(cv, ci, m, lane) : wave_best3_of<T, 4>(cv, ci, m, lane);
-        if (lane < 3) out[lane] = b;
-    }
+    else
+        merge_few_leaders<T>(cv, ci, n, out);
 }
 
 }  // namespace qpm

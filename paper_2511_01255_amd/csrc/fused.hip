@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void fused_words_kernel(FusedArgs a)
 // 2300 cycles with 8 lanes, 2550 with 16)
 constexpr int kFusedLanes = 8;
 
-// the value of lane l + OFF (OFF in {1, 2, 4, 8}) of the same 16-lane row, by
+// the value of lane l + OFF (OFF in {1, 2, 4}) of the same 16-lane row, by
 // DPP row shifts (lanes past the row's end read 0; they are not used)
 template <int OFF>
 __device__ __forceinline__ double row_down(double v)
@@ -254,11 +254,10 @@ __device__ __forceinline__ void fused_fitness(const FusedArgs &a, const FusedLay
         }
     }
     // fold the T triples of each genome in block order
-    static_assert(T == 8 || T == 16, "a genome's lanes lie in one DPP row");
+    static_assert(T == 8, "a genome's lanes lie in one DPP row, folded in three levels");
     fold_level<1>(t);
     fold_level<2>(t);
     fold_level<4>(t);
-    if constexpr (T == 16) fold_level<8>(t);
     if (i < np && s == 0) {
         const double sr = t.qr + Cr, si = t.qi + Ci;
         double fnew = fma(sr, sr, si * si);

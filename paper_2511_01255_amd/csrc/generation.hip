@@ -44,7 +44,7 @@ __global__ __launch_bounds__(64 * NR) void finish_kernel(const double *__restric
     // candidates, as the tail kernel would take them, without that launch
     if (top3_direct != nullptr) {
         __syncthreads();
-        merge_leaders<T, 64 * NR>(cand_v, cand_i, 3, top3_direct);
+        merge_few_leaders<T>(cand_v, cand_i, 3, top3_direct);
     }
 }
 

@@ -438,10 +438,8 @@ __device__ __forceinline__ void gwo_rows(const PopView &pv, int i0, int64_t q, i
     if ((threadIdx.x & 7) == 7 && 4 * (q & ~int64_t(7)) < D) {
         uint32_t *const b = bits + ((q >> 3) * ld + i0);
         if (plain || whole) {
-            if constexpr (R == 4)
-                *reinterpret_cast<uint4u *>(b) = uint4u{w[0], w[1], w[2], w[3]};
-            else
-                for (int r = 0; r < R; ++r) b[r] = w[r];
+            static_assert(R == 4, "the individuals' words are one 16-byte store");
+            *reinterpret_cast<uint4u *>(b) = uint4u{w[0], w[1], w[2], w[3]};
         } else {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
