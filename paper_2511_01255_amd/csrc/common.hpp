@@ -123,7 +123,7 @@ struct FitPlan {
     int waves = 16;                // waves per workgroup (segmented) or genome groups (table)
     int wpw = 2;                   // bit words per wave
     int gy = 1;                    // workgroup segments along the domain axis
-    bool direct = false;           // launch_fitness walks all segments in one workgroup (no partials)
+    bool direct = false;           // launch_fitness walks all (<= 3) segments in one workgroup (no partials)
 };
 
 constexpr size_t kNoAllocScratchBytes = size_t(16) << 20;  // the fixed scratch of qpm_eval_fitness_noalloc
@@ -298,7 +298,7 @@ __host__ __device__ constexpr int table_max_wpw(bool f32) { return f32 ? 5 : 2; 
 // wave that a plan takes
 constexpr int kTabPlanWords = 16;
 // LDS of one table-kernel workgroup (tables, reused for the combine)
-size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw, bool staged = false);
+size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw);
 // DE draws of generation *gen_dev for every individual
 qpm_status launch_draws(int64_t np, int64_t D, uint64_t seed, const uint32_t *gen_dev, uint32_t inst, int4 *draws,
                         hipStream_t s);

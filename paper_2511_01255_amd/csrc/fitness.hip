@@ -146,9 +146,8 @@ __global__ __launch_bounds__(128) void fit_per_genome_kernel(const uint32_t *__r
 // order. FP32: the word's A and B summed exactly in fixed point, its Q in
 // binary32, each word's triple folded into FP64 (word_tab_q); FP64:
 // binary64 throughout.
-// STAGED: 1, segments of more words than table_max_wpw; 2, every segment of a
-// short design one after the other (tab_segment_staged); 3, side by side, GW of
-// them (tab_segment).
+// STAGED: 1, segments of more words than table_max_wpw (tab_segment_staged); 2,
+// the GW segments of a short design side by side, then its fitness.
 template <bool F32, int GW, int STAGED>
 __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__restrict__ bits, int64_t ld, int W,
                                                            const double2 *__restrict__ tab64,
@@ -163,13 +162,13 @@ __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__res
     // read the counter (the finish step after it reads the new value)
     if (advance != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) advance[0] += 1u;
     const int wbase = static_cast<int>(blockIdx.y) * 4 * wpw;
-    const int64_t i = (STAGED == 3 ? static_cast<int64_t>(blockIdx.x)
+    const int64_t i = (STAGED == 2 ? static_cast<int64_t>(blockIdx.x)
                                    : static_cast<int64_t>(blockIdx.x) * GW + (threadIdx.x >> 8)) * 64 + (threadIdx.x & 63);
     Tri t;
-    if constexpr (STAGED == 3) {
+    if constexpr (STAGED == 2) {
         if (!tab_segment<F32, GW, true>(t, bits, ld, W, 0, tab64, tabq, wsc, wpw, np, lds)) return;
-    } else if constexpr (STAGED != 0) {
-        if (!tab_segment_staged<F32, GW, STAGED == 2>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
+    } else if constexpr (STAGED == 1) {
+        if (!tab_segment_staged<F32, GW>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
     } else {
         if (!tab_segment<F32, GW>(t, bits, ld, W, wbase, tab64, tabq, wsc, wpw, np, lds)) return;
     }
@@ -186,26 +185,25 @@ __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__res
     }
 }
 
-// Designs of at most this many words: one workgroup walks all their segments and
-// writes the fitness itself, so that nothing is launched after it; segment by segment
-// in the order of the fold, so that the bits are those of a run's evaluation and its
-// finish step. Side by side (4 waves each, every table in LDS) while a workgroup
-// takes one group of genomes, else one after the other. us per call back to
-// back / with a wait after each, two launches against one that walked a single
-// segment (both precisions, NP = 64 to 5000), and side by side (NP = 300):
+// Designs of at most this many words: one workgroup walks all their segments, side
+// by side (4 waves each, every table in LDS), and writes the fitness itself, so that
+// nothing is launched after it; the segments are folded in the order of a run's
+// finish step, whose bits it gives. us per call back to back / with a wait after
+// each, two launches against one that walked a single segment (both precisions, NP
+// = 64 to 5000):
 //   N =  640 (20 words): FP32 10.0 / 21.0, 7.2 / 20.0; FP64 10.0 / 21.0, 7.2 / 21.2
 //   N =  800 (25):       FP32 9.9 / 21.0, 7.2 / 21.7;  FP64 9.9 / 21.0, 8.1 / 22.7
 //   N = 1280 (40):       FP32 10.0 / 21.2, 8.8 / 23.5; FP64 9.9 / 21.2, 10.7 / 25.2
-//   N =  640, single segment / one after the other / side by side, with a wait:
-//                        FP32 21.1 / 23.4 / 20.4, FP64 22.4 / 24.2 / 20.7
+// and N = 640, NP = 300 with a wait, one segment / three side by side (one after
+// the other in a workgroup of 4 waves): FP32 21.1 / 20.4 (23.4), FP64 22.4 / 20.7 (24.2)
 constexpr int64_t kDirectWords = 20;
 // the most segments that one workgroup walks to the end (FitPlan::direct)
 constexpr int kDirectSegments = 3;
 
-size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw, bool staged)
+size_t table_lds_bytes(int64_t W, bool f32, int gw, int wpw)
 {
     const int64_t words = std::min<int64_t>(W, 4 * static_cast<int64_t>(wpw));
-    const size_t tab = staged || wpw > table_max_wpw(f32) ? 2 * (f32 ? TabStage<true>::kBytes : TabStage<false>::kBytes)
+    const size_t tab = wpw > table_max_wpw(f32) ? 2 * (f32 ? TabStage<true>::kBytes : TabStage<false>::kBytes)
                                                 : static_cast<size_t>(words) * 8 * 48 * (f32 ? 8 : 16);
     const size_t comb = static_cast<size_t>(gw) * 4 * 64 * 6 * 8;
     return std::max(tab, comb);
@@ -217,21 +215,18 @@ static qpm_status launch_tab(const Design &d, const FitPlan &pl, const uint32_t 
                              uint32_t *advance = nullptr)
 {
     const int gw = pl.waves;
-    const bool many = direct_ok && pl.direct && pl.gy > 1;
-    const dim3 grid(static_cast<unsigned>((np + 64 * gw - 1) / (64 * gw)), static_cast<unsigned>(many ? 1 : pl.gy));
-    const int direct = direct_ok && (many || pl.gy == 1);
+    const bool side = direct_ok && pl.direct && pl.gy > 1;  // the segments side by side
+    const dim3 grid(static_cast<unsigned>((np + 64 * gw - 1) / (64 * gw)), static_cast<unsigned>(side ? 1 : pl.gy));
+    const int direct = direct_ok && (side || pl.gy == 1);
     const int W = static_cast<int>(d.words);
-    const bool side = many && gw == 1;  // the segments side by side
     const size_t lds = side ? std::max<size_t>(static_cast<size_t>(W) * 8 * 48 * (F32 ? 8 : 16), pl.gy * 4 * 64 * 6 * 8)
-                            : table_lds_bytes(d.words, F32, gw, pl.wpw, many);
+                            : table_lds_bytes(d.words, F32, gw, pl.wpw);
 #define QPM_TAB_KERNEL(G, ST)                                                                                 \
     fit_tab_kernel<F32, G, ST><<<grid, dim3(G * 256), lds, s>>>(bits, ld, W, d.tab64, d.tabq, d.wsc, pl.wpw, np,  \
                                                                 part, d.Cdev, fit, direct, out_f64, advance)
 #define QPM_TAB_CASE(G)                                                                                       \
     case G:                                                                                                   \
-        if (many)                                                                                             \
-            QPM_TAB_KERNEL(G, 2);                                                                             \
-        else if (pl.wpw > table_max_wpw(F32))                                                                 \
+        if (pl.wpw > table_max_wpw(F32))                                                                 \
             QPM_TAB_KERNEL(G, 1);                                                                             \
         else                                                                                                  \
             QPM_TAB_KERNEL(G, 0);                                                                             \
@@ -239,9 +234,9 @@ static qpm_status launch_tab(const Design &d, const FitPlan &pl, const uint32_t 
     if (side) {
         static_assert(kDirectSegments == 3, "two or three segments side by side");
         if (pl.gy == 2)
-            QPM_TAB_KERNEL(2, 3);
+            QPM_TAB_KERNEL(2, 2);
         else
-            QPM_TAB_KERNEL(3, 3);
+            QPM_TAB_KERNEL(3, 2);
         return QPM_OK;
     }
     switch (gw) {
@@ -295,9 +290,9 @@ qpm_status prepare_fitness(const Design &d)
 {
     const int lds = static_cast<int>(d.words * 8 * 48 * 16);
     if (d.words > kDirectWords || lds <= 65536) return QPM_OK;
-    QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fit_tab_kernel<false, 2, 3>),
+    QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fit_tab_kernel<false, 2, 2>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kFusedMaxLds));
-    QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fit_tab_kernel<false, 3, 3>),
+    QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fit_tab_kernel<false, 3, 2>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kFusedMaxLds));
     return QPM_OK;
 }
@@ -359,7 +354,9 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel, int64_
     if (kernel == QPM_FIT_AUTO || kernel == QPM_FIT_TABLE) {
         int gw, wpw;
         table_shape(p == QPM_PREC_F32, np, d.words, &gw, &wpw);
-        wpw = std::min(wpw, static_cast<int>((d.words + 3) / 4));
+        // one segment, of a short design, where a workgroup takes several genome groups
+        const int all = static_cast<int>(std::min<int64_t>((d.words + 3) / 4, kTabPlanWords));
+        wpw = d.words <= kDirectWords && gw > 1 ? all : std::min(wpw, all);
         pl = plan_fitness_table(d, p, gw, wpw);
         for (int w = wpw; w <= std::max(wpw, kFoldWords); ++w) {
             const FitPlan q = plan_fitness_table(d, p, gw, w);
@@ -368,7 +365,8 @@ FitPlan plan_fitness(const Design &d, qpm_prec p, int64_t np, int kernel, int64_
                 break;
             }
         }
-        pl.direct = d.words <= kDirectWords && pl.gy <= kDirectSegments;
+        pl.direct = d.words <= kDirectWords &&
+                    (pl.gy == 1 || (gw == 1 && pl.gy <= kDirectSegments && pl.wpw <= table_max_wpw(p == QPM_PREC_F32)));
         // few genomes in wide rows: no more partials than 4 words per wave leave,
         // where the fixed scratch holds only those
         if (p == QPM_PREC_F32 && pl.wpw < 4 && fitness_workspace_bytes(pl, ld) > kNoAllocScratchBytes)

@@ -383,10 +383,7 @@ struct TabStage {
 // designs of up to 5 x 10^4 domains, NP = 256, FP32 63.6 + 9.1 -> 56.2 + 6.6, FP64
 // 76 + 19 -> 66 + 6. Short segments gain nothing and pay for the stages (2000 x
 // 500 FP32: 4.1 -> 4.5).
-// MANY (wbase 0): the design's two or three segments one after the other, each
-// folded by its waves and then appended to those before it, as a fold of so few
-// segments does (kDirectWords).
-template <bool F32, int GW, bool MANY = false>
+template <bool F32, int GW>
 __device__ __forceinline__ bool tab_segment_staged(Tri &t, const uint32_t *__restrict__ bits, int64_t ld, int W, int wbase,
                                             const double2 *__restrict__ tab64, const int2 *__restrict__ tabq,
                                             const double *__restrict__ wsc, int wpw, int64_t np, unsigned char *lds)
@@ -400,26 +397,25 @@ __device__ __forceinline__ bool tab_segment_staged(Tri &t, const uint32_t *__res
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int gsub = wave / SW, ssub = wave % SW;
     const int64_t i = (static_cast<int64_t>(blockIdx.x) * GW + gsub) * 64 + lane;
-    const int nw = MANY ? W : min(W - wbase, SW * wpw);  // >= 1 by the grid
+    const int nw = min(W - wbase, SW * wpw);  // >= 1 by the grid
     const uint4 *const tabs =
         F32 ? reinterpret_cast<const uint4 *>(tabq) : reinterpret_cast<const uint4 *>(tab64);
     const bool live = i < np;
-    const int w0 = ssub * wpw;
+    const int w0 = ssub * wpw, w1 = min(nw, w0 + wpw);
     const int64_t ic = i < ld ? i : ld - 1;
     uint32_t next[WS];
-    // stage k of the segment at word `at`: words at + s wpw + k WS .. of every
-    // wave s, straight to LDS (16 bytes per lane per load, no registers, no wait
-    // between loads)
-    auto issue = [&](int at, int k, int half) {
-        unsigned char *const to = lds + half * Stage::kBytes;
+    // stage k: words s wpw + k WS .. of every segment s, straight to LDS (16
+    // bytes per lane per load, no registers, no wait between loads)
+    auto issue = [&](int k) {
+        unsigned char *const to = lds + (k & 1) * Stage::kBytes;
 #pragma unroll
         for (int u = 0; u < (SW * PIECE + NT - 1) / NT; ++u) {
             const int idx = u * NT + static_cast<int>(threadIdx.x);
             const int s = idx / PIECE, in = idx % PIECE;
-            const int w = at + s * wpw + k * WS + in / (PIECE / WS);  // the unit's word
-            if (idx < SW * PIECE && w < min(nw, at + (s + 1) * wpw))
+            const int w = s * wpw + k * WS + in / (PIECE / WS);  // the unit's word
+            if (idx < SW * PIECE && w < min(nw, (s + 1) * wpw))
                 __builtin_amdgcn_global_load_lds(
-                    tabs + (static_cast<int64_t>(wbase + at + s * wpw + k * WS) * (PIECE / WS) + in),
+                    tabs + (static_cast<int64_t>(wbase + s * wpw + k * WS) * (PIECE / WS) + in),
                     reinterpret_cast<__attribute__((address_space(3))) void *>(
                         reinterpret_cast<uintptr_t>(to + static_cast<size_t>(u * NT + wave * 64) * 16)),
                     16, 0, 0);
@@ -427,17 +423,13 @@ __device__ __forceinline__ bool tab_segment_staged(Tri &t, const uint32_t *__res
         // this wave's bit words (clamped addresses, so every load is in
         // bounds and none is branched around)
 #pragma unroll
-        for (int j = 0; j < WS; ++j)
-            next[j] = bits[static_cast<int64_t>(min(wbase + at + w0 + k * WS + j, W - 1)) * ld + ic];
+        for (int j = 0; j < WS; ++j) next[j] = bits[static_cast<int64_t>(min(wbase + w0 + k * WS + j, W - 1)) * ld + ic];
     };
-    issue(0, 0, 0);
+    issue(0);
     t = Tri{0, 0, 0, 0, 0, 0};
-    Tri done[2] = {t, t};  // MANY: this wave's share of the segments before the last
-    const int stages = (min(wpw, nw) + WS - 1) / WS;  // of a segment, the same in every wave
-    const int total = MANY ? stages * ((nw + SW * wpw - 1) / (SW * wpw)) : stages;
-    int at = 0, k = 0;
+    const int stages = (min(wpw, nw) + WS - 1) / WS;  // the same in every wave
 #pragma unroll 1
-    for (int st = 0; st < total; ++st) {
+    for (int k = 0; k < stages; ++k) {
         // this stage's loads have arrived in every wave, and every wave is
         // done with the half the next ones go to
         __builtin_amdgcn_s_waitcnt(0);
@@ -445,14 +437,11 @@ __device__ __forceinline__ bool tab_segment_staged(Tri &t, const uint32_t *__res
         uint32_t wv[WS];
 #pragma unroll
         for (int j = 0; j < WS; ++j) wv[j] = live ? next[j] : 0u;
-        const bool last = MANY && k + 1 == stages;  // of the segment
-        const int at_next = last ? at + SW * wpw : at, k_next = last ? 0 : k + 1;
-        if (st + 1 < total) issue(at_next, k_next, (st + 1) & 1);
-        const unsigned char *const from = lds + (st & 1) * Stage::kBytes + ssub * (PIECE * 16);
-        const int w1 = min(nw, at + w0 + wpw);
+        if (k + 1 < stages) issue(k + 1);
+        const unsigned char *const from = lds + (k & 1) * Stage::kBytes + ssub * (PIECE * 16);
 #pragma unroll
         for (int j = 0; j < WS; ++j) {
-            const int wr = at + w0 + k * WS + j;
+            const int wr = w0 + k * WS + j;
             if (wr >= w1) break;
             const uint32_t word = wv[j];
             if constexpr (F32) {
@@ -472,38 +461,8 @@ __device__ __forceinline__ bool tab_segment_staged(Tri &t, const uint32_t *__res
                 }
             }
         }
-        if constexpr (MANY) {
-            if (last && st + 1 < total) {
-                if (at == 0)
-                    done[0] = t;
-                else
-                    done[1] = t;
-                t = Tri{0, 0, 0, 0, 0, 0};
-            }
-        }
-        at = at_next;
-        k = k_next;
     }
-    if constexpr (MANY) {
-        const int seg = SW * wpw, before = (nw - 1) / seg;  // segments before the last: 0, 1 or 2
-        Tri sum{0, 0, 0, 0, 0, 0};
-        if (before > 0) {
-            fold_segment_waves<GW>(done[0], wpw, seg, gsub, ssub, wave, lane, live, lds);
-            sum = done[0];
-        }
-        if (before > 1) {
-            fold_segment_waves<GW>(done[1], wpw, seg, gsub, ssub, wave, lane, live, lds);
-            tri_append(sum, done[1]);
-        }
-        if (!fold_segment_waves<GW>(t, wpw, nw - before * seg, gsub, ssub, wave, lane, live, lds)) return false;
-        if (before > 0) {
-            tri_append(sum, t);
-            t = sum;
-        }
-        return true;
-    } else {
-        return fold_segment_waves<GW>(t, wpw, nw, gsub, ssub, wave, lane, live, lds);
-    }
+    return fold_segment_waves<GW>(t, wpw, nw, gsub, ssub, wave, lane, live, lds);
 }
 
 }  // namespace qpm

@@ -30,7 +30,7 @@ def _bits(x):
 @pytest.mark.parametrize("prec", [1, 0])
 @pytest.mark.parametrize("n,npop", [(128, 80), (300, 70), (500, 1000), (640, 300), (641, 300), (2000, 500),
                                     (7680, 130), (12224, 86), (12472, 86), (13000, 200), (20000, 300), (30000, 130),
-                                    (31000, 80), (10000, 1300), (49999, 1001)])
+                                    (31000, 80), (10000, 1300), (49999, 1001), (640, 19264), (600, 38500)])
 def test_run_fitness_equals_the_call(q, n, npop, prec):
     D = q.precompute_phases(inputs.jittered_boundaries(n, 2.0, 0.2, seed=n), inputs.DK1, inputs.DK2)
     R = q.Run(D, npop, 4, seed=5, prec=prec, fused=-1)
