@@ -1,5 +1,6 @@
-"""The default launch shapes of the table fitness at the sizes where they change:
-256 and 12,000 wave words of work, 6,000 in FP64, 8 and 16 genome groups.
+"""The default launch shapes of the table fitness over the sizes where they change
+(12,000 wave words of work, 8 and 16 genome groups, 20 words; the other lines are
+bracketed in test_gpu_fitness_lines.py).
 Tolerances are the fitness's own (FP64 1e-12, FP32 1e-5, plain or against 1 % of
 the median below it)."""
 import numpy as np
