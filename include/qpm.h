@@ -36,9 +36,9 @@
  *     64-bit seed; the counter is (c0, individual, generation,
  *     instance << 8 | stream tag), so every draw depends only on its
  *     coordinates, never on launch shape.
- *   - Scratch: the evaluation entry points on a design or an objective
- *     (fitness, objective, relaxation) keep their device scratch with that
- *     handle between calls, one buffer per stream handle for up to 4
+ *   - Scratch: the evaluation entry points on a design, an objective or a
+ *     batch (fitness, objective, relaxation) keep their device scratch with
+ *     that handle between calls, one buffer per stream handle for up to 4
  *     streams, freed with the handle. Successive
  *     uses of a buffer are ordered by its stream, and one host lock per
  *     handle covers a call's enqueueing, so calls from several streams and
@@ -599,7 +599,10 @@ qpm_status qpm_batch_info(qpm_batch b, int32_t *n_inst, int64_t *n_domains, doub
  * (instance-major). With waves_per_group = words_per_wave = 0 the
  * sign-pattern table kernel runs with its default shape; otherwise the
  * per-domain kernel with waves_per_group in {0 (default), 4, 8, 16} and
- * words_per_wave >= 0 (0 = default).
+ * words_per_wave >= 0 (0 = default). The work tables of up to 8 launch shapes
+ * stay with the batch until it is freed; the first call of a shape uploads
+ * them and synchronises s, so only a shape used before can be captured (and
+ * the batch must outlive the graph).
  */
 qpm_status qpm_batch_eval_fitness(qpm_batch b, qpm_prec p, const uint32_t *bits, int64_t np,
                                   int64_t ld, void *fitness, int32_t waves_per_group,
