@@ -162,8 +162,8 @@ __global__ __launch_bounds__(GW * 256) void fit_tab_kernel(const uint32_t *__res
     // read the counter (the finish step after it reads the new value)
     if (advance != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) advance[0] += 1u;
     const int wbase = static_cast<int>(blockIdx.y) * 4 * wpw;
-    const int64_t i = (STAGED == 2 ? static_cast<int64_t>(blockIdx.x)
-                                   : static_cast<int64_t>(blockIdx.x) * GW + (threadIdx.x >> 8)) * 64 + (threadIdx.x & 63);
+    const int64_t group = STAGED == 2 ? blockIdx.x : static_cast<int64_t>(blockIdx.x) * GW + (threadIdx.x >> 8);
+    const int64_t i = group * 64 + (threadIdx.x & 63);
     Tri t;
     if constexpr (STAGED == 2) {
         if (!tab_segment<F32, GW, true>(t, bits, ld, W, 0, tab64, tabq, wsc, wpw, np, lds)) return;
@@ -226,7 +226,7 @@ static qpm_status launch_tab(const Design &d, const FitPlan &pl, const uint32_t 
                                                                 part, d.Cdev, fit, direct, out_f64, advance)
 #define QPM_TAB_CASE(G)                                                                                       \
     case G:                                                                                                   \
-        if (pl.wpw > table_max_wpw(F32))                                                                 \
+        if (pl.wpw > table_max_wpw(F32))                                                                      \
             QPM_TAB_KERNEL(G, 1);                                                                             \
         else                                                                                                  \
             QPM_TAB_KERNEL(G, 0);                                                                             \
@@ -288,8 +288,7 @@ FitPlan plan_fitness_table(const Design &d, qpm_prec p, int gw, int wpw)
 
 qpm_status prepare_fitness(const Design &d)
 {
-    const int lds = static_cast<int>(d.words * 8 * 48 * 16);
-    if (d.words > kDirectWords || lds <= 65536) return QPM_OK;
+    if (d.words > kDirectWords || d.words * 8 * 48 * 16 <= 65536) return QPM_OK;
     QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fit_tab_kernel<false, 2, 2>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kFusedMaxLds));
     QPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fit_tab_kernel<false, 3, 2>),
